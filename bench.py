@@ -53,16 +53,17 @@ PEAK_HBM_GBS = 8000.0
 FLOPS_PER_PAIR = {"pass_density_force": 38, "pass_viscous_integrate": 34}
 # Algorithmic HBM bytes per launch of each kernel of a step: (per particle, per cell-table entry).
 # Neighbour data re-read by the pair passes is reuse through the caches, not algorithmic traffic.
-#  radix_hist: the key; radix_scatter: key and value read and written; reorder_field: the
-#  permutation, key, offsets, flags and id read (32 B), key, position + h, flags and id written
-#  (28 B), the cell table written; pair passes: the particle's own key, position and flags (24 B)
+#  cell_scan: the counts read, the cell table written; cell_place: key, arrival number, cell start
+#  and slot (28 B, the arrival number with its 16-byte offset word), the counts cleared;
+#  reorder_field: slot, key, cell range, offsets, flags and id read (40 B), key, position + h, flags,
+#  id and source index written (32 B); pair passes: the particle's own key, position and flags (24 B)
 #  and the cell table read, a written (16 B); the viscous pass also reads a and the id (20 B)
 #  and writes the new state (28 B).
-KERNEL_BYTES = {"radix_hist": (4, 0), "radix_scatter": (16, 0), "reorder_field": (60, 4),
+KERNEL_BYTES = {"cell_scan": (0, 8), "cell_place": (28, 4), "reorder_field": (72, 0),
                 "pass_density_force": (40, 4), "pass_viscous_integrate": (72, 4)}
 TRAFFIC_DIR = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1906_07925_amd", "csrc", f)
-                  for f in ("mpsph.hip", "mpsph_device.h", "pair_scan.h", "adjoint.h", "sort.hip", "sort.h")]
+                  for f in ("mpsph.hip", "mpsph_device.h", "pair_scan.h", "adjoint.h", "sort.hip", "sort.h", "cells.hip", "cells.h")]
 
 
 def kernel_source_digest() -> str:
@@ -316,7 +317,7 @@ def mesh_run(torch, M, W, steps: int = 50, warmup: int = 20):
     R.close()
     launches, ms = kern["reorder_field"]
     avg_s = ms / launches / 1e3
-    gather_bytes = 56.0 * n + 4.0 * ncells
+    gather_bytes = 72.0 * n
     gbs = gather_bytes / avg_s / 1e9
     print(f"[bench] mesh: 2^{k} cells per axis, {lanes} lanes (autotuned): {1e3 * dt / steps:.2f} ms/step, "
           f"field gather {1e3 * avg_s:.3f} ms", file=sys.stderr, flush=True)
@@ -324,8 +325,8 @@ def mesh_run(torch, M, W, steps: int = 50, warmup: int = 20):
             "cell_log2": k, "lanes": lanes, "autotuned": True,
             "ms_per_step": 1e3 * dt / steps, "field_gather_ms": 1e3 * avg_s,
             "field_gather_roofline": {"bound": "hbm", "achieved": gbs, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                                      "frac": gbs / PEAK_HBM_GBS, "bytes_per_particle": 56, "cells": ncells,
-                                      "bytes_per_cell": 4},
+                                      "frac": gbs / PEAK_HBM_GBS, "bytes_per_particle": 72, "cells": ncells,
+                                      "bytes_per_cell": 0},
             "n_feature": m["n_feature"], "nonfinite": m["nonfinite"]}
 
 

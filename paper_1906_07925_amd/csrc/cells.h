@@ -1,0 +1,25 @@
+// Host interface of the counting order of the particles by cell key.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "sort.h"
+
+namespace mpsph {
+
+// Entries of the count array for ncells cells: whole tiles of the scan, the rest zero.
+size_t cell_count_words(uint32_t ncells);
+// Words of the tile sums.
+size_t cell_sum_words(uint32_t ncells);
+
+// Counts the particles per cell from their keys: counts[key] over all particles and each
+// particle's arrival number in its cell (the bits of off[i].w).  counts is all zero on entry.
+hipError_t count_cells(const uint32_t *keys, float4 *off, uint32_t *counts, int n, hipStream_t stream);
+
+// From the counts and arrival numbers: the cell table cstart[c] = particles in cells below c
+// (c <= ncells), and the particles grouped by cell, slots[s] for s in [cstart[c], cstart[c + 1])
+// naming those of cell c in an unspecified order.  Leaves counts all zero.  Enqueued on stream.
+hipError_t cell_order(const uint32_t *keys, const float4 *off, uint32_t *counts, uint32_t *sums, uint32_t *cstart,
+                      uint32_t *slots, int n, uint32_t ncells, hipStream_t stream, LaunchHook *hook);
+
+}  // namespace mpsph

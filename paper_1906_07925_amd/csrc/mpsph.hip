@@ -46,6 +46,7 @@
 #include "mpsph.h"
 #include "mpsph_device.h"
 #include "adjoint.h"
+#include "cells.h"
 #include "pair_scan.h"
 #include "sort.h"
 
@@ -57,6 +58,14 @@ namespace {
 // Kernels
 // ------------------------------------------------------------------------------------------
 
+// Counts a particle into its new cell and returns its arrival number there as the bits of a float
+// (kept in the offset's fourth word); counts is null when the context sorts by radix instead.
+// The atomics make the viscous pass of 2M particles 22 us longer, with or without the answer;
+// taking the arrival numbers in cell_place instead costs 34 us more there.
+__device__ __forceinline__ float count_arrival(uint32_t *counts, uint32_t key) {
+  return counts ? __uint_as_float(atomicAdd(&counts[key], 1u)) : 0.f;
+}
+
 // Domain units -> (cell, offset) in FP64 (identical inputs give identical keys), validation.
 // Internal particles [i0, i1) of one dimension group.
 template <int D>
@@ -64,7 +73,8 @@ __global__ __launch_bounds__(kBlock) void load_kernel(const DomDev *__restrict__
                                                       const float *__restrict__ pos, const int32_t *__restrict__ colour,
                                                       const int32_t *__restrict__ type, uint32_t *__restrict__ key,
                                                       float4 *__restrict__ off, uint32_t *__restrict__ ct,
-                                                      uint32_t *__restrict__ id, int *__restrict__ bad) {
+                                                      uint32_t *__restrict__ id, uint32_t *__restrict__ counts,
+                                                      int *__restrict__ bad) {
   const int i = i0 + blockIdx.x * kBlock + threadIdx.x;
   if (i >= i1) return;
   const DomDev &dd = doms[domain_of(doms, ndom, i)];
@@ -92,8 +102,9 @@ __global__ __launch_bounds__(kBlock) void load_kernel(const DomDev *__restrict__
   const int t = type ? type[u] : 0;
   if (col < 0 || col >= (1 << 16) || t < 0 || t > 3) ok = false;
   if (!ok) atomicOr(bad, 1);
-  key[i] = dd.cellbase + pack_key<D>(c, o, dd.g);
-  off[i] = make_float4(o[0], o[1], D == 3 ? o[2] : 0.f, 0.f);
+  const uint32_t kk = dd.cellbase + pack_key<D>(c, o, dd.g);
+  key[i] = kk;
+  off[i] = make_float4(o[0], o[1], D == 3 ? o[2] : 0.f, count_arrival(counts, kk));
   ct[i] = (uint32_t)(t & 3) | ((uint32_t)col << 2);
   id[i] = (uint32_t)u;
 }
@@ -134,6 +145,25 @@ __global__ __launch_bounds__(256) void fill_gaps(const uint4 *__restrict__ gaps,
   }
 }
 
+// Particle s of the state to sorted index i: the field evaluated, the working arrays written.
+template <int D>
+__device__ __forceinline__ void gather_particle(const DomDev &dd, uint32_t s, int i, uint32_t key,
+                                                const float4 *__restrict__ soff, const uint32_t *__restrict__ sct,
+                                                const uint32_t *__restrict__ sid, uint32_t *__restrict__ wkey,
+                                                float4 *__restrict__ wpos, uint32_t *__restrict__ wjaux,
+                                                uint32_t *__restrict__ wid) {
+  const float4 o4 = soff[s];
+  const uint32_t ct = sct[s];
+  int c[3];
+  unpack_key<D>(key - dd.cellbase, dd.g, c);
+  const float o[3] = {o4.x, o4.y, o4.z};
+  const float spc = field_spacing<D>(dd.f, c, o);
+  wkey[i] = key;
+  wpos[i] = make_float4(o4.x, o4.y, o4.z, dd.sp.tau * spc);
+  wjaux[i] = pack_aux((uint32_t)c[0], ct & 3u, ct >> 2);
+  wid[i] = sid[s];
+}
+
 // Gather the state in sorted order, evaluate the size field (h = tau s, Eq. 16) and build the
 // cell table: cstart[c] = first sorted index with key >= c, cstart[ncells] = n.  Sorted keys are
 // grouped by domain, so the sorted range of domain d is [off_d, off_d + n_d); one launch covers
@@ -163,19 +193,32 @@ __global__ __launch_bounds__(kBlock) void reorder_field(
     for (uint32_t c = lo; c <= hi; ++c) cstart[c] = (uint32_t)i;
   }
   if (i == n) return;
-  const DomDev &dd = doms[domain_of(doms, ndom, i)];
-  const uint32_t s = perm[i];
-  const uint32_t key = skey[i];
-  const float4 o4 = soff[s];
-  const uint32_t ct = sct[s];
-  int c[3];
-  unpack_key<D>(key - dd.cellbase, dd.g, c);
-  const float o[3] = {o4.x, o4.y, o4.z};
-  const float spc = field_spacing<D>(dd.f, c, o);
-  wkey[i] = key;
-  wpos[i] = make_float4(o4.x, o4.y, o4.z, dd.sp.tau * spc);
-  wjaux[i] = pack_aux((uint32_t)c[0], ct & 3u, ct >> 2);
-  wid[i] = sid[s];
+  gather_particle<D>(doms[domain_of(doms, ndom, i)], perm[i], i, skey[i], soff, sct, sid, wkey, wpos, wjaux, wid);
+}
+
+// The gather of a context that orders its particles by counting (cells.h), whose cell table is
+// complete before it: slot i names one of its cell's particles, whose place in the cell is its
+// rank by index among the cell's slots (a cell's particles are all candidates of one another, so
+// the ranking is small against the pair passes whatever the occupancy).
+template <int D>
+__global__ __launch_bounds__(kBlock) void reorder_cells(
+    const DomDev *__restrict__ doms, int ndom, int i0, int i1, int nreset, const uint32_t *__restrict__ slots,
+    const uint32_t *__restrict__ cstart, const uint32_t *__restrict__ skey, const float4 *__restrict__ soff,
+    const uint32_t *__restrict__ sct, const uint32_t *__restrict__ sid, uint32_t *__restrict__ wkey,
+    float4 *__restrict__ wpos, uint32_t *__restrict__ wjaux, uint32_t *__restrict__ wid, uint32_t *__restrict__ perm,
+    uint32_t *__restrict__ dtslots) {
+  const int t = blockIdx.x * kBlock + threadIdx.x;
+  if (t < nreset) dtslots[t] = kInfBits;
+  const int i = i0 + t;
+  if (i >= i1) return;
+  const uint32_t s = slots[i];
+  const uint32_t key = skey[s];
+  const uint32_t a = cstart[key], b = cstart[key + 1u];
+  uint32_t at = a;
+  if (b - a > 1u)
+    for (uint32_t q = a; q < b; ++q) at += slots[q] < s ? 1u : 0u;
+  perm[at] = s;
+  gather_particle<D>(doms[domain_of(doms, ndom, i)], s, (int)at, key, soff, sct, sid, wkey, wpos, wjaux, wid);
 }
 
 // Pass 1: density (Eq. 17, self term included, radius kappa h_i) and
@@ -635,10 +678,10 @@ __device__ __forceinline__ int type_from_faces(int nf, int d) {
   const DomDev *__restrict__ doms, int ndom, const uint32_t *__restrict__ wkey, const float4 *__restrict__ wpos, \
       const uint32_t *__restrict__ wjaux, const uint32_t *__restrict__ wid, const uint32_t *__restrict__ cstart,  \
       const float4 *__restrict__ acc, const uint32_t *__restrict__ dtslots, uint32_t *__restrict__ skey,         \
-      float4 *__restrict__ soff, uint32_t *__restrict__ sct, uint32_t *__restrict__ sid, float4 *__restrict__ at_out, \
-      float4 *__restrict__ v_out, float4 *__restrict__ dr_out, double *__restrict__ partials
+      float4 *__restrict__ soff, uint32_t *__restrict__ sct, uint32_t *__restrict__ sid, uint32_t *__restrict__ counts, \
+      float4 *__restrict__ at_out, float4 *__restrict__ v_out, float4 *__restrict__ dr_out, double *__restrict__ partials
 #define MPSPH_PASS2_ARGS \
-  doms, ndom, wkey, wpos, wjaux, wid, cstart, acc, dtslots, skey, soff, sct, sid, at_out, v_out, dr_out, partials
+  doms, ndom, wkey, wpos, wjaux, wid, cstart, acc, dtslots, skey, soff, sct, sid, counts, at_out, v_out, dr_out, partials
 // One logical block lb of the pass; PIPE as for density_force_block.
 template <int D, int L, bool PER, bool PIPE>
 __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, MPSPH_PASS2_PARAMS) {
@@ -887,8 +930,9 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, M
           o[a] = 0.f;
         }
       }
-      skey[io] = cellbase + pack_key<D>(c, o, g);
-      soff[io] = make_float4(o[0], o[1], D == 3 ? o[2] : 0.f, 0.f);
+      const uint32_t kk = cellbase + pack_key<D>(c, o, g);
+      skey[io] = kk;
+      soff[io] = make_float4(o[0], o[1], D == 3 ? o[2] : 0.f, count_arrival(counts, kk));
       sct[io] = (uint32_t)ti | (aux_colour(ai) << 2);
       sid[io] = wid[io];
       if (at_out) at_out[io] = make_float4(b[0], b[1], b[2], 0.f);
@@ -1956,7 +2000,13 @@ struct Layout {
   int64_t chunk = 1;  // block partials per first-level reduction row
   size_t n_rbf = 0;
   size_t bytes = 0;
-  size_t s_key, s_off, s_ct, s_id, w_key, w_pos, w_jaux, w_id, k0, v0, k1, v1, hist, cstart, acc, rho, nn, aabs, at, v,
+  // particles ordered by counting into the cell table (cells.h) instead of a radix sort: tables of
+  // at most 8 cells per particle (what the size rule gives), whose scan costs less than the
+  // sort's passes (order and gather of 4096 particles 9.4 us a step against 54, of 262,144 25 against
+  // 98, of 2M with 4M cells 56 + 22 in the viscous pass against 133).  A caller's much finer table is
+  // mostly empty: there the sort touches it once, the scan three times
+  bool counted = false;
+  size_t s_key, s_off, s_ct, s_id, w_key, w_pos, w_jaux, w_id, k0, v0, k1, v1, hist, counts, sums, cstart, acc, rho, nn, aabs, at, v,
       dr, partials, partials2, groups, metrics, dtslots, stepctr, bad, paircount, queue, doms, vscale, rbf_c, rbf_o, rbf_k,
       gphi, gs, gaps, gcount;
 };
@@ -2048,14 +2098,17 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   L.w_pos = take(nn * 16);
   L.w_jaux = take(nn * 4);
   L.w_id = take(nn * 4);
-  L.k0 = take(nn * 4);
-  L.v0 = take(nn * 4);
-  L.k1 = take(nn * 4);
-  L.v1 = take(nn * 4);
-  L.hist = take(radix_hist_words((int)n) * 4);
+  L.counted = cells <= 8 * (uint64_t)std::max<int64_t>(n, 64);
+  const size_t nr = L.counted ? 0 : nn;      // the arrays of one of the two orders only
+  L.k0 = take(nr * 4);
+  L.v0 = take(nr * 4);
+  L.k1 = take(nr * 4);
+  L.v1 = take(nr * 4);
+  L.hist = take(L.counted ? 0 : radix_hist_words((int)n) * 4);
   L.cstart = take(((size_t)L.ncells + 1) * 4);
-  L.gaps = take((nn + 1) * sizeof(uint4));   // at most one empty-cell run per sorted particle
+  L.gaps = take(L.counted ? 0 : (nn + 1) * sizeof(uint4));   // at most one empty-cell run per sorted particle
   L.gcount = take(8);                       // run count, finished blocks of fill_gaps
+  L.sums = take(L.counted ? cell_sum_words(L.ncells) * 4 : 0);
   L.acc = take(nn * 16);
   L.rho = take(nn * 4);
   L.nn = take(nn * 4);
@@ -2066,10 +2119,12 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   L.partials = take((size_t)std::max(L.nblocks_pair, 1) * kNumPartials * 8);
   L.partials2 = take((size_t)std::max(L.nrows, 1) * kNumPartials * 8);
   L.groups = take((size_t)std::max(L.nrows, 1) * sizeof(int2));
+  // what a load clears, in one range: metrics, step counter, validation flag, cell counts
   L.metrics = take((size_t)L.ndom * 32 * 8);
-  L.dtslots = take((size_t)L.ndom * kDtSlots * 4);
   L.stepctr = take(8);
   L.bad = take(4);
+  L.counts = take(L.counted ? cell_count_words(L.ncells) * 4 : 0);
+  L.dtslots = take((size_t)L.ndom * kDtSlots * 4);
   L.paircount = take(8);
   L.queue = take(32 * 4);                   // work queues of the persistent pair passes (2 x 16 words)
   L.doms = take((size_t)L.ndom * sizeof(DomDev));
@@ -2223,6 +2278,29 @@ int fail(mpsph_ctx *c, int code) {
     if ((expr) != hipSuccess) return fail(ctx, MPSPH_E_DEVICE); \
   } while (0)
 
+// Scratch of the counting order: the slots and the sorted order's source indices, in the
+// acceleration array, which the density pass writes only after both were read.
+uint32_t *slots_of(mpsph_ctx *ctx) { return ctx->at<uint32_t>(ctx->L.acc); }
+uint32_t *perm_of(mpsph_ctx *ctx) { return ctx->at<uint32_t>(ctx->L.acc) + std::max<int64_t>(ctx->L.n, 1); }
+
+// Orders the state by cell key: the sorted keys (radix sort only) and, after launch_group, the
+// source index of every sorted position.
+hipError_t order_state(mpsph_ctx *ctx, hipStream_t st, const uint32_t **skeys, const uint32_t **perm, LaunchHook *hk) {
+  const Layout &L = ctx->L;
+  const int n = (int)L.n;
+  if (!L.counted)
+    return radix_sort(ctx->at<uint32_t>(L.s_key), ctx->at<uint32_t>(L.k0), ctx->at<uint32_t>(L.v0),
+                      ctx->at<uint32_t>(L.k1), ctx->at<uint32_t>(L.v1), ctx->at<uint32_t>(L.hist), n, L.key_bits, st,
+                      skeys, perm, hk);
+  *skeys = nullptr;
+  *perm = perm_of(ctx);
+  return cell_order(ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.counts),
+                    ctx->at<uint32_t>(L.sums), ctx->at<uint32_t>(L.cstart), slots_of(ctx), n, L.ncells, st, hk);
+}
+
+// The cell counts the integrator and the load write (null: radix sort).
+uint32_t *counts_of(mpsph_ctx *ctx) { return ctx->L.counted ? ctx->at<uint32_t>(ctx->L.counts) : nullptr; }
+
 // Kernels of one step for one dimension group.
 template <int D>
 void launch_group(mpsph_ctx *ctx, const Group &gr, const uint32_t *skeys, const uint32_t *perm, int nreset,
@@ -2231,6 +2309,16 @@ void launch_group(mpsph_ctx *ctx, const Group &gr, const uint32_t *skeys, const 
   const int n = (int)L.n;
   const DomDev *doms = ctx->at<DomDev>(L.doms) + gr.d0;
   if (hk) hk->begin("reorder_field");
+  if (L.counted) {
+    const int nt = std::max(gr.i1 - gr.i0, nreset);
+    reorder_cells<D><<<(nt + kBlock - 1) / kBlock, kBlock, 0, st>>>(
+        doms, gr.nd, gr.i0, gr.i1, nreset, slots_of(ctx), ctx->at<uint32_t>(L.cstart), ctx->at<uint32_t>(L.s_key),
+        ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.w_key),
+        ctx->at<float4>(L.w_pos), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), perm_of(ctx),
+        ctx->at<uint32_t>(L.dtslots));
+    if (hk) hk->end();
+    return;
+  }
   const int nthr = std::max(gr.i1 - gr.i0 + (gr.i1 == n ? 1 : 0), nreset);
   reorder_field<D><<<(nthr + kBlock - 1) / kBlock, kBlock, 0, st>>>(
       doms, gr.nd, gr.i0, gr.i1, n, L.ncells, nreset, skeys, perm, ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct),
@@ -2280,7 +2368,7 @@ void launch_pass2_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st, float4 *at_
       gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos),
       ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart), ctx->at<float4>(L.acc),
       ctx->at<uint32_t>(L.dtslots) + (size_t)gr.d0 * kDtSlots, ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
-      ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), at_o, v_o, dbg ? ctx->at<float4>(L.dr) : nullptr,
+      ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), counts_of(ctx), at_o, v_o, dbg ? ctx->at<float4>(L.dr) : nullptr,
       ctx->at<double>(L.partials));
 }
 
@@ -2330,7 +2418,7 @@ void launch_pass2_queue_l(mpsph_ctx *ctx, int b0, int nb2, int nb, hipStream_t s
       b0, nb2, nb, ctx->at<uint32_t>(L.queue) + 16, ctx->at<DomDev>(L.doms), L.ndom, ctx->at<uint32_t>(L.w_key),
       ctx->at<float4>(L.w_pos), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),
       ctx->at<float4>(L.acc), ctx->at<uint32_t>(L.dtslots), ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
-      ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), dbg ? ctx->at<float4>(L.at) : nullptr,
+      ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), counts_of(ctx), dbg ? ctx->at<float4>(L.at) : nullptr,
       dbg ? ctx->at<float4>(L.v) : nullptr, dbg ? ctx->at<float4>(L.dr) : nullptr, ctx->at<double>(L.partials));
 }
 
@@ -2375,9 +2463,7 @@ int enqueue(mpsph_ctx *ctx, int nsteps, hipStream_t st, EventHook *hk) {
   for (int s = 0; s < nsteps; ++s) {
     if (n > 0) {
       const uint32_t *skeys = nullptr, *perm = nullptr;
-      if (radix_sort(ctx->at<uint32_t>(L.s_key), ctx->at<uint32_t>(L.k0), ctx->at<uint32_t>(L.v0),
-                     ctx->at<uint32_t>(L.k1), ctx->at<uint32_t>(L.v1), ctx->at<uint32_t>(L.hist), n, L.key_bits, st,
-                     &skeys, &perm, hk) != hipSuccess)
+      if (order_state(ctx, st, &skeys, &perm, hk) != hipSuccess)
         return fail(ctx, MPSPH_E_DEVICE);
       int nreset = ndom * kDtSlots;  // the first launch resets every domain's time-step slots
       for (const Group &gr : L.grp) {
@@ -2686,6 +2772,11 @@ int copy_state(GradRun &R, int k, bool save) {
     void *cp = c + off_ck[a];
     HIP_OK(hipMemcpyAsync(save ? cp : ws, save ? ws : cp, sz[a], hipMemcpyDeviceToDevice, R.st));
   }
+  // a restored state's cell counts: those of the state it replaces go
+  if (!save && L.counted) {
+    HIP_OK(hipMemsetAsync(ctx->at<uint32_t>(L.counts), 0, cell_count_words(L.ncells) * 4, R.st));
+    HIP_OK(count_cells(ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.counts), (int)L.n, R.st));
+  }
   return MPSPH_OK;
 }
 
@@ -2696,12 +2787,11 @@ int record_step(GradRun &R, int m) {
   const Layout &L = ctx->L;
   const int n = (int)L.n;
   const uint32_t *skeys = nullptr, *perm = nullptr;
-  if (radix_sort(ctx->at<uint32_t>(L.s_key), ctx->at<uint32_t>(L.k0), ctx->at<uint32_t>(L.v0), ctx->at<uint32_t>(L.k1),
-                 ctx->at<uint32_t>(L.v1), ctx->at<uint32_t>(L.hist), n, L.key_bits, R.st, &skeys, &perm,
-                 nullptr) != hipSuccess)
+  if (order_state(ctx, R.st, &skeys, &perm, nullptr) != hipSuccess)
     return fail(ctx, MPSPH_E_DEVICE);
   char *b = R.tp(m);
   launch_group<D>(ctx, *R.gr, skeys, perm, kDtSlots, R.st, nullptr);
+  HIP_OK(hipMemcpyAsync(b + R.P.tp_perm, perm, (size_t)n * 4, hipMemcpyDeviceToDevice, R.st));
   launch_pass1<D>(ctx, *R.gr, R.st, nullptr);
   launch_pass2<D>(ctx, *R.gr, R.st, nullptr, reinterpret_cast<float4 *>(b + R.P.tp_at),
                   reinterpret_cast<float4 *>(b + R.P.tp_v));
@@ -2712,7 +2802,6 @@ int record_step(GradRun &R, int m) {
                                 ctx->at<double>(L.metrics), ctx->at<int64_t>(L.stepctr));
   HIP_OK(hipGetLastError());
   const size_t nn = (size_t)n;
-  HIP_OK(hipMemcpyAsync(b + R.P.tp_perm, perm, nn * 4, hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_wkey, ctx->at<uint32_t>(L.w_key), nn * 4, hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_wpos, ctx->at<float4>(L.w_pos), nn * 16, hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_wjaux, ctx->at<uint32_t>(L.w_jaux), nn * 4, hipMemcpyDeviceToDevice, R.st));
@@ -2732,9 +2821,7 @@ int loss_backward(GradRun &R, double lam) {
   const int n = (int)L.n;
   const DomDev *dom = ctx->at<DomDev>(L.doms);
   const uint32_t *skeys = nullptr, *perm = nullptr;
-  if (radix_sort(ctx->at<uint32_t>(L.s_key), ctx->at<uint32_t>(L.k0), ctx->at<uint32_t>(L.v0), ctx->at<uint32_t>(L.k1),
-                 ctx->at<uint32_t>(L.v1), ctx->at<uint32_t>(L.hist), n, L.key_bits, R.st, &skeys, &perm,
-                 nullptr) != hipSuccess)
+  if (order_state(ctx, R.st, &skeys, &perm, nullptr) != hipSuccess)
     return fail(ctx, MPSPH_E_DEVICE);
   launch_group<D>(ctx, *R.gr, skeys, perm, kDtSlots, R.st, nullptr);
   const int nbp = R.nbp;
@@ -3130,15 +3217,13 @@ int mpsph_load(mpsph_ctx *ctx, const float *d_pos, const int32_t *d_colour, cons
   const Layout &L = ctx->L;
   const int n = (int)L.n;
   if (n > 0 && (!d_pos || !d_colour)) return MPSPH_E_INVALID;
-  HIP_OK(hipMemsetAsync(ctx->at<int>(L.bad), 0, 4, ctx->stream));
-  HIP_OK(hipMemsetAsync(ctx->at<double>(L.metrics), 0, (size_t)L.ndom * 32 * 8, ctx->stream));
-  HIP_OK(hipMemsetAsync(ctx->at<int64_t>(L.stepctr), 0, 8, ctx->stream));
+  HIP_OK(hipMemsetAsync(ctx->ws + L.metrics, 0, L.dtslots - L.metrics, ctx->stream));
   for (const Group &gr : L.grp) {
     if (gr.i1 <= gr.i0) continue;
     auto kern = gr.D == 2 ? load_kernel<2> : load_kernel<3>;
     kern<<<(gr.i1 - gr.i0 + kBlock - 1) / kBlock, kBlock, 0, ctx->stream>>>(
         ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, gr.i0, gr.i1, d_pos, d_colour, d_type, ctx->at<uint32_t>(L.s_key),
-        ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<int>(L.bad));
+        ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), counts_of(ctx), ctx->at<int>(L.bad));
     HIP_OK(hipGetLastError());
   }
   int bad = 0;
