@@ -21,9 +21,10 @@
 // (time is unchanged; the EOS constant is scaled by cs^(d-2) to make this exact).
 //
 // Launch sequence of one step (all on the context stream, no host synchronisation):
-//   radix sort of the keys (3 kernels per digit of at most 8 bits)
-//   reorder_field   gather the state in key order, evaluate the target field (Eq. 1-2, 16), fill
-//                   the cell table
+//   cell_scan, cell_place   cell table and cell order from the counts that the load and the integrator
+//                   keep (cells.hip); a radix sort of the keys for tables much larger than n
+//   reorder_cells   gather the state in key order, evaluate the target field (Eq. 1-2, 16)
+//                   (reorder_field after a radix sort: the cell table too)
 //   pass_density_force  density (Eq. 17), pressure + surface tension (Eq. 18-19, 23-25),
 //                   projection (Eq. 30-31), first time step (Eq. 29, block minima); like the
 //                   viscous pass, a lane group per particle walks its candidates through a row
@@ -31,7 +32,8 @@
 //   pass_viscous_integrate  mid-point velocity (Eq. 26), viscosity (Eq. 21-22), viscous
 //                   acceleration (Eq. 20), second time step (Eq. 29), velocity (Eq. 27), drift
 //                   (Eq. 28), feature projection and re-tagging (Eq. 32)
-//   reduce_partials, finalize   FP64 reduction of the per-block partials in a fixed order
+//   finalize        FP64 reduction of the per-block partials in a fixed order (small grids: at the end
+//                   of pass_viscous_integrate)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -666,6 +668,117 @@ __device__ __forceinline__ int type_from_faces(int nf, int d) {
   return nf <= 0 ? 0 : (nf == 1 ? 1 : (nf == 2 ? (d == 3 ? 2 : 3) : 3));
 }
 
+// Combine partials slot by slot: sums, or min / max for the slots that hold extrema.
+__device__ __forceinline__ double combine_slot(int s, double a, double b) {
+  return (s == P_EMAX || s == P_ELRMAX) ? fmax(a, b) : (s == P_ELRMIN ? fmin(a, b) : a + b);
+}
+__device__ __forceinline__ double slot_identity(int s) { return s == P_ELRMIN ? INFINITY : 0.0; }
+
+// End of a domain's step by one thread, after the slots 0..15 of its metrics block md are known: 16: dt1,
+// 17: dt2, 18..20: running totals of pairs, candidates and steps, then the automatic t0.  stepctr
+// (may be null) is the context's step counter, advanced with its first domain.
+__device__ __forceinline__ void close_domain_step(const DomDev &dd, const uint32_t *dtslots, double *md, double pairs,
+                                                  double cand, double ifc, double ifcp, int64_t *stepctr) {
+  float d1 = INFINITY;
+  for (int s = 0; s < kDtSlots; ++s) d1 = fminf(d1, __uint_as_float(dtslots[s]));
+  md[16] = d1 < INFINITY ? (double)d1 : 0.0;
+  md[17] = d1 < INFINITY ? (double)(d1 * dd.sp.dt2_factor) : 0.0;
+  // running totals since the last load (exact integers below 2^53)
+  md[18] += pairs;
+  md[19] += cand;
+  md[20] += 1.0;
+  // automatic t0 (reading of the paper's "topology static for some iterations"): the
+  // interface-pair count and the number of particles with an interface pair stay within
+  // t0_tol of a reference for t0_window steps; otherwise the reference restarts here
+  const StepDev &sp = dd.sp;
+  if (sp.auto_t0 && !(md[kAutoT0] > 0.0)) {
+    const double t = md[20] - 1.0;  // index of this step since the load
+    const double I = ifc * 0.5, P = ifcp;
+    const double tol = (double)sp.t0_tol;
+    if (t == 0.0 || fabs(I - md[kAutoT0 + 1]) > tol * md[kAutoT0 + 1] ||
+        fabs(P - md[kAutoT0 + 2]) > tol * md[kAutoT0 + 2]) {
+      md[kAutoT0 + 1] = I;
+      md[kAutoT0 + 2] = P;
+      md[kAutoT0 + 3] = t;
+    } else if (t - md[kAutoT0 + 3] >= (double)sp.t0_window) {
+      md[kAutoT0] = t + 1.0;
+    }
+  }
+  if (stepctr) *stepctr += 1;
+}
+
+// The step's end: the block partials of each domain reduced to its metrics block, its step closed.
+// Contexts whose domains all have at most kFusedChunk pair-kernel blocks close it inside the viscous
+// pass: the last block of a domain to finish reduces the domain's partials.  The others launch
+// finalize after it, one block per reduction row; the last row of a domain reduces the domain's rows.
+// (The viscous pass of larger grids gains nothing from closing the step: every block waits about
+// 2 us for its counter, 5 % of a block's life in each round of blocks.)  All sums run in a fixed
+// order, so the result does not depend on which block does them.
+struct StepEnd {
+  int d0;             // first domain of the launch (doms, metrics and dtslots start there)
+  uint32_t *domdone;  // finished blocks (or rows) per domain, zero between steps
+  double *metrics;
+  int64_t *stepctr;
+};
+
+// What another block of the same launch may have written: read at agent scope (past this XCD's L2).
+__device__ __forceinline__ double agent_load(const double *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void agent_store(double *p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Whether the calling block is the last of `total` to get here.  The first wave's agent-scope stores
+// before the call are complete when the counter moves.  lds: one word.
+__device__ __forceinline__ bool last_to_finish(uint32_t *counter, uint32_t total, uint32_t *lds) {
+  if (threadIdx.x < kWave) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (threadIdx.x == 0) *lds = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __syncthreads();
+  const bool last = *lds == total - 1u;
+  if (last) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (threadIdx.x == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return last;
+}
+
+// Rows [0, n) of kNumPartials slots combined in a fixed order; the result of slot s in thread s < kNumPartials.
+// red: kBlock doubles of LDS, free after the next barrier.
+__device__ __forceinline__ double combine_rows(const double *rows, int n, double *red) {
+  const int s = threadIdx.x & (kNumPartials - 1), r0 = threadIdx.x / kNumPartials;
+  double acc = slot_identity(s);
+#pragma unroll 4
+  for (int r = r0; r < n; r += kBlock / kNumPartials) acc = combine_slot(s, acc, agent_load(&rows[(size_t)r * kNumPartials + s]));
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  acc = red[s];
+#pragma unroll 1
+  for (int q = 1; q < kBlock / kNumPartials; ++q) acc = combine_slot(s, acc, red[q * kNumPartials + s]);
+  return acc;
+}
+
+// One of the `total` partial rows of domain d (at rows) is stored, by agent-scope stores of the first
+// wave; the last one to get here closes the domain's step.  Called by every thread of the block.
+// red: kBlock + 1 doubles of LDS, not in use by any wave.
+__device__ __forceinline__ void close_step(const StepEnd &fin, const DomDev &dd, int d, const double *rows, int total,
+                                           const uint32_t *dtslots, double *red) {
+  if (!last_to_finish(fin.domdone + fin.d0 + d, (uint32_t)total, reinterpret_cast<uint32_t *>(red + kBlock))) return;
+  const double x = combine_rows(rows, total, red);
+  double *md = fin.metrics + (size_t)d * 32;
+  __syncthreads();
+  if (threadIdx.x < kNumPartials) {
+    md[threadIdx.x] = x;
+    red[threadIdx.x] = x;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    close_domain_step(dd, dtslots + d * kDtSlots, md, red[P_PAIRS], red[P_CAND], red[P_IFC], red[P_IFCP],
+                      fin.d0 + d == 0 ? fin.stepctr : nullptr);
+}
+
 // Pass 2: viscous acceleration (Eq. 20 with rho = rho_t, Eq. 22)
 //   a~_i = sum_j [2 eta_i eta_j / (eta_i + eta_j)] (1/rho_t,i^2 + 1/rho_t,j^2) dW(r_ij,h_ij)/dr v~_ij / r_ij
 // over the same pairs as pass 1, with the mid-point velocity v~ = a dt1 / 2 (Eq. 26 after the
@@ -679,11 +792,13 @@ __device__ __forceinline__ int type_from_faces(int nf, int d) {
       const uint32_t *__restrict__ wjaux, const uint32_t *__restrict__ wid, const uint32_t *__restrict__ cstart,  \
       const float4 *__restrict__ acc, const uint32_t *__restrict__ dtslots, uint32_t *__restrict__ skey,         \
       float4 *__restrict__ soff, uint32_t *__restrict__ sct, uint32_t *__restrict__ sid, uint32_t *__restrict__ counts, \
-      float4 *__restrict__ at_out, float4 *__restrict__ v_out, float4 *__restrict__ dr_out, double *__restrict__ partials
+      float4 *__restrict__ at_out, float4 *__restrict__ v_out, float4 *__restrict__ dr_out,                       \
+      double *__restrict__ partials, StepEnd fin
 #define MPSPH_PASS2_ARGS \
-  doms, ndom, wkey, wpos, wjaux, wid, cstart, acc, dtslots, skey, soff, sct, sid, counts, at_out, v_out, dr_out, partials
-// One logical block lb of the pass; PIPE as for density_force_block.
-template <int D, int L, bool PER, bool PIPE>
+  doms, ndom, wkey, wpos, wjaux, wid, cstart, acc, dtslots, skey, soff, sct, sid, counts, at_out, v_out, dr_out, partials, \
+      fin
+// One logical block lb of the pass; PIPE as for density_force_block, END: the pass closes the step.
+template <int D, int L, bool PER, bool PIPE, bool END = false>
 __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, MPSPH_PASS2_PARAMS) {
   const int d = domain_of_block(doms, ndom, lb);
   const GridDev g = doms[d].g;
@@ -945,18 +1060,27 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, M
   }
   // block sums through LDS, after the epilogue's values
   constexpr size_t kEpBytes = (size_t)3 * P * sizeof(float), kRedBytes = (size_t)(P + 1) * 3 * sizeof(double);
-  static_assert((kEpBytes + 15) / 16 * 16 + kRedBytes <= (size_t)row_table_rows<L>() * row_table_stride<L>() * sizeof(uint4),
-                "the epilogue and the reduction fit in the row table");
+  constexpr size_t kEndBytes = (size_t)(kBlock + 1) * sizeof(double);
+  static_assert((kEpBytes + 15) / 16 * 16 + (kRedBytes > kEndBytes ? kRedBytes : kEndBytes) <=
+                    (size_t)row_table_rows<L>() * row_table_stride<L>() * sizeof(uint4),
+                "the epilogue and the reductions fit in the row table");
   double *rb = reinterpret_cast<double *>(reinterpret_cast<char *>(rowtab) + (kEpBytes + 15) / 16 * 16);
   double *out = partials + (size_t)lb * kNumPartials + P_KE;
   block_reduce_lds<3, P, false>(part, threadIdx.x < P ? (int)threadIdx.x : -1, 0u, 0u, rb,
-                                [&](int s, double x) { out[s] = x; });
+                                [&](int s, double x) {
+    if constexpr (END) agent_store(&out[s], x);
+    else out[s] = x;
+  });
+  if constexpr (END) {
+    __syncthreads();   // the first wave is done with the reduction's LDS
+    close_step(fin, doms[d], d, partials + (size_t)doms[d].blk0 * kNumPartials, doms[d].nblk, dtslots, rb);
+  }
 }
 
-template <int D, int L, bool PER>
+template <int D, int L, bool PER, bool END>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_integrate(int b0, MPSPH_PASS2_PARAMS) {
   __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  viscous_integrate_block<D, L, PER, !PER || D == 2>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, MPSPH_PASS2_ARGS);
+  viscous_integrate_block<D, L, PER, !PER || D == 2, END>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, MPSPH_PASS2_ARGS);
 }
 
 
@@ -1080,85 +1204,19 @@ __global__ __launch_bounds__(kBlock) void dump_pairs(const DomDev *__restrict__ 
   });
 }
 
-// Combine partials slot by slot: sums, or min / max for the slots that hold extrema.
-__device__ __forceinline__ double combine_slot(int s, double a, double b) {
-  return (s == P_EMAX || s == P_ELRMAX) ? fmax(a, b) : (s == P_ELRMIN ? fmin(a, b) : a + b);
-}
-__device__ __forceinline__ double slot_identity(int s) { return s == P_ELRMIN ? INFINITY : 0.0; }
-
-// Fixed-order reduction of nrows partial rows (kNumPartials doubles each) by one block:
-// thread t owns rows t, t + 256, ..., then a fixed tree over the threads.  Result in red[s][0].
-__device__ __forceinline__ void reduce_rows(const double *__restrict__ rows, int nrows, double (*red)[257]) {
-  double acc[kNumPartials];
-#pragma unroll
-  for (int s = 0; s < kNumPartials; ++s) acc[s] = slot_identity(s);
-  for (int b = threadIdx.x; b < nrows; b += 256) {
-    const double *p = rows + (size_t)b * kNumPartials;
-#pragma unroll
-    for (int s = 0; s < kNumPartials; ++s) acc[s] = combine_slot(s, acc[s], p[s]);
-  }
-#pragma unroll
-  for (int s = 0; s < kNumPartials; ++s) red[s][threadIdx.x] = acc[s];
+// The step's end as a launch of its own: block r reduces the pair-kernel block partials of reduction
+// row r (groups[r]: domain, first and last block partial, none of another domain), the last row of a
+// domain to finish the domain's rows.
+__global__ __launch_bounds__(kBlock) void finalize(const DomDev *__restrict__ doms, const int4 *__restrict__ groups,
+                                                   const double *__restrict__ partials, double *__restrict__ rows,
+                                                   const uint32_t *__restrict__ dtslots, StepEnd fin) {
+  __shared__ double red[kBlock + 1];
+  const int4 gr = groups[blockIdx.x];
+  const DomDev &dd = doms[gr.x];
+  const double x = combine_rows(partials + (size_t)gr.y * kNumPartials, gr.z - gr.y, red);
+  if (threadIdx.x < kNumPartials) agent_store(&rows[(size_t)blockIdx.x * kNumPartials + threadIdx.x], x);
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) {
-#pragma unroll
-      for (int s = 0; s < kNumPartials; ++s)
-        red[s][threadIdx.x] = combine_slot(s, red[s][threadIdx.x], red[s][threadIdx.x + w]);
-    }
-    __syncthreads();
-  }
-}
-
-// First level of the metric reduction: row group r (never straddling two domains) reduces the
-// pair-kernel block partials [groups[r].x, groups[r].y) into one row.
-__global__ __launch_bounds__(256) void reduce_partials(const int2 *__restrict__ groups, const double *__restrict__ partials,
-                                                       double *__restrict__ out) {
-  __shared__ double red[kNumPartials][257];
-  const int2 gr = groups[blockIdx.x];
-  reduce_rows(partials + (size_t)gr.x * kNumPartials, gr.y - gr.x, red);
-  if (threadIdx.x < kNumPartials) out[(size_t)blockIdx.x * kNumPartials + threadIdx.x] = red[threadIdx.x][0];
-}
-
-// Second level, one block per domain: the domain's first-level rows into its metrics block m[32 d ...]:
-// slots 0..15 as laid out in kNumPartials, 16: dt1, 17: dt2, 18..20: running totals of pairs,
-// candidates and steps.  Block 0 then advances the device step counter.
-__global__ __launch_bounds__(256) void finalize(const DomDev *__restrict__ doms, const double *__restrict__ rows,
-                                                const uint32_t *__restrict__ dtslots, double *__restrict__ m,
-                                                int64_t *__restrict__ stepctr) {
-  __shared__ double red[kNumPartials][257];
-  const int d = blockIdx.x;
-  reduce_rows(rows + (size_t)doms[d].row0 * kNumPartials, doms[d].nrow, red);
-  double *md = m + (size_t)d * 32;
-  if (threadIdx.x < kNumPartials) md[threadIdx.x] = red[threadIdx.x][0];
-  if (threadIdx.x == 0) {
-    float d1 = INFINITY;
-    for (int s = 0; s < kDtSlots; ++s) d1 = fminf(d1, __uint_as_float(dtslots[d * kDtSlots + s]));
-    md[16] = d1 < INFINITY ? (double)d1 : 0.0;
-    md[17] = d1 < INFINITY ? (double)(d1 * doms[d].sp.dt2_factor) : 0.0;
-    // running totals since the last load (exact integers below 2^53)
-    md[18] += red[P_PAIRS][0];
-    md[19] += red[P_CAND][0];
-    md[20] += 1.0;
-    // automatic t0 (reading of the paper's "topology static for some iterations"): the
-    // interface-pair count and the number of particles with an interface pair stay within
-    // t0_tol of a reference for t0_window steps; otherwise the reference restarts here
-    const StepDev &sp = doms[d].sp;
-    if (sp.auto_t0 && !(md[kAutoT0] > 0.0)) {
-      const double t = md[20] - 1.0;  // index of this step since the load
-      const double I = red[P_IFC][0] * 0.5, P = red[P_IFCP][0];
-      const double tol = (double)sp.t0_tol;
-      if (t == 0.0 || fabs(I - md[kAutoT0 + 1]) > tol * md[kAutoT0 + 1] ||
-          fabs(P - md[kAutoT0 + 2]) > tol * md[kAutoT0 + 2]) {
-        md[kAutoT0 + 1] = I;
-        md[kAutoT0 + 2] = P;
-        md[kAutoT0 + 3] = t;
-      } else if (t - md[kAutoT0 + 3] >= (double)sp.t0_window) {
-        md[kAutoT0] = t + 1.0;
-      }
-    }
-    if (d == 0) *stepctr += 1;
-  }
+  close_step(fin, dd, gr.x, rows + (size_t)dd.row0 * kNumPartials, dd.nrow, dtslots, red);
 }
 
 // Positions back to domain units (FP64) in the load order; state indices [i0, i1).
@@ -1942,6 +2000,10 @@ struct Domain {
   }
 };
 
+// Most pair-kernel blocks of a domain whose step the viscous pass closes; fewest block partials per
+// reduction row otherwise (8 loads in turn per thread).
+constexpr int64_t kFusedChunk = 128;
+
 // Domains of one dimension occupy consecutive internal domain, particle and block ranges.
 struct Group {
   int D = 0;
@@ -1998,6 +2060,7 @@ struct Layout {
   int nblocks_pair = 0, nrows = 0;
   int lanes = MPSPH_LANES;  // lanes per particle in the forward pair kernels
   int64_t chunk = 1;  // block partials per first-level reduction row
+  bool fused = false; // the viscous pass closes the step (StepEnd)
   size_t n_rbf = 0;
   size_t bytes = 0;
   // particles ordered by counting into the cell table (cells.h) instead of a radix sort: tables of
@@ -2008,7 +2071,7 @@ struct Layout {
   bool counted = false;
   size_t s_key, s_off, s_ct, s_id, w_key, w_pos, w_jaux, w_id, k0, v0, k1, v1, hist, counts, sums, cstart, acc, rho, nn, aabs, at, v,
       dr, partials, partials2, groups, metrics, dtslots, stepctr, bad, paircount, queue, doms, vscale, rbf_c, rbf_o, rbf_k,
-      gphi, gs, gaps, gcount;
+      gphi, gs, gaps, gcount, domdone;
 };
 
 // Orders the domains internally (2D before 3D, otherwise as given), assigns particle offsets,
@@ -2048,7 +2111,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     dm.off = n;
     dm.cellbase = (uint32_t)cells;
     dm.blk0 = (int)blocks;
-    dm.nblk = (int)((dm.n * lanes + kBlock - 1) / kBlock);
+    dm.nblk = std::max(1, (int)((dm.n * lanes + kBlock - 1) / kBlock));   // an empty domain's one block closes its step
     dm.rbf0 = nrbf;
     dm.gphi0 = ngphi;
     dm.gs0 = ngs;
@@ -2068,7 +2131,9 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     g.periodic |= dm.p.geometry == MPSPH_PERIODIC;
   }
   // first-level reduction: rows of at most `chunk` block partials, never straddling domains
-  const int64_t chunk = std::max<int64_t>(1, (blocks + kReduceBlocks - 1) / kReduceBlocks);
+  const int64_t chunk = std::max<int64_t>(kFusedChunk, (blocks + kReduceBlocks - 1) / kReduceBlocks);
+  L.fused = n > 0;
+  for (const auto &dm : doms) L.fused = L.fused && dm.nblk <= kFusedChunk;
   int rows = 0;
   for (auto &dm : doms) {
     dm.row0 = rows;
@@ -2118,13 +2183,14 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   L.dr = take(nn * 16);
   L.partials = take((size_t)std::max(L.nblocks_pair, 1) * kNumPartials * 8);
   L.partials2 = take((size_t)std::max(L.nrows, 1) * kNumPartials * 8);
-  L.groups = take((size_t)std::max(L.nrows, 1) * sizeof(int2));
+  L.groups = take((size_t)std::max(L.nrows, 1) * sizeof(int4));
   // what a load clears, in one range: metrics, step counter, validation flag, cell counts
   L.metrics = take((size_t)L.ndom * 32 * 8);
   L.stepctr = take(8);
   L.bad = take(4);
   L.counts = take(L.counted ? cell_count_words(L.ncells) * 4 : 0);
   L.dtslots = take((size_t)L.ndom * kDtSlots * 4);
+  L.domdone = take((size_t)L.ndom * 4);
   L.paircount = take(8);
   L.queue = take(32 * 4);                   // work queues of the persistent pair passes (2 x 16 words)
   L.doms = take((size_t)L.ndom * sizeof(DomDev));
@@ -2298,6 +2364,15 @@ hipError_t order_state(mpsph_ctx *ctx, hipStream_t st, const uint32_t **skeys, c
                     ctx->at<uint32_t>(L.sums), ctx->at<uint32_t>(L.cstart), slots_of(ctx), n, L.ncells, st, hk);
 }
 
+// Whether the viscous pass closes the step (not the persistent launches: their blocks are not co-resident).
+bool fused_end(const mpsph_ctx *ctx) { return ctx->L.fused && ctx->variant != MPSPH_PAIRS_PERSISTENT; }
+
+// The step's end for a launch whose first domain is d0.
+StepEnd step_end(mpsph_ctx *ctx, int d0) {
+  const Layout &L = ctx->L;
+  return StepEnd{d0, ctx->at<uint32_t>(L.domdone), ctx->at<double>(L.metrics) + (size_t)d0 * 32, ctx->at<int64_t>(L.stepctr)};
+}
+
 // The cell counts the integrator and the load write (null: radix sort).
 uint32_t *counts_of(mpsph_ctx *ctx) { return ctx->L.counted ? ctx->at<uint32_t>(ctx->L.counts) : nullptr; }
 
@@ -2364,12 +2439,13 @@ template <int D, int L_, bool PER>
 void launch_pass2_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st, float4 *at_o, float4 *v_o) {
   const Layout &L = ctx->L;
   const bool dbg = ctx->dom[0].p.debug != 0;
-  pass_viscous_integrate<D, L_, PER><<<gr.nb, kBlock, 0, st>>>(
+  auto kern = fused_end(ctx) ? pass_viscous_integrate<D, L_, PER, true> : pass_viscous_integrate<D, L_, PER, false>;
+  kern<<<gr.nb, kBlock, 0, st>>>(
       gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos),
       ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart), ctx->at<float4>(L.acc),
       ctx->at<uint32_t>(L.dtslots) + (size_t)gr.d0 * kDtSlots, ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
       ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), counts_of(ctx), at_o, v_o, dbg ? ctx->at<float4>(L.dr) : nullptr,
-      ctx->at<double>(L.partials));
+      ctx->at<double>(L.partials), step_end(ctx, gr.d0));
 }
 
 template <int D>
@@ -2419,7 +2495,8 @@ void launch_pass2_queue_l(mpsph_ctx *ctx, int b0, int nb2, int nb, hipStream_t s
       ctx->at<float4>(L.w_pos), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),
       ctx->at<float4>(L.acc), ctx->at<uint32_t>(L.dtslots), ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
       ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), counts_of(ctx), dbg ? ctx->at<float4>(L.at) : nullptr,
-      dbg ? ctx->at<float4>(L.v) : nullptr, dbg ? ctx->at<float4>(L.dr) : nullptr, ctx->at<double>(L.partials));
+      dbg ? ctx->at<float4>(L.v) : nullptr, dbg ? ctx->at<float4>(L.dr) : nullptr, ctx->at<double>(L.partials),
+      step_end(ctx, 0));
 }
 
 template <int DM>
@@ -2452,6 +2529,16 @@ void launch_pairs_queue(mpsph_ctx *ctx, hipStream_t st, EventHook *hk) {
     }
     if (hk) hk->end();
   }
+}
+
+// The step's end where the viscous pass does not hold it.
+void launch_step_end(mpsph_ctx *ctx, hipStream_t st, EventHook *hk) {
+  const Layout &L = ctx->L;
+  if (fused_end(ctx)) return;
+  if (hk) hk->begin("finalize");
+  finalize<<<L.nrows, kBlock, 0, st>>>(ctx->at<DomDev>(L.doms), ctx->at<int4>(L.groups), ctx->at<double>(L.partials),
+                                       ctx->at<double>(L.partials2), ctx->at<uint32_t>(L.dtslots), step_end(ctx, 0));
+  if (hk) hk->end();
 }
 
 // Enqueues nsteps steps of every domain on stream st.  No host synchronisation, no memset and
@@ -2487,13 +2574,7 @@ int enqueue(mpsph_ctx *ctx, int nsteps, hipStream_t st, EventHook *hk) {
         }
       }
     }
-    if (hk) hk->begin("finalize");
-    if (L.nrows > 0)
-      reduce_partials<<<L.nrows, 256, 0, st>>>(ctx->at<int2>(L.groups), ctx->at<double>(L.partials),
-                                               ctx->at<double>(L.partials2));
-    finalize<<<ndom, 256, 0, st>>>(ctx->at<DomDev>(L.doms), ctx->at<double>(L.partials2), ctx->at<uint32_t>(L.dtslots),
-                                   ctx->at<double>(L.metrics), ctx->at<int64_t>(L.stepctr));
-    if (hk) hk->end();
+    launch_step_end(ctx, st, hk);
     if (hipGetLastError() != hipSuccess) return fail(ctx, MPSPH_E_DEVICE);
   }
   return MPSPH_OK;
@@ -2586,7 +2667,7 @@ int setup_device(mpsph_ctx *ctx) {
   // a zeroed workspace keeps every table entry a valid index before its first write
   HIP_OK(hipMemset(ctx->ws, 0, L.bytes));
   std::vector<DomDev> dd(ndom);
-  std::vector<int2> groups;
+  std::vector<int4> groups;
   std::vector<int> rc3(3 * std::max<size_t>(L.n_rbf, 1), 0);
   std::vector<float> ro3(3 * std::max<size_t>(L.n_rbf, 1), 0.f), rk(std::max<size_t>(L.n_rbf, 1), 0.f);
   for (int d = 0; d < ndom; ++d) {
@@ -2595,7 +2676,7 @@ int setup_device(mpsph_ctx *ctx) {
                           ctx->at<float>(L.gphi), ctx->at<float>(L.gs));
     for (int r = 0; r < dm.nrow; ++r) {
       const int64_t a = dm.blk0 + (int64_t)r * L.chunk;
-      groups.push_back(make_int2((int)a, (int)std::min<int64_t>(a + L.chunk, dm.blk0 + dm.nblk)));
+      groups.push_back(make_int4(d, (int)a, (int)std::min<int64_t>(a + L.chunk, dm.blk0 + dm.nblk), 0));
     }
     for (int t = 0; t < dm.p.n_rbf; ++t) {
       const size_t kk = dm.rbf0 + t;
@@ -2606,7 +2687,7 @@ int setup_device(mpsph_ctx *ctx) {
   }
   HIP_OK(hipMemcpy(ctx->at<DomDev>(L.doms), dd.data(), dd.size() * sizeof(DomDev), hipMemcpyHostToDevice));
   if (!groups.empty())
-    HIP_OK(hipMemcpy(ctx->at<int2>(L.groups), groups.data(), groups.size() * sizeof(int2), hipMemcpyHostToDevice));
+    HIP_OK(hipMemcpy(ctx->at<int4>(L.groups), groups.data(), groups.size() * sizeof(int4), hipMemcpyHostToDevice));
   HIP_OK(hipMemcpy(ctx->at<int>(L.rbf_c), rc3.data(), rc3.size() * 4, hipMemcpyHostToDevice));
   HIP_OK(hipMemcpy(ctx->at<float>(L.rbf_o), ro3.data(), ro3.size() * 4, hipMemcpyHostToDevice));
   HIP_OK(hipMemcpy(ctx->at<float>(L.rbf_k), rk.data(), rk.size() * 4, hipMemcpyHostToDevice));
@@ -2795,11 +2876,7 @@ int record_step(GradRun &R, int m) {
   launch_pass1<D>(ctx, *R.gr, R.st, nullptr);
   launch_pass2<D>(ctx, *R.gr, R.st, nullptr, reinterpret_cast<float4 *>(b + R.P.tp_at),
                   reinterpret_cast<float4 *>(b + R.P.tp_v));
-  if (L.nrows > 0)
-    reduce_partials<<<L.nrows, 256, 0, R.st>>>(ctx->at<int2>(L.groups), ctx->at<double>(L.partials),
-                                                 ctx->at<double>(L.partials2));
-  finalize<<<1, 256, 0, R.st>>>(ctx->at<DomDev>(L.doms), ctx->at<double>(L.partials2), ctx->at<uint32_t>(L.dtslots),
-                                ctx->at<double>(L.metrics), ctx->at<int64_t>(L.stepctr));
+  launch_step_end(ctx, R.st, nullptr);
   HIP_OK(hipGetLastError());
   const size_t nn = (size_t)n;
   HIP_OK(hipMemcpyAsync(b + R.P.tp_wkey, ctx->at<uint32_t>(L.w_key), nn * 4, hipMemcpyDeviceToDevice, R.st));
