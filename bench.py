@@ -63,7 +63,7 @@ KERNEL_BYTES = {"cell_scan": (0, 8), "cell_place": (28, 4), "reorder_field": (72
                 "pass_density_force": (40, 4), "pass_viscous_integrate": (72, 4)}
 TRAFFIC_DIR = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1906_07925_amd", "csrc", f)
-                  for f in ("mpsph.hip", "mpsph_device.h", "pair_scan.h", "adjoint.h", "sort.hip", "sort.h", "cells.hip", "cells.h")]
+                  for f in ("mpsph.hip", "mpsph_device.h", "pair_scan.h", "adjoint.h", "cells.hip", "cells.h")]
 
 
 def kernel_source_digest() -> str:

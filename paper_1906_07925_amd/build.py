@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmpsph.so")
 
-SOURCES = ["mpsph.hip", "sort.hip", "cells.hip"]
+SOURCES = ["mpsph.hip", "cells.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -49,7 +49,8 @@ constexpr int kMaxRbf = 64;
 struct TapeView {
   const uint32_t *wkey;
   const float4 *wpos;    // offsets, h
-  const uint32_t *wjaux; // colour | cx << 16 | type << 30
+  const float4 *wfix;    // fixed-point coordinates, h
+  const uint32_t *wjaux; // colour | type << 30
   const uint32_t *cstart;
   const uint32_t *perm;  // state index of each sorted index
   const float4 *acc;     // a (after the force mapping), e = rho_t nu_coeff r_c |a|
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
   const StepDev &sp = dom->sp;
   const int local = lb * kBlock + threadIdx.x;
   const int i = local / L, sub = local % L;
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   // per lane group, the particle's (v~, eta) and (a~-bar, d s^(2d)/ds): read from LDS by the
   // pair terms instead of being held in registers across the pair loop
   __shared__ float4 gdat[kBlock / L][2];
@@ -224,8 +225,10 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
     // that the kernel fits its register budget without spilling
     int ci[3];
     unpack_key<D>(tp.wkey[i], g, ci);
-    const float4 pi = tp.wpos[i];
-    const float oi[3] = {pi.x, pi.y, pi.z};
+    const float4 pi = tp.wfix[i];
+    const FixedPos xi = fixed_of(pi);
+    const OwnRow own = own_row<D>(ci, xi, g);
+    const float unit = g.funit;
     const int ti = aux_type(tp.wjaux[i]);
     const float hi = pi.w, si = hi * sp.inv_tau;
     const float s2di = pow2d<D>(si);
@@ -234,7 +237,7 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
     const float kh = 0.5f * sp.kappa, a5 = 5.f * sp.alpha, a75 = 7.5f * sp.alpha;
     if (ei > 0.f) {
-      const BufRes rpos = buf_res(tp.wpos, 16, (uint32_t)g.n), raux = buf_res(tp.wjaux, 4, (uint32_t)g.n);
+      const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n), raux = buf_res(tp.wjaux, 4, (uint32_t)g.n);
       const BufRes racc = buf_res(tp.acc, 16, (uint32_t)g.n), rabv = buf_res(abv, 16, (uint32_t)g.n);
       struct Nb {
         float4 p, a4, ab;
@@ -245,19 +248,19 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
       const auto fetch = [&](uint32_t jr) {
         return Nb{buf_f4(rpos, jr), buf_f4(racc, jr), buf_f4(rabv, jr), buf_u32(raux, jr)};
       };
-      const auto use = [&](const Nb &nb, float dy0, float dz0, bool v) {
+      const auto use = [&](const Nb &nb) {
         const float4 pj = nb.p, aj4 = nb.a4, abj = nb.ab;
         const uint32_t aj = nb.a;
-        const float dx = ((float)ci[0] - cell_x<D>(aj)) + (oi[0] - pj.x);
-        const float dy = dy0 - pj.y;
+        const float dx = fixed_diff(xi.x, pj.x) * unit;
+        const float dy = fixed_diff(xi.y, pj.y) * unit;
         float dz = 0.f;
         float r2 = dx * dx + dy * dy;
         if constexpr (D == 3) {
-          dz = dz0 - pj.z;
+          dz = fixed_diff(xi.z, pj.z) * unit;
           r2 += dz * dz;
         }
         const float hij = kh * (hi + pj.w);
-        if (!(v && r2 > 1e-30f && r2 < hij * hij)) return;
+        if (!(r2 > 0.f && r2 < hij * hij)) return;
         const int tj = aux_type(aj);
         const float ej = hdt * aj4.w;
         if (!(ej > 0.f)) return;  // eta_j = 0: the pair's K and every derivative of it vanish
@@ -292,8 +295,8 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
         xb[1] = fmaf(cx, dy, xb[1]);
         if constexpr (D == 3) xb[2] = fmaf(cx, dz, xb[2]);
       };
-      scan_group_table<D, L, row_table_rows<L>()>(i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), ci, oi, rs,
-                                                  g, 0u, tp.cstart, pair_body<true>(fetch, use));
+      scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own,
+                                                  rs, g, 0u, tp.cstart, pair_body<true>(fetch, use));
     }
     }
 #pragma unroll
@@ -406,12 +409,14 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   const StepDev &sp = dom->sp;
   const int local = lb * kBlock + threadIdx.x;
   const int i = local / L, sub = local % L;
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   if (i >= dom->n) return;
   int ci[3];
   unpack_key<D>(tp.wkey[i], g, ci);
-  const float4 pi = tp.wpos[i];
-  const float oi[3] = {pi.x, pi.y, pi.z};
+  const float4 pi = tp.wfix[i];
+  const FixedPos xi = fixed_of(pi);
+  const OwnRow own = own_row<D>(ci, xi, g);
+  const float unit = g.funit;
   const uint32_t ai = tp.wjaux[i];
   const int ti = aux_type(ai);
   const float hi = pi.w, si = hi * sp.inv_tau;
@@ -422,7 +427,7 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   const float kh = 0.5f * sp.kappa, a5 = 5.f * sp.alpha, a75 = 7.5f * sp.alpha;
   const float opb = 1.f + sigma_of(sp, tstep);   // surface tension of the step (Eq. 24-25)
   float xb[3] = {0.f, 0.f, 0.f}, sb = 0.f;
-  const BufRes rpos = buf_res(tp.wpos, 16, (uint32_t)g.n), raux = buf_res(tp.wjaux, 4, (uint32_t)g.n);
+  const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n), raux = buf_res(tp.wjaux, 4, (uint32_t)g.n);
   const BufRes rfb = buf_res(fbar, 16, (uint32_t)g.n);
   struct Nb {
     float4 p, f;
@@ -431,19 +436,19 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   // the neighbour's loads (bounds-checked: slots past the arrays read zeros) are issued one slot
   // round ahead of the pair's arithmetic
   const auto fetch = [&](uint32_t jr) { return Nb{buf_f4(rpos, jr), buf_f4(rfb, jr), buf_u32(raux, jr)}; };
-  const auto use = [&](const Nb &nb, float dy0, float dz0, bool v) {
+  const auto use = [&](const Nb &nb) {
     const float4 pj = nb.p, fj = nb.f;
     const uint32_t aj = nb.a;
-    const float dx = ((float)ci[0] - cell_x<D>(aj)) + (oi[0] - pj.x);
-    const float dy = dy0 - pj.y;
+    const float dx = fixed_diff(xi.x, pj.x) * unit;
+    const float dy = fixed_diff(xi.y, pj.y) * unit;
     float dz = 0.f;
     float r2 = dx * dx + dy * dy;
     if constexpr (D == 3) {
-      dz = dz0 - pj.z;
+      dz = fixed_diff(xi.z, pj.z) * unit;
       r2 += dz * dz;
     }
     const float hij = kh * (hi + pj.w);
-    if (!(v && r2 > 1e-30f && r2 < hij * hij)) return;
+    if (!(r2 > 0.f && r2 < hij * hij)) return;
     const int tj = aux_type(aj);
     const float mkj = tj >= ti ? 1.f : 0.f, mjk = ti >= tj ? 1.f : 0.f;
     const float wf[3] = {mkj * fi.x - mjk * fj.x, mkj * fi.y - mjk * fj.y, mkj * fi.z - mjk * fj.z};
@@ -467,7 +472,7 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
     if constexpr (D == 3) xb[2] += w * wf[2] + cr * dz;
     sb = fmaf(uw * B, dPi * gg + Psum * dgh * (0.5f * sp.tau), sb);
   };
-  scan_group_table<D, L, row_table_rows<L>()>(i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), ci, oi, rs, g,
+  scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
                                               0u, tp.cstart, pair_body<true>(fetch, use));
 #pragma unroll
   for (int a = 0; a < 3; ++a) xb[a] = group_sum<L>(xb[a]);
@@ -553,7 +558,7 @@ __global__ __launch_bounds__(kCoeffSumThreads) void adj_sum_coeff(const double *
 //   and of the interface sum (slot 1).
 template <int D, int L>
 __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict__ dom, const uint32_t *__restrict__ wkey,
-                                                       const float4 *__restrict__ wpos, const uint32_t *__restrict__ wjaux,
+                                                       const float4 *__restrict__ wfix, const uint32_t *__restrict__ wjaux,
                                                        const uint32_t *__restrict__ cstart, float *__restrict__ e_out,
                                                        double *__restrict__ partials) {
   const int lb = xcd_block(blockIdx.x, gridDim.x);
@@ -561,34 +566,34 @@ __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict_
   const StepDev &sp = dom->sp;
   const int local = lb * kBlock + threadIdx.x;
   const int i = local / L, sub = local % L;
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   double part[2] = {0.0, 0.0};
   const int ops[2] = {0, 0};
   if (i < dom->n) {
     int ci[3];
     unpack_key<D>(wkey[i], g, ci);
-    const float4 pi = wpos[i];
-    const float oi[3] = {pi.x, pi.y, pi.z};
+    const float4 pi = wfix[i];
+    const FixedPos xi = fixed_of(pi);
+    const OwnRow own = own_row<D>(ci, xi, g);
+    const float unit = g.funit;
     const uint32_t ai = wjaux[i];
     const float hi = pi.w, ihi = fast_rcp(hi);
     const float rci = sp.kappa * hi, rci2 = rci * rci;
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
     const float kh = 0.5f * sp.kappa;
     float ws = 0.f, wi = 0.f;
-    const BufRes rpos = buf_res(wpos, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
-    scan_group_table<D, L, row_table_rows<L>()>(i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), ci, oi, rs, g,
-                                                 0u, cstart, [&](uint32_t jr, float dy0, float dz0, bool v) {
-      // jr lies past the arrays for invalid slots: bounds-checked loads first
+    const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
+    scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
+                                                 0u, cstart, [&](uint32_t jr) {
       const float4 pj = buf_f4(rpos, jr);
       const uint32_t aj = buf_u32(raux, jr);
-      const float dx = ((float)ci[0] - cell_x<D>(aj)) + (oi[0] - pj.x);
-      const float dy = dy0 - pj.y;
+      const float dx = fixed_diff(xi.x, pj.x) * unit;
+      const float dy = fixed_diff(xi.y, pj.y) * unit;
       float r2 = dx * dx + dy * dy;
       if constexpr (D == 3) {
-        const float dz = dz0 - pj.z;
+        const float dz = fixed_diff(xi.z, pj.z) * unit;
         r2 += dz * dz;
       }
-      if (!v) return;
       const float r = sqrtf(r2);
       if (r2 < rci2) {
         const float q = r * ihi, u = fmaf(-0.5f, q, 1.f);
@@ -620,7 +625,7 @@ __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict_
 // every j whose support reaches k: r < kappa h_j <= kappa h_k / (1 - kappa L_h).
 template <int D, int L>
 __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ dom, const uint32_t *__restrict__ wkey,
-                                                    const float4 *__restrict__ wpos, const uint32_t *__restrict__ wjaux,
+                                                    const float4 *__restrict__ wfix, const uint32_t *__restrict__ wjaux,
                                                     const uint32_t *__restrict__ cstart, const float *__restrict__ e,
                                                     float ebar_scale, float cl, float reach_fac,
                                                     float4 *__restrict__ xacc, float *__restrict__ sbar) {
@@ -629,12 +634,14 @@ __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ d
   const StepDev &sp = dom->sp;
   const int local = lb * kBlock + threadIdx.x;
   const int i = local / L, sub = local % L;
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   if (i >= dom->n) return;
   int ci[3];
   unpack_key<D>(wkey[i], g, ci);
-  const float4 pi = wpos[i];
-  const float oi[3] = {pi.x, pi.y, pi.z};
+  const float4 pi = wfix[i];
+  const FixedPos xi = fixed_of(pi);
+  const OwnRow own = own_row<D>(ci, xi, g);
+  const float unit = g.funit;
   const uint32_t ai = wjaux[i];
   const float hi = pi.w, ihi = fast_rcp(hi);
   const float A = sp.alpha * (D == 3 ? sp.inv_tau * sp.inv_tau * sp.inv_tau : sp.inv_tau * sp.inv_tau);
@@ -642,21 +649,21 @@ __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ d
   const float rs = fminf(reach_fac * hi, sp.kappa * sp.hmax) * 1.0001f;
   const float kh = 0.5f * sp.kappa;
   float xb[3] = {0.f, 0.f, 0.f}, sb = 0.f;
-  const BufRes rpos = buf_res(wpos, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
-  scan_group_table<D, L, row_table_rows<L>()>(i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), ci, oi, rs, g,
-                                                 0u, cstart, [&](uint32_t jr, float dy0, float dz0, bool v) {
-    const int j = (int)jr;  // past the arrays for invalid slots: bounds-checked loads first
+  const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
+  scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
+                                                 0u, cstart, [&](uint32_t jr) {
+    const int j = (int)jr;
     const float4 pj = buf_f4(rpos, jr);
     const uint32_t aj = buf_u32(raux, jr);
-    const float dx = ((float)ci[0] - cell_x<D>(aj)) + (oi[0] - pj.x);
-    const float dy = dy0 - pj.y;
+    const float dx = fixed_diff(xi.x, pj.x) * unit;
+    const float dy = fixed_diff(xi.y, pj.y) * unit;
     float dz = 0.f;
     float r2 = dx * dx + dy * dy;
     if constexpr (D == 3) {
-      dz = dz0 - pj.z;
+      dz = fixed_diff(xi.z, pj.z) * unit;
       r2 += dz * dz;
     }
-    if (!(v && r2 > 1e-30f)) return;
+    if (!(r2 > 0.f)) return;
     const float r = sqrtf(r2);
     float cx = 0.f;
     const float qi = r * ihi;

@@ -3,9 +3,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "sort.h"
-
 namespace mpsph {
+
+// Optional per-launch hook (event timing); begin() before a launch, end() after it.
+struct LaunchHook {
+  virtual void begin(const char *name) = 0;
+  virtual void end() = 0;
+  virtual ~LaunchHook() = default;
+};
 
 // Entries of the count array for ncells cells: whole tiles of the scan, the rest zero.
 size_t cell_count_words(uint32_t ncells);

@@ -7,24 +7,26 @@
 // table.  The step counter lives on the device, so a captured step can be replayed.
 //
 // Data layout (HBM, structure of arrays, n particles over all domains):
-//   state  (order of the previous step's sort): key u32 (domain cell base + packed cell), off
-//          float4 (cell offsets), ct u32 (type | colour << 2), id u32 (index at load)
-//   work   (order of this step's sort): key u32, pos float4 (offsets, h), jaux u32
-//          (colour | cx << 16 | type << 30), id u32
-//   per step: acc float4 (a, e = rho_t nu_coeff r_c |a|), cell table u32[ncells+1]; rho, sum|term|,
-//             a~, v, dr, nearest distance only in debug mode
+//   state  (order of the previous step): key u32 (domain cell base + packed cell), off float4 (cell
+//          offsets, arrival number), ct u32 (type | colour << 2), id u32 (index at load), cell u32
+//          (search cell)
+//   work   (this step's search order): key u32, pos float4 (offsets, h), fix float4 (fixed-point
+//          coordinates, h), jaux u32 (colour | type << 30), id u32
+//   per step: acc float4 (a, e = rho_t nu_coeff r_c |a|), search table u32[cells+1]; rho, sum|term|,
+//             a~, v, nearest distance only in debug mode
 // Positions are an integer cell coordinate per axis (packed in the key: x fastest and at
 // sub-cell resolution, 3D rows numbered in tiles by row_index) plus a float offset in [0, 1) in
-// cell units, so pair separations are formed from exact integer differences plus differences of
-// numbers below one.  Lengths inside the kernels are
+// cell units.  The pair passes read neighbours as 32-bit fixed-point coordinates of the same positions
+// (multiples of 2^-27 cells as a rule), so a separation is an exact integer difference, rounded once.
+// The order of the particles and the table of the pair scan belong to a search grid of their own,
+// whose rows follow the cut-off (search_rows_rule).  Lengths inside the kernels are
 // in cell units; accelerations and velocities are the domain values divided by the cell size
 // (time is unchanged; the EOS constant is scaled by cs^(d-2) to make this exact).
 //
 // Launch sequence of one step (all on the context stream, no host synchronisation):
-//   cell_scan, cell_place   cell table and cell order from the counts that the load and the integrator
-//                   keep (cells.hip); a radix sort of the keys for tables much larger than n
-//   reorder_cells   gather the state in key order, evaluate the target field (Eq. 1-2, 16)
-//                   (reorder_field after a radix sort: the cell table too)
+//   cell_scan, cell_place   search table and order from the counts that the load and the integrator
+//                   keep (cells.hip)
+//   reorder_field   gather the state in search order, evaluate the target field (Eq. 1-2, 16)
 //   pass_density_force  density (Eq. 17), pressure + surface tension (Eq. 18-19, 23-25),
 //                   projection (Eq. 30-31), first time step (Eq. 29, block minima); like the
 //                   viscous pass, a lane group per particle walks its candidates through a row
@@ -50,7 +52,6 @@
 #include "adjoint.h"
 #include "cells.h"
 #include "pair_scan.h"
-#include "sort.h"
 
 using namespace mpsph;
 
@@ -60,12 +61,12 @@ namespace {
 // Kernels
 // ------------------------------------------------------------------------------------------
 
-// Counts a particle into its new cell and returns its arrival number there as the bits of a float
-// (kept in the offset's fourth word); counts is null when the context sorts by radix instead.
+// Counts a particle into its new search cell and returns its arrival number there as the bits of a
+// float (kept in the offset's fourth word).
 // The atomics make the viscous pass of 2M particles 22 us longer, with or without the answer;
 // taking the arrival numbers in cell_place instead costs 34 us more there.
 __device__ __forceinline__ float count_arrival(uint32_t *counts, uint32_t key) {
-  return counts ? __uint_as_float(atomicAdd(&counts[key], 1u)) : 0.f;
+  return __uint_as_float(atomicAdd(&counts[key], 1u));
 }
 
 // Domain units -> (cell, offset) in FP64 (identical inputs give identical keys), validation.
@@ -75,8 +76,8 @@ __global__ __launch_bounds__(kBlock) void load_kernel(const DomDev *__restrict__
                                                       const float *__restrict__ pos, const int32_t *__restrict__ colour,
                                                       const int32_t *__restrict__ type, uint32_t *__restrict__ key,
                                                       float4 *__restrict__ off, uint32_t *__restrict__ ct,
-                                                      uint32_t *__restrict__ id, uint32_t *__restrict__ counts,
-                                                      int *__restrict__ bad) {
+                                                      uint32_t *__restrict__ id, uint32_t *__restrict__ cell,
+                                                      uint32_t *__restrict__ counts, int *__restrict__ bad) {
   const int i = i0 + blockIdx.x * kBlock + threadIdx.x;
   if (i >= i1) return;
   const DomDev &dd = doms[domain_of(doms, ndom, i)];
@@ -104,9 +105,10 @@ __global__ __launch_bounds__(kBlock) void load_kernel(const DomDev *__restrict__
   const int t = type ? type[u] : 0;
   if (col < 0 || col >= (1 << 16) || t < 0 || t > 3) ok = false;
   if (!ok) atomicOr(bad, 1);
-  const uint32_t kk = dd.cellbase + pack_key<D>(c, o, dd.g);
-  key[i] = kk;
-  off[i] = make_float4(o[0], o[1], D == 3 ? o[2] : 0.f, count_arrival(counts, kk));
+  key[i] = dd.cellbase + pack_key<D>(c, o, dd.g);
+  const uint32_t sc = dd.sbase + search_key<D>(c, o, dd.g);
+  cell[i] = sc;
+  off[i] = make_float4(o[0], o[1], D == 3 ? o[2] : 0.f, count_arrival(counts, sc));
   ct[i] = (uint32_t)(t & 3) | ((uint32_t)col << 2);
   id[i] = (uint32_t)u;
 }
@@ -123,104 +125,43 @@ __global__ __launch_bounds__(kBlock) void load_kernel(const DomDev *__restrict__
 #define MPSPH_PAIR_OCCUPANCY
 #endif
 
-// Empty-cell runs of at least this length are filled by fill_gaps instead of one thread.
-constexpr uint32_t kShortGap = 64;
-constexpr int kGapBlocks = 256;
-
-// Fills the long empty-cell runs listed by reorder_field: block b takes runs b, b + grid, ...,
-// its threads stride over the cells of a run.  The last block to finish resets the list (no
-// memset, so the launch can be captured in a graph).
-__global__ __launch_bounds__(256) void fill_gaps(const uint4 *__restrict__ gaps, uint32_t *__restrict__ gcount,
-                                                 uint32_t *__restrict__ gdone, uint32_t *__restrict__ cstart) {
-  const uint32_t cnt = *(volatile uint32_t *)gcount;
-  for (uint32_t g = blockIdx.x; g < cnt; g += gridDim.x) {
-    const uint4 r = gaps[g];
-    for (uint32_t c = r.x + threadIdx.x; c <= r.y; c += blockDim.x) cstart[c] = r.z;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    if (atomicAdd(gdone, 1u) == gridDim.x - 1) {
-      *gcount = 0u;
-      *gdone = 0u;
-    }
-  }
-}
-
-// Particle s of the state to sorted index i: the field evaluated, the working arrays written.
-template <int D>
-__device__ __forceinline__ void gather_particle(const DomDev &dd, uint32_t s, int i, uint32_t key,
-                                                const float4 *__restrict__ soff, const uint32_t *__restrict__ sct,
-                                                const uint32_t *__restrict__ sid, uint32_t *__restrict__ wkey,
-                                                float4 *__restrict__ wpos, uint32_t *__restrict__ wjaux,
-                                                uint32_t *__restrict__ wid) {
-  const float4 o4 = soff[s];
-  const uint32_t ct = sct[s];
-  int c[3];
-  unpack_key<D>(key - dd.cellbase, dd.g, c);
-  const float o[3] = {o4.x, o4.y, o4.z};
-  const float spc = field_spacing<D>(dd.f, c, o);
-  wkey[i] = key;
-  wpos[i] = make_float4(o4.x, o4.y, o4.z, dd.sp.tau * spc);
-  wjaux[i] = pack_aux((uint32_t)c[0], ct & 3u, ct >> 2);
-  wid[i] = sid[s];
-}
-
-// Gather the state in sorted order, evaluate the size field (h = tau s, Eq. 16) and build the
-// cell table: cstart[c] = first sorted index with key >= c, cstart[ncells] = n.  Sorted keys are
-// grouped by domain, so the sorted range of domain d is [off_d, off_d + n_d); one launch covers
-// the sorted indices [i0, i1) of one dimension group (and the sentinel i = n if i1 = n).  The
-// first nreset threads also reset the time-step slots.
+// Gather the state in search order, evaluate the size field (h = tau s, Eq. 16) and write the working
+// arrays; sorted indices [i0, i1) of one dimension group.  Slot i names one of its search cell's
+// particles, whose place in the cell is its rank by index among the cell's slots (a cell's particles
+// are all candidates of one another, so the ranking is small against the pair passes whatever the
+// occupancy).  The first nreset threads also reset the time-step slots.
 template <int D>
 __global__ __launch_bounds__(kBlock) void reorder_field(
-    const DomDev *__restrict__ doms, int ndom, int i0, int i1, int n, uint32_t ncells, int nreset,
-    const uint32_t *__restrict__ skey, const uint32_t *__restrict__ perm, const float4 *__restrict__ soff,
-    const uint32_t *__restrict__ sct, const uint32_t *__restrict__ sid, uint32_t *__restrict__ wkey,
-    float4 *__restrict__ wpos, uint32_t *__restrict__ wjaux, uint32_t *__restrict__ wid,
-    uint32_t *__restrict__ cstart, uint32_t *__restrict__ dtslots, uint4 *__restrict__ gaps,
-    uint32_t *__restrict__ gcount) {
-  const int t = blockIdx.x * kBlock + threadIdx.x;
-  if (t < nreset) dtslots[t] = kInfBits;
-  const int i = i0 + t;
-  if (i > i1 || (i == i1 && i1 != n)) return;
-  // cells (key[i-1], key[i]] start at sorted index i; the sentinel thread i = n closes the table.
-  // Long runs of empty cells (regions without particles) go to a list that fill_gaps spreads
-  // over many threads.
-  const uint32_t lo = i == 0 ? 0u : skey[i - 1] + 1u;
-  const uint32_t hi = i == n ? ncells : min(skey[i], ncells);
-  if (hi >= lo && hi - lo >= kShortGap) {
-    const uint32_t slot = atomicAdd(gcount, 1u);
-    gaps[slot] = make_uint4(lo, hi, (uint32_t)i, 0u);
-  } else {
-    for (uint32_t c = lo; c <= hi; ++c) cstart[c] = (uint32_t)i;
-  }
-  if (i == n) return;
-  gather_particle<D>(doms[domain_of(doms, ndom, i)], perm[i], i, skey[i], soff, sct, sid, wkey, wpos, wjaux, wid);
-}
-
-// The gather of a context that orders its particles by counting (cells.h), whose cell table is
-// complete before it: slot i names one of its cell's particles, whose place in the cell is its
-// rank by index among the cell's slots (a cell's particles are all candidates of one another, so
-// the ranking is small against the pair passes whatever the occupancy).
-template <int D>
-__global__ __launch_bounds__(kBlock) void reorder_cells(
     const DomDev *__restrict__ doms, int ndom, int i0, int i1, int nreset, const uint32_t *__restrict__ slots,
-    const uint32_t *__restrict__ cstart, const uint32_t *__restrict__ skey, const float4 *__restrict__ soff,
-    const uint32_t *__restrict__ sct, const uint32_t *__restrict__ sid, uint32_t *__restrict__ wkey,
-    float4 *__restrict__ wpos, uint32_t *__restrict__ wjaux, uint32_t *__restrict__ wid, uint32_t *__restrict__ perm,
-    uint32_t *__restrict__ dtslots) {
+    const uint32_t *__restrict__ cstart, const uint32_t *__restrict__ cell, const uint32_t *__restrict__ skey,
+    const float4 *__restrict__ soff, const uint32_t *__restrict__ sct, const uint32_t *__restrict__ sid,
+    uint32_t *__restrict__ wkey, float4 *__restrict__ wpos, float4 *__restrict__ wfix, uint32_t *__restrict__ wjaux,
+    uint32_t *__restrict__ wid, uint32_t *__restrict__ perm, uint32_t *__restrict__ dtslots) {
   const int t = blockIdx.x * kBlock + threadIdx.x;
   if (t < nreset) dtslots[t] = kInfBits;
   const int i = i0 + t;
   if (i >= i1) return;
   const uint32_t s = slots[i];
-  const uint32_t key = skey[s];
-  const uint32_t a = cstart[key], b = cstart[key + 1u];
+  const uint32_t sc = cell[s];
+  const uint32_t a = cstart[sc], b = cstart[sc + 1u];
   uint32_t at = a;
   if (b - a > 1u)
     for (uint32_t q = a; q < b; ++q) at += slots[q] < s ? 1u : 0u;
+  const DomDev &dd = doms[domain_of(doms, ndom, i)];
+  const uint32_t key = skey[s];
+  const float4 o4 = soff[s];
+  const uint32_t ct = sct[s];
+  int c[3];
+  unpack_key<D>(key - dd.cellbase, dd.g, c);
+  const float o[3] = {o4.x, o4.y, o4.z};
+  const float h = dd.sp.tau * field_spacing<D>(dd.f, c, o);
   perm[at] = s;
-  gather_particle<D>(doms[domain_of(doms, ndom, i)], s, (int)at, key, soff, sct, sid, wkey, wpos, wjaux, wid);
+  wkey[at] = key;
+  wpos[at] = make_float4(o4.x, o4.y, o4.z, h);
+  wfix[at] = make_float4(fixed_bits(c[0], o[0], dd.g), fixed_bits(c[1], o[1], dd.g),
+                         D == 3 ? fixed_bits(c[2], o[2], dd.g) : 0.f, h);
+  wjaux[at] = pack_aux(ct & 3u, ct >> 2);
+  wid[at] = sid[s];
 }
 
 // Pass 1: density (Eq. 17, self term included, radius kappa h_i) and
@@ -246,7 +187,7 @@ __global__ __launch_bounds__(kBlock) void reorder_cells(
 constexpr int kTileRows = kBlock;
 struct TileLds {
   int y0, y1, z0, z1;
-  int ux0[kTileRows], ux1[kTileRows];        // union x-run of each row (x sub-cells)
+  int ux0[kTileRows], ux1[kTileRows];        // union x-run of each search row (x sub-cells)
   uint32_t ra[kTileRows];                    // global index of the first staged particle of a row
   uint32_t roff[kTileRows + 1];              // LDS index of a row's first particle; roff[rows] = total
   float4 pos[MPSPH_TILE_CAP];
@@ -288,17 +229,18 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t *t
 // those of scan_group_table.  Called by every thread of the block; returns the same value in
 // every thread (false: the union does not fit).
 template <int L>
-__device__ bool stage_tile(TileLds *T, bool active, int sub, const int *ci, const float *oi, float rs,
-                           const GridDev &g, uint32_t cellbase, const uint32_t *__restrict__ cstart,
-                           const float4 *__restrict__ wpos, const uint32_t *__restrict__ wjaux) {
-  rs = fminf(fmaxf(rs, 0.f), 2.f * (float)g.gmax + 2.f);
+__device__ bool stage_tile(TileLds *T, bool active, int sub, const OwnRow &own, float rs, const GridDev &g,
+                           uint32_t sbase, const uint32_t *__restrict__ cstart, const float4 *__restrict__ wfix,
+                           const uint32_t *__restrict__ wjaux) {
+  rs = fminf(fmaxf(rs, 0.f), 2.f * (float)g.gmax + 2.f) * g.rowinv;
   const float rs2 = rs * rs;
+  const int gmaxr = (1 << g.skr) - 1;
   int y0 = 0, y1 = -1, z0 = 0, z1 = -1;
   if (active) {
-    z0 = max(0, ci[2] + (int)floorf(oi[2] - rs));
-    z1 = min(g.gmax, ci[2] + (int)floorf(oi[2] + rs));
-    y0 = max(0, ci[1] + (int)floorf(oi[1] - rs));
-    y1 = min(g.gmax, ci[1] + (int)floorf(oi[1] + rs));
+    z0 = max(0, own.rz + (int)floorf(own.oz - rs));
+    z1 = min(gmaxr, own.rz + (int)floorf(own.oz + rs));
+    y0 = max(0, own.ry + (int)floorf(own.oy - rs));
+    y1 = min(gmaxr, own.ry + (int)floorf(own.oy + rs));
   }
   if (threadIdx.x == 0) {
     T->y0 = INT_MAX;
@@ -322,21 +264,21 @@ __device__ bool stage_tile(TileLds *T, bool active, int sub, const int *ci, cons
     T->ux1[r] = -1;
   }
   __syncthreads();
-  const float fx = (float)(1u << g.xe);
-  const int xlast = ((g.gmax + 1) << g.xe) - 1;
+  const int xi = own.cx << g.xb, xlast = ((g.gmax + 1) << g.xb) - 1;
+  const float oxs = own.ox * g.fx;
   if (active) {
     const int ny = y1 - y0 + 1, nrows = ny * (z1 - z0 + 1);
     for (int q = sub; q < nrows; q += L) {
       const int cz = z0 + q / ny, cy = y0 + q % ny;
-      const float lz = (float)(cz - ci[2]) - oi[2], hz = lz + 1.f;
+      const float lz = (float)(cz - own.rz) - own.oz, hz = lz + 1.f;
       const float ez = lz > 0.f ? lz : (hz < 0.f ? -hz : 0.f);
-      const float ly = (float)(cy - ci[1]) - oi[1], hy = ly + 1.f;
+      const float ly = (float)(cy - own.ry) - own.oy, hy = ly + 1.f;
       const float ey = ly > 0.f ? ly : (hy < 0.f ? -hy : 0.f);
       const float d2 = ey * ey + ez * ez;
       if (d2 < rs2) {
-        const float wx = fast_sqrt(fmaxf(rs2 - d2, 0.f));
-        const int x0 = max(0, (ci[0] << g.xe) + (int)floorf((oi[0] - wx) * fx));
-        const int x1 = min(xlast, (ci[0] << g.xe) + (int)floorf((oi[0] + wx) * fx));
+        const float wx = fast_sqrt(fmaxf(rs2 - d2, 0.f)) * g.rfx;
+        const int x0 = max(0, xi + (int)floorf(oxs - wx));
+        const int x1 = min(xlast, xi + (int)floorf(oxs + wx));
         const int r = (cz - T->z0) * W + (cy - T->y0);
         atomicMin(&T->ux0[r], x0);
         atomicMax(&T->ux1[r], x1);
@@ -350,7 +292,7 @@ __device__ bool stage_tile(TileLds *T, bool active, int sub, const int *ci, cons
   if (r < nr && T->ux1[r] >= 0) {
     const int cy = T->y0 + r % W, cz = T->z0 + r / W;
     const int x0 = T->ux0[r], x1 = T->ux1[r];
-    const uint32_t kb = cellbase + ((uint32_t)x0 | (row_index(cy, cz, g) << (g.k + g.xe)));
+    const uint32_t kb = sbase + ((uint32_t)x0 | (search_row(cy, cz, g) << (g.k + g.xb)));
     a = cstart[kb];
     const uint32_t b = min(cstart[kb + (uint32_t)(x1 - x0) + 1u], (uint32_t)g.n);
     cnt = b > a ? b - a : 0u;
@@ -373,7 +315,7 @@ __device__ bool stage_tile(TileLds *T, bool active, int sub, const int *ci, cons
       else hi = mid - 1;
     }
     const uint32_t j = T->ra[lo] + (s - T->roff[lo]);
-    T->pos[s] = wpos[j];
+    T->pos[s] = wfix[j];
     T->aux[s] = wjaux[j];
   }
   __syncthreads();
@@ -384,19 +326,18 @@ __device__ bool stage_tile(TileLds *T, bool active, int sub, const int *ci, cons
 // block numbers refer to); rowtab is the block's LDS row table, tile the LDS copy of the
 // neighbours of the TILE variant (unused otherwise).  With PIPE the scan issues the neighbour
 // loads of a lane's next slot before the arithmetic of the current one (same arithmetic, same
-// order: the results do not depend on it).  The single-domain passes take it except in 3D
-// periodic boxes, where the minimum image's extra registers would spill; the persistent and
-// staged variants keep the one-round body.
+// order: the results do not depend on it).  The default passes take it; the persistent and staged
+// variants keep the one-round body.
 #define MPSPH_PASS1_PARAMS                                                                                   \
   const DomDev *__restrict__ doms, int ndom, const int64_t *__restrict__ stepctr,                            \
-      const uint32_t *__restrict__ wkey, const float4 *__restrict__ wpos, const uint32_t *__restrict__ wjaux, \
-      const uint32_t *__restrict__ cstart, float4 *__restrict__ acc, float *__restrict__ rho_out,           \
+      const uint32_t *__restrict__ wkey, const float4 *__restrict__ wpos, const float4 *__restrict__ wfix,    \
+      const uint32_t *__restrict__ wjaux, const uint32_t *__restrict__ cstart, float4 *__restrict__ acc, float *__restrict__ rho_out,           \
       float *__restrict__ nn_out, float *__restrict__ aabs_out, uint32_t *__restrict__ dtslots,             \
       const double *__restrict__ metrics, double *__restrict__ partials
 #define MPSPH_PASS1_ARGS \
-  doms, ndom, stepctr, wkey, wpos, wjaux, cstart, acc, rho_out, nn_out, aabs_out, dtslots, metrics, partials
+  doms, ndom, stepctr, wkey, wpos, wfix, wjaux, cstart, acc, rho_out, nn_out, aabs_out, dtslots, metrics, partials
 template <int D, int L, bool PER, bool DBG, bool TILE, bool PIPE>
-__device__ __forceinline__ void density_force_block(int lb, uint4 *rowtab, TileLds *tile, MPSPH_PASS1_PARAMS) {
+__device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileLds *tile, MPSPH_PASS1_PARAMS) {
   const int d = domain_of_block(doms, ndom, lb);
   const GridDev g = doms[d].g;
   const StepDev sp = doms[d].sp;
@@ -414,22 +355,20 @@ __device__ __forceinline__ void density_force_block(int lb, uint4 *rowtab, TileL
   int tw = 0;
   if constexpr (TILE) {
     static_assert(D == 3 && !PER, "the staged variant covers 3D regions without periodic wrap");
-    int cs[3] = {0, 0, 0};
-    float os[3] = {0.f, 0.f, 0.f};
+    OwnRow own{0, 0, 0, 0.f, 0.f, 0.f};
     float rst = 0.f;
     if (active) {
+      int cs[3] = {0, 0, 0};
       unpack_key<D>(wkey[i] - cellbase, g, cs);
-      const float4 p4 = wpos[i];
-      os[0] = p4.x;
-      os[1] = p4.y;
-      os[2] = p4.z;
+      const float4 p4 = wfix[i];
+      own = own_row<D>(cs, fixed_of(p4), g);
       rst = fminf(sp.search_fac * p4.w, sp.kappa * 0.5f * (p4.w + sp.hmax)) * 1.0001f;
     }
-    staged = stage_tile<L>(tile, active, sub, cs, os, rst, g, cellbase, cstart, wpos, wjaux);
+    staged = stage_tile<L>(tile, active, sub, own, rst, g, doms[d].sbase, cstart, wfix, wjaux);
     if (staged) {
       tw = tile->y1 - tile->y0 + 1;
       if (active) {
-        const int r = (cs[2] - tile->z0) * tw + (cs[1] - tile->y0);
+        const int r = (own.rz - tile->z0) * tw + (own.ry - tile->y0);
         self_t = tile->roff[r] + ((uint32_t)i - tile->ra[r]);
       }
     }
@@ -437,37 +376,40 @@ __device__ __forceinline__ void density_force_block(int lb, uint4 *rowtab, TileL
   if (active) {
     int ci[3];
     unpack_key<D>(wkey[i] - cellbase, g, ci);
-    const float4 pi = wpos[i];
-    const float oi[3] = {pi.x, pi.y, pi.z};
+    const float4 pi = wfix[i];
+    const FixedPos xi = fixed_of(pi);
+    const OwnRow own = own_row<D>(ci, xi, g);
     const uint32_t ai = wjaux[i];
     const int ti = aux_type(ai);
     const float hi = pi.w;
     // P = p0 / rho_t^2 = p0 tau^-2d h^2d and -dW/dr / r = 5 alpha 2^(d+2) (h_i + h_j)^-(d+2) (1 - q/2)^3
     // for the pair's h_ij: the pair sum takes h^2d and (h_i + h_j)^-(d+2), and the factors
-    // common to every pair are applied once to the group's total
+    // common to every pair are applied once to the group's total.  Separations are in fixed-point
+    // units: squared distances are compared in them, the distance itself is converted to cells
     const float Phi = powd<D>(hi * hi);
-    const float fscale = sp.p0c * powd<D>(sp.inv_tau * sp.inv_tau) * (5.f * sp.alpha) * (D == 3 ? 32.f : 16.f);
+    const float fscale = sp.p0c * powd<D>(sp.inv_tau * sp.inv_tau) * (5.f * sp.alpha) * (D == 3 ? 32.f : 16.f) * g.funit;
     const float ihi = fast_rcp(hi);
-    const float rci = sp.kappa * hi, rci2 = rci * rci;
+    const float units = (float)(1u << g.fb);
+    const float rci = sp.kappa * hi * units, rci2 = rci * rci;
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
-    const float kh = 0.5f * sp.kappa;
+    const float kh = 0.5f * sp.kappa * units;
+    const float unit = g.funit;
     const float opb = 1.f + sigma;
     float wsum = 0.f, ax = 0.f, ay = 0.f, az = 0.f, A = 0.f, nn2 = INFINITY;
     uint32_t npair = 0, nifc = 0;
-    const BufRes rpos = buf_res(wpos, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
-    const auto pair = [&](const float4 pj, const uint32_t aj, float dy0, float dz0, bool v) {
-      const float dx = sep_x<PER, D>(g, (float)ci[0], aj, oi[0], pj.x);
-      const float dy = dy0 - pj.y;
+    const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
+    const auto pair = [&](const float4 pj, const uint32_t aj) {
+      const float dx = fixed_diff(xi.x, pj.x), dy = fixed_diff(xi.y, pj.y);
       float r2 = dx * dx + dy * dy;
       float dz = 0.f;
       if constexpr (D == 3) {
-        dz = dz0 - pj.z;
+        dz = fixed_diff(xi.z, pj.z);
         r2 += dz * dz;
       }
       const float hs = hi + pj.w;                   // 2 h_ij
-      const float hij = kh * hs;                    // kappa h_ij
-      const bool dens = v && r2 < rci2;
-      const bool inter = v && r2 < hij * hij;
+      const float hij = kh * hs;                    // kappa h_ij in units
+      const bool dens = r2 < rci2;
+      const bool inter = r2 < hij * hij;
       // the counts and the nearest distance in every lane, so that the branch below is taken
       // only for the kernel sums
       const bool diff = colour_differs(aj, ai);
@@ -479,16 +421,15 @@ __device__ __forceinline__ void density_force_block(int lb, uint4 *rowtab, TileL
       // of a select and an add after the branch
       asm volatile("" : "+v"(npair), "+v"(nifc));
       if (inter && r2 < nn2) nn2 = r2;
-      // coincident particles (two particles clamped into one corner): r = 0, no direction
-      const bool apart = r2 > 1e-30f;
-      const bool force = feel && apart;
-      if (!(dens || force)) return;
-      const float r = fast_sqrt(r2);
+      // coincident particles (two particles clamped into one corner) need no test: their separation
+      // is zero and the force factor finite
+      if (!(dens || feel)) return;
+      const float r = fast_sqrt(r2) * unit;
       if (dens) {
         const float q = r * ihi, u = fmaf(-0.5f, q, 1.f), u2 = u * u;
         wsum += u2 * u2 * fmaf(2.f, q, 1.f);
       }
-      if (!force) return;
+      if (!feel) return;
       const float hj2 = pj.w * pj.w;
       // (P_i + P_j) (-dW/dr / r) over the common factor fscale (>= 0)
       const float s = (diff ? opb : 1.f) * powd_add<D>(hj2, Phi) * kernel_slope_factor<D>(r, fast_rcp(hs));
@@ -502,32 +443,30 @@ __device__ __forceinline__ void density_force_block(int lb, uint4 *rowtab, TileL
       uint32_t a;
     };
     const auto body = pair_body<PIPE>([&](uint32_t j) { return Nb{buf_f4(rpos, j), buf_u32(raux, j)}; },
-                                      [&](const Nb &nb, float dy0, float dz0, bool v) { pair(nb.p, nb.a, dy0, dz0, v); });
+                                      [&](const Nb &nb) { pair(nb.p, nb.a); });
+    const uint32_t sbase = doms[d].sbase;
     uint32_t ncand;
     if constexpr (TILE) {
       if (staged) {
-        // slots index the LDS copy; an invalid slot reads entry 0
-        const auto tbody = [&](uint32_t j, float dy0, float dz0, bool v) {
-          const uint32_t jc = v ? j : 0u;
-          pair(tile->pos[jc], tile->aux[jc], dy0, dz0, v);
-        };
-        ncand = scan_group_table<D, L, row_table_rows<L>(), PER>(i, sub, rowtab + threadIdx.x / L,
-                                                                 row_table_stride<L>(), ci, oi, rs, g, cellbase,
-                                                                 cstart, tbody, TileRemap{tile, tw}, self_t);
+        // slots index the LDS copy
+        const auto tbody = [&](uint32_t j) { pair(tile->pos[j], tile->aux[j]); };
+        ncand = scan_group_table<D, L, row_table_rows<L>(), PER>(self_t, sub, rowtab + threadIdx.x / L,
+                                                                 row_table_stride<L>(), own, rs, g, sbase, cstart, tbody,
+                                                                 TileRemap{tile, tw});
       } else {
         ncand = scan_group_table<D, L, row_table_rows<L>(), PER>(
-            i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), ci, oi, rs, g, cellbase, cstart, body);
+            (uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g, sbase, cstart, body);
       }
     } else {
       ncand = scan_group_table<D, L, row_table_rows<L>(), PER>(
-          i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), ci, oi, rs, g, cellbase, cstart, body);
+          (uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g, sbase, cstart, body);
     }
     gw = group_sum<L>(wsum);
     gx = fscale * group_sum<L>(ax);
     gy = fscale * group_sum<L>(ay);
     if constexpr (D == 3) gz = fscale * group_sum<L>(az);
-    if constexpr (DBG) gA = fscale * group_sum<L>(A);
-    gn = group_min<L>(nn2);
+    if constexpr (DBG) gA = fscale * units * group_sum<L>(A);
+    gn = group_min<L>(nn2) * (unit * unit);
     gp = group_sum_u<L>(npair);
     gi = group_sum_u<L>(nifc);
     gc = ncand;
@@ -608,7 +547,7 @@ __device__ __forceinline__ void density_force_block(int lb, uint4 *rowtab, TileL
   }
   // block results through LDS (after the epilogue's values when both fit in the row table)
   constexpr size_t kEpBytes = (size_t)kEp * P * sizeof(float), kRedBytes = (size_t)(P + 1) * 14 * sizeof(double);
-  constexpr size_t kTableBytes = (size_t)row_table_rows<L>() * row_table_stride<L>() * sizeof(uint4);
+  constexpr size_t kTableBytes = (size_t)row_table_rows<L>() * row_table_stride<L>() * sizeof(uint2);
   constexpr bool kApart = kEpBytes + kRedBytes <= kTableBytes;
   static_assert(kRedBytes <= kTableBytes && kEpBytes <= kTableBytes, "the epilogue and the reduction fit in the row table");
   double *rb = reinterpret_cast<double *>(reinterpret_cast<char *>(rowtab) + (kApart ? (kEpBytes + 15) / 16 * 16 : 0));
@@ -625,15 +564,15 @@ __device__ __forceinline__ void density_force_block(int lb, uint4 *rowtab, TileL
 // The pass over the logical blocks b0 + [0, gridDim.x) (one dimension group).
 template <int D, int L, bool PER, bool DBG>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_density_force(int b0, MPSPH_PASS1_PARAMS) {
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  density_force_block<D, L, PER, DBG, false, !PER || D == 2>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, nullptr, MPSPH_PASS1_ARGS);
+  __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  density_force_block<D, L, PER, DBG, false, true>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, nullptr, MPSPH_PASS1_ARGS);
 }
 
 // The staged copy limits a CU to 4 blocks (4 waves per SIMD), which the register budget follows.
 template <int L, bool DBG>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void pass_density_force_tile(
     int b0, MPSPH_PASS1_PARAMS) {
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   __shared__ TileLds tile;
   density_force_block<3, L, false, DBG, true, false>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, &tile, MPSPH_PASS1_ARGS);
 }
@@ -789,17 +728,19 @@ __device__ __forceinline__ void close_step(const StepEnd &fin, const DomDev &dd,
 // dt2 = dt1 min(1, 2 min(c_vel, c_visc / nu_coeff) / c_acc^2) (sp.dt2_factor).
 #define MPSPH_PASS2_PARAMS                                                                                    \
   const DomDev *__restrict__ doms, int ndom, const uint32_t *__restrict__ wkey, const float4 *__restrict__ wpos, \
-      const uint32_t *__restrict__ wjaux, const uint32_t *__restrict__ wid, const uint32_t *__restrict__ cstart,  \
+      const float4 *__restrict__ wfix, const uint32_t *__restrict__ wjaux, const uint32_t *__restrict__ wid,      \
+      const uint32_t *__restrict__ cstart,                                                                       \
       const float4 *__restrict__ acc, const uint32_t *__restrict__ dtslots, uint32_t *__restrict__ skey,         \
-      float4 *__restrict__ soff, uint32_t *__restrict__ sct, uint32_t *__restrict__ sid, uint32_t *__restrict__ counts, \
-      float4 *__restrict__ at_out, float4 *__restrict__ v_out, float4 *__restrict__ dr_out,                       \
+      float4 *__restrict__ soff, uint32_t *__restrict__ sct, uint32_t *__restrict__ sid, uint32_t *__restrict__ cell, \
+      uint32_t *__restrict__ counts,                                                                             \
+      float4 *__restrict__ at_out, float4 *__restrict__ v_out,                                                    \
       double *__restrict__ partials, StepEnd fin
 #define MPSPH_PASS2_ARGS \
-  doms, ndom, wkey, wpos, wjaux, wid, cstart, acc, dtslots, skey, soff, sct, sid, counts, at_out, v_out, dr_out, partials, \
+  doms, ndom, wkey, wpos, wfix, wjaux, wid, cstart, acc, dtslots, skey, soff, sct, sid, cell, counts, at_out, v_out, partials, \
       fin
 // One logical block lb of the pass; PIPE as for density_force_block, END: the pass closes the step.
 template <int D, int L, bool PER, bool PIPE, bool END = false>
-__device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, MPSPH_PASS2_PARAMS) {
+__device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, MPSPH_PASS2_PARAMS) {
   const int d = domain_of_block(doms, ndom, lb);
   const GridDev g = doms[d].g;
   const StepDev sp = doms[d].sp;
@@ -820,8 +761,9 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, M
       // the pair sum; the particle's own data is scoped to it (the epilogue reads it again)
       int ci[3];
       unpack_key<D>(wkey[i] - cellbase, g, ci);
-      const float4 pi = wpos[i];
-      const float oi[3] = {pi.x, pi.y, pi.z};
+      const float4 pi = wfix[i];
+      const FixedPos xi = fixed_of(pi);
+      const OwnRow own = own_row<D>(ci, xi, g);
       const int ti = aux_type(wjaux[i]);
       const float hi = pi.w;
       // 1 / rho_t^2 = tau^-2d h^2d, v = (dt1/2) a, eta = (dt1/2) e and dW/dr / r =
@@ -832,32 +774,34 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, M
       const float4 acci = acc[i];
       const float ei = (0.5f * dt1) * acci.w;
       const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
-      const float kh = 0.5f * sp.kappa;
+      const float kh = 0.5f * sp.kappa * (float)(1u << g.fb);   // distances are compared in fixed-point units
+      const float unit = g.funit;
       // with eta_i = 0 every harmonic-mean viscosity of particle i vanishes: nothing to sum
       if (ei > 0.f) {
-        const BufRes rpos = buf_res(wpos, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
+        const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
         const BufRes racc = buf_res(acc, 16, (uint32_t)g.n);
         struct Nb {
           float4 p, acc;
           uint32_t a;
         };
-        const auto fetch = [&](uint32_t j) { return Nb{buf_f4(rpos, j), buf_f4(racc, j), buf_u32(raux, j)}; };
-        const auto use = [&](const Nb &nb, float dy0, float dz0, bool) {
+        // a normal particle feels every type: only feature particles load their neighbours' flags
+        const auto fetch = [&](uint32_t j) {
+          return Nb{buf_f4(rpos, j), buf_f4(racc, j), ti > 0 ? buf_u32(raux, j) : 0xFFFFFFFFu};
+        };
+        const auto use = [&](const Nb &nb) {
           const float4 pj = nb.p, accj = nb.acc;
-          const uint32_t aj = nb.a;
-          const float dx = sep_x<PER, D>(g, (float)ci[0], aj, oi[0], pj.x);
-          const float dy = dy0 - pj.y;
+          const float dx = fixed_diff(xi.x, pj.x), dy = fixed_diff(xi.y, pj.y);
           float r2 = dx * dx + dy * dy;
           if constexpr (D == 3) {
-            const float dz = dz0 - pj.z;
+            const float dz = fixed_diff(xi.z, pj.z);
             r2 += dz * dz;
           }
           const float hs = hi + pj.w;   // 2 h_ij
           const float hij = kh * hs;
-          // the particle itself (r = 0 exactly: its own offsets are subtracted from themselves)
-          // and coincident particles fail r^2 > 0, so the slot's self flag v is not needed
-          if (!(r2 > 1e-30f && r2 < hij * hij && type_at_least(aj, ti))) return;
-          const float r = fast_sqrt(r2);
+          // the particle itself and coincident particles have r^2 = 0 exactly
+          if (!(r2 > 0.f && r2 < hij * hij && type_at_least(nb.a, ti))) return;
+          const float r = fast_sqrt(r2) * unit;
+          // e_j          const float r = fast_sqrt(r2);
           // e_j / (e_i + e_j): half the harmonic mean e_i e_j / (e_i + e_j) over e_i, which
           // multiplies the sum once; e_i > 0 here and e_j >= 0, so the sum is positive
           const float eh = accj.w * fast_rcp(acci.w + accj.w);
@@ -867,9 +811,9 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, M
           by = fmaf(s, acci.y - accj.y, by);
           if constexpr (D == 3) bz = fmaf(s, acci.z - accj.z, bz);
         };
-        scan_group_table<D, L, row_table_rows<L>(), PER, false>(i, sub, rowtab + threadIdx.x / L,
-                                                                 row_table_stride<L>(), ci, oi, rs, g, cellbase, cstart,
-                                                                 pair_body<PIPE>(fetch, use));
+        scan_group_table<D, L, row_table_rows<L>(), PER, false>((uint32_t)i, sub, rowtab + threadIdx.x / L,
+                                                                 row_table_stride<L>(), own, rs, g, doms[d].sbase,
+                                                                 cstart, pair_body<PIPE>(fetch, use));
         // the factor e_i of every pair term
         bx *= acci.w;
         by *= acci.w;
@@ -1045,14 +989,14 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, M
           o[a] = 0.f;
         }
       }
-      const uint32_t kk = cellbase + pack_key<D>(c, o, g);
-      skey[io] = kk;
-      soff[io] = make_float4(o[0], o[1], D == 3 ? o[2] : 0.f, count_arrival(counts, kk));
+      skey[io] = cellbase + pack_key<D>(c, o, g);
+      const uint32_t sc = doms[d].sbase + search_key<D>(c, o, g);
+      cell[io] = sc;
+      soff[io] = make_float4(o[0], o[1], D == 3 ? o[2] : 0.f, count_arrival(counts, sc));
       sct[io] = (uint32_t)ti | (aux_colour(ai) << 2);
       sid[io] = wid[io];
       if (at_out) at_out[io] = make_float4(b[0], b[1], b[2], 0.f);
       if (v_out) v_out[io] = make_float4(v[0], v[1], v[2], 0.f);
-      if (dr_out) dr_out[io] = make_float4(dr[0], dr[1], dr[2], 0.f);
       part[0] = (double)ke;
       part[1] = fin ? 0.0 : 1.0;
       part[2] = ti != 0 ? 1.0 : 0.0;
@@ -1062,7 +1006,7 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, M
   constexpr size_t kEpBytes = (size_t)3 * P * sizeof(float), kRedBytes = (size_t)(P + 1) * 3 * sizeof(double);
   constexpr size_t kEndBytes = (size_t)(kBlock + 1) * sizeof(double);
   static_assert((kEpBytes + 15) / 16 * 16 + (kRedBytes > kEndBytes ? kRedBytes : kEndBytes) <=
-                    (size_t)row_table_rows<L>() * row_table_stride<L>() * sizeof(uint4),
+                    (size_t)row_table_rows<L>() * row_table_stride<L>() * sizeof(uint2),
                 "the epilogue and the reductions fit in the row table");
   double *rb = reinterpret_cast<double *>(reinterpret_cast<char *>(rowtab) + (kEpBytes + 15) / 16 * 16);
   double *out = partials + (size_t)lb * kNumPartials + P_KE;
@@ -1079,8 +1023,8 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint4 *rowtab, M
 
 template <int D, int L, bool PER, bool END>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_integrate(int b0, MPSPH_PASS2_PARAMS) {
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  viscous_integrate_block<D, L, PER, !PER || D == 2, END>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, MPSPH_PASS2_ARGS);
+  __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  viscous_integrate_block<D, L, PER, true, END>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, MPSPH_PASS2_ARGS);
 }
 
 
@@ -1113,7 +1057,7 @@ template <int DM, int L, bool PER, bool DBG>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_density_force_queue(int b0, int nb2, int nb,
                                                                                         uint32_t *queue,
                                                                                         MPSPH_PASS1_PARAMS) {
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   __shared__ int sitem;
   for (;;) {
     __syncthreads();   // the previous block's LDS (row table, reductions) is no longer read
@@ -1135,7 +1079,7 @@ template <int DM, int L, bool PER>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_integrate_queue(int b0, int nb2, int nb,
                                                                                             uint32_t *queue,
                                                                                             MPSPH_PASS2_PARAMS) {
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   __shared__ int sitem;
   for (;;) {
     __syncthreads();   // the previous block's LDS (row table, reductions) is no longer read
@@ -1160,8 +1104,8 @@ __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_inte
 // running count stays below cap; *count receives the total.
 template <int D, bool PER>
 __global__ __launch_bounds__(kBlock) void dump_pairs(const DomDev *__restrict__ doms, int ndom, int i0, int i1,
-                                                     const uint32_t *__restrict__ wkey, const float4 *__restrict__ wpos,
-                                                     const uint32_t *__restrict__ wjaux, const uint32_t *__restrict__ wid,
+                                                     const uint32_t *__restrict__ wkey, const float4 *__restrict__ wfix,
+                                                     const uint32_t *__restrict__ wid,
                                                      const uint32_t *__restrict__ cstart, unsigned long long cap,
                                                      uint32_t *__restrict__ out_i, uint32_t *__restrict__ out_j,
                                                      unsigned long long *__restrict__ count) {
@@ -1174,28 +1118,24 @@ __global__ __launch_bounds__(kBlock) void dump_pairs(const DomDev *__restrict__ 
   const StepDev &sp = dd.sp;
   int ci[3];
   unpack_key<D>(wkey[i] - dd.cellbase, g, ci);
-  const float4 pi = wpos[i];
-  const float oi[3] = {pi.x, pi.y, pi.z};
+  const float4 pi = wfix[i];
+  const FixedPos xi = fixed_of(pi);
   const float hi = pi.w;
   const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
-  const float kh = 0.5f * sp.kappa;
+  const float kh = 0.5f * sp.kappa * (float)(1u << g.fb);
   const uint32_t idi = wid[i];
-  __shared__ uint4 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  scan_group_table<D, L, row_table_rows<L>(), PER>(i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), ci, oi, rs,
-                                                   g, dd.cellbase, cstart, [&](uint32_t jr, float dy0, float dz0, bool v) {
-    // a slot past the chunk's end may carry an index outside the arrays (and NaN offsets)
-    const int j = v && jr < (uint32_t)g.n ? (int)jr : i;
-    const float4 pj = wpos[j];
-    const uint32_t aj = wjaux[j];
-    const float dx = sep_x<PER, D>(g, (float)ci[0], aj, oi[0], pj.x);
-    const float dy = dy0 - pj.y;
+  __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  scan_group_table<D, L, row_table_rows<L>(), PER>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(),
+                                                   own_row<D>(ci, xi, g), rs, g, dd.sbase, cstart, [&](uint32_t j) {
+    const float4 pj = wfix[j];
+    const float dx = fixed_diff(xi.x, pj.x), dy = fixed_diff(xi.y, pj.y);
     float r2 = dx * dx + dy * dy;
     if constexpr (D == 3) {
-      const float dz = dz0 - pj.z;
+      const float dz = fixed_diff(xi.z, pj.z);
       r2 += dz * dz;
     }
     const float hij = kh * (hi + pj.w);
-    if (!(v && r2 < hij * hij)) return;
+    if (!(r2 < hij * hij)) return;
     const unsigned long long k = atomicAdd(count, 1ull);
     if (k < cap) {
       out_i[k] = idi;
@@ -1298,6 +1238,7 @@ inline size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 struct Derived {
   int dim, k, gmax;
   int xe;                  // x sub-cells per cell in the cell key: 2^xe
+  int rb, xb;              // search grid: rows of 2^rb cells, 2^xb x sub-cells per cell
   double L, cs, inv_cs, lo[3], xhi[3];
   double smin, smax, lip;  // spacing bounds (domain units), Lipschitz constant of s
   double search_fac;
@@ -1838,6 +1779,58 @@ int derive(const mpsph_params *p, int64_t n, double s0, Derived *d) {
   return MPSPH_OK;
 }
 
+// Mean spacing over particles distributed by the target density: int s^(1-d) / int s^-d (midpoints of a
+// coarse grid over the region).
+double mean_spacing(const mpsph_params *p, double s0, double smin) {
+  const int d = p->dim, m = d == 2 ? 24 : 8;
+  if (p->field == MPSPH_UNIFORM) return s0;
+  double w = 0.0, ws = 0.0;
+  const int mz = d == 3 ? m : 1;
+  for (int iz = 0; iz < mz; ++iz)
+    for (int iy = 0; iy < m; ++iy)
+      for (int ix = 0; ix < m; ++ix) {
+        const int idx[3] = {ix, iy, iz};
+        double x[3] = {0, 0, 0};
+        for (int a = 0; a < d; ++a) x[a] = p->lo[a] + (p->hi[a] - p->lo[a]) * (idx[a] + 0.5) / m;
+        if (!inside_region(p, x)) continue;
+        const double s = host_spacing(p, s0, x), v = 1.0 / (d == 2 ? s * s : s * s * s);
+        w += v;
+        ws += v * s;
+      }
+  return w > 0 && std::isfinite(ws / w) ? ws / w : smin;
+}
+
+// Search rows: a row about as wide as the cut-off of a mean particle, whatever the cell size.
+// The rule's cells follow the finest one, which in a graded field makes the rows of most particles
+// narrow: a row costs as much as six candidates, the candidates fall by less.  Measured per step at 4
+// lanes with rows of one and two cells: graded cube, 1M particles 1280 and 936 us, ball 1:3, 262,144
+// particles 462 and 346; with a mean cut-off of 0.93, 1.95 and 3.9 rows (8192 particles, uniform) 88, 82 and 105.
+int search_rows_rule(const mpsph_params *p, double s0, const Derived &d) {
+  const double rc = p->kappa * p->tau * mean_spacing(p, s0, d.smin) * d.inv_cs;
+  const int rb = (int)std::floor(std::log2(std::max(rc / 1.05, 1e-3)));
+  return std::min(std::max(rb, -1), d.k);
+}
+
+// x sub-cells of the search grid, and coarser rows where the table would be much larger than the
+// particle count (at most 8 entries per particle or 2^20).
+void fit_search(int dim, int64_t n, Derived *d) {
+  const double most = std::max(8.0 * (double)std::max<int64_t>(n, 1), 1048576.0);
+  auto bits = [&] { return d->k + d->xb + (dim - 1) * (d->k - d->rb); };
+  d->xb = 0;
+  while (std::pow(2.0, bits()) > most && d->rb < d->k) ++d->rb;
+  // x sub-cells: up to 2^MPSPH_XSUB per cell while the table stays within 4 entries per particle (its scan is
+  // part of every step)
+  while (d->xb < MPSPH_XSUB && bits() < 26 && std::pow(2.0, bits() + 1) <= 4.0 * (double)std::max<int64_t>(n, 1)) ++d->xb;
+}
+
+// Bits of the fixed-point coordinates' fraction: any separation of candidates stays below 2^31 units; in a
+// periodic box the coordinates' wrap divides the period.
+int fixed_fraction(const mpsph_params *p, const Derived &d) {
+  const double reach = p->kappa * p->tau * d.smax * d.inv_cs * 1.001 + std::pow(2.0, std::max(d.rb, 0)) + 1.0;
+  int fb = std::min(27, 31 - (int)std::ceil(std::log2(reach)));
+  if (p->geometry == MPSPH_PERIODIC) fb = std::max(fb, 32 - d.k);
+  return std::max(fb, 0);
+}
 
 struct EventHook : LaunchHook {
   struct Rec {
@@ -1954,7 +1947,8 @@ struct Domain {
   Derived d{};
   double s0 = 0;
   int64_t n = 0, off = 0;
-  uint32_t ncells = 0, cellbase = 0;
+  uint32_t ncells = 0, cellbase = 0;   // cells of the exported cell table
+  uint32_t scells = 0, sbase = 0;      // cells of the search table
   int blk0 = 0, nblk = 0, row0 = 0, nrow = 0;
   size_t rbf0 = 0;  // first RBF term of this domain in the packed RBF arrays
   std::vector<double> gphi, gs;  // background-mesh node values (level set, field)
@@ -1978,6 +1972,8 @@ struct Domain {
     off = o.off;
     ncells = o.ncells;
     cellbase = o.cellbase;
+    scells = o.scells;
+    sbase = o.sbase;
     blk0 = o.blk0;
     nblk = o.nblk;
     row0 = o.row0;
@@ -2013,6 +2009,13 @@ struct Group {
   int b0 = 0, nb = 0;   // pair-kernel blocks
 };
 
+// Cells of the domain's two tables, for its cell size and search rows (d.rb).
+void count_cells_of(Domain *dm) {
+  fit_search(dm->p.dim, dm->n, &dm->d);
+  dm->ncells = (uint32_t)1u << (dm->p.dim * dm->d.k + dm->d.xe);
+  dm->scells = (uint32_t)1u << (dm->d.k + dm->d.xb + (dm->p.dim - 1) * (dm->d.k - dm->d.rb));
+}
+
 // Parameters copied into a domain; s0 normalised and the grid derived.  n is the domain's count.
 int make_domain(const mpsph_params *params, int64_t n, Domain *dm) {
   if (!valid_params(params) || n < 0 || n > (int64_t)1 << 30) return MPSPH_E_INVALID;
@@ -2045,7 +2048,8 @@ int make_domain(const mpsph_params *params, int64_t n, Domain *dm) {
   dm->s0 = s0;
   int rc = derive(&dm->p, n, s0, &dm->d);
   if (rc) return rc;
-  dm->ncells = (uint32_t)1u << (params->dim * dm->d.k + dm->d.xe);
+  dm->d.rb = search_rows_rule(&dm->p, s0, dm->d);
+  count_cells_of(dm);
   return MPSPH_OK;
 }
 
@@ -2055,23 +2059,17 @@ struct Layout {
   Group grp[2];  // 2D domains, then 3D domains
   std::vector<int> internal;  // caller's domain index -> internal index
   int64_t n = 0;
-  uint32_t ncells = 0;  // cells of all domains
-  int key_bits = 0;
+  uint32_t ncells = 0;  // cells of all domains (exported cell table)
+  uint32_t scells = 0;  // cells of the search table
   int nblocks_pair = 0, nrows = 0;
   int lanes = MPSPH_LANES;  // lanes per particle in the forward pair kernels
   int64_t chunk = 1;  // block partials per first-level reduction row
   bool fused = false; // the viscous pass closes the step (StepEnd)
   size_t n_rbf = 0;
   size_t bytes = 0;
-  // particles ordered by counting into the cell table (cells.h) instead of a radix sort: tables of
-  // at most 8 cells per particle (what the size rule gives), whose scan costs less than the
-  // sort's passes (order and gather of 4096 particles 9.4 us a step against 54, of 262,144 25 against
-  // 98, of 2M with 4M cells 56 + 22 in the viscous pass against 133).  A caller's much finer table is
-  // mostly empty: there the sort touches it once, the scan three times
-  bool counted = false;
-  size_t s_key, s_off, s_ct, s_id, w_key, w_pos, w_jaux, w_id, k0, v0, k1, v1, hist, counts, sums, cstart, acc, rho, nn, aabs, at, v,
-      dr, partials, partials2, groups, metrics, dtslots, stepctr, bad, paircount, queue, doms, vscale, rbf_c, rbf_o, rbf_k,
-      gphi, gs, gaps, gcount, domdone;
+  size_t s_key, s_off, s_ct, s_id, s_cell, w_key, w_pos, w_fix, w_jaux, w_id, counts, sums, cstart, acc, rho, nn, aabs, at, v,
+      partials, partials2, groups, metrics, dtslots, stepctr, bad, paircount, queue, doms, vscale, rbf_c, rbf_o, rbf_k,
+      gphi, gs, domdone;
 };
 
 // Orders the domains internally (2D before 3D, otherwise as given), assigns particle offsets,
@@ -2092,7 +2090,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   std::stable_sort(doms.begin(), doms.end(), [](const Domain &a, const Domain &b) { return a.p.dim < b.p.dim; });
   L.internal.assign(L.ndom, 0);
   for (int d = 0; d < L.ndom; ++d) L.internal[doms[d].uidx] = d;
-  uint64_t cells = 0;
+  uint64_t cells = 0, scells = 0;
   int64_t n = 0;
   int64_t blocks = 0;
   size_t nrbf = 0, ngphi = 0, ngs = 0;
@@ -2110,6 +2108,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     }
     dm.off = n;
     dm.cellbase = (uint32_t)cells;
+    dm.sbase = (uint32_t)scells;
     dm.blk0 = (int)blocks;
     dm.nblk = std::max(1, (int)((dm.n * lanes + kBlock - 1) / kBlock));   // an empty domain's one block closes its step
     dm.rbf0 = nrbf;
@@ -2119,6 +2118,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     ngs += dm.gs.size();
     n += dm.n;
     cells += dm.ncells;
+    scells += dm.scells;
     blocks += dm.nblk;
     nrbf += (size_t)dm.p.n_rbf;
     // thread indices of the pair kernels (particles x lanes) stay below 2^31
@@ -2142,8 +2142,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   }
   L.n = n;
   L.ncells = (uint32_t)cells;
-  L.key_bits = 1;
-  while (((uint64_t)1 << L.key_bits) < cells) ++L.key_bits;
+  L.scells = (uint32_t)scells;
   L.nblocks_pair = (int)blocks;
   L.nrows = rows;
   L.chunk = chunk;
@@ -2163,24 +2162,18 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   L.w_pos = take(nn * 16);
   L.w_jaux = take(nn * 4);
   L.w_id = take(nn * 4);
-  L.counted = cells <= 8 * (uint64_t)std::max<int64_t>(n, 64);
-  const size_t nr = L.counted ? 0 : nn;      // the arrays of one of the two orders only
-  L.k0 = take(nr * 4);
-  L.v0 = take(nr * 4);
-  L.k1 = take(nr * 4);
-  L.v1 = take(nr * 4);
-  L.hist = take(L.counted ? 0 : radix_hist_words((int)n) * 4);
-  L.cstart = take(((size_t)L.ncells + 1) * 4);
-  L.gaps = take(L.counted ? 0 : (nn + 1) * sizeof(uint4));   // at most one empty-cell run per sorted particle
-  L.gcount = take(8);                       // run count, finished blocks of fill_gaps
-  L.sums = take(L.counted ? cell_sum_words(L.ncells) * 4 : 0);
+  L.s_cell = take(nn * 4);
+  L.w_fix = take(nn * 16);
+  L.cstart = take(((size_t)L.scells + 1) * 4);
+  L.sums = take(cell_sum_words(L.scells) * 4);
   L.acc = take(nn * 16);
-  L.rho = take(nn * 4);
-  L.nn = take(nn * 4);
-  L.aabs = take(nn * 4);
-  L.at = take(nn * 16);
-  L.v = take(nn * 16);
-  L.dr = take(nn * 16);
+  // debug exports only
+  const size_t nd = !doms.empty() && doms[0].p.debug ? nn : 0;
+  L.rho = take(nd * 4);
+  L.nn = take(nd * 4);
+  L.aabs = take(nd * 4);
+  L.at = take(nd * 16);
+  L.v = take(nd * 16);
   L.partials = take((size_t)std::max(L.nblocks_pair, 1) * kNumPartials * 8);
   L.partials2 = take((size_t)std::max(L.nrows, 1) * kNumPartials * 8);
   L.groups = take((size_t)std::max(L.nrows, 1) * sizeof(int4));
@@ -2188,7 +2181,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   L.metrics = take((size_t)L.ndom * 32 * 8);
   L.stepctr = take(8);
   L.bad = take(4);
-  L.counts = take(L.counted ? cell_count_words(L.ncells) * 4 : 0);
+  L.counts = take(cell_count_words(L.scells) * 4);
   L.dtslots = take((size_t)L.ndom * kDtSlots * 4);
   L.domdone = take((size_t)L.ndom * 4);
   L.paircount = take(8);
@@ -2236,6 +2229,16 @@ DomDev domain_device(const Domain &dm, const int *rbf_c, const float *rbf_o, con
   g.xe = (uint32_t)dm.d.xe;
   g.ly = D == 3 ? (uint32_t)std::min(MPSPH_TILE_LY, g.k) : 0u;
   g.lz = D == 3 ? (uint32_t)std::min(MPSPH_TILE_LZ, g.k) : 0u;
+  g.rb = dm.d.rb;
+  g.skr = (uint32_t)(g.k - g.rb);
+  g.xb = (uint32_t)dm.d.xb;
+  g.sly = D == 3 ? std::min((uint32_t)MPSPH_TILE_LY, g.skr) : 0u;
+  g.slz = D == 3 ? std::min((uint32_t)MPSPH_TILE_LZ, g.skr) : 0u;
+  g.rowinv = std::ldexp(1.f, -g.rb);
+  g.fx = std::ldexp(1.f, (int)g.xb);
+  g.rfx = std::ldexp(1.f, g.rb + (int)g.xb);
+  g.fb = fixed_fraction(&p, dm.d);
+  g.funit = std::ldexp(1.f, -g.fb);
   // background mesh: node spacing (hi - lo) / (n - 1) in cell units
   for (int a = 0; a < 3; ++a) {
     const int na = a < D ? std::max(p.grid_n[a], 2) : 2;
@@ -2283,6 +2286,7 @@ DomDev domain_device(const Domain &dm, const int *rbf_c, const float *rbf_o, con
   sp.t0_tol = (float)(p.t0_tol > 0 ? p.t0_tol : 1e-3);
   sp.theta = (float)(p.theta > 0 ? p.theta : 0.2);
   dd.cellbase = dm.cellbase;
+  dd.sbase = dm.sbase;
   dd.off = (int)dm.off;
   dd.n = (int)dm.n;
   dd.uoff = (int)dm.uoff;
@@ -2349,20 +2353,14 @@ int fail(mpsph_ctx *c, int code) {
 uint32_t *slots_of(mpsph_ctx *ctx) { return ctx->at<uint32_t>(ctx->L.acc); }
 uint32_t *perm_of(mpsph_ctx *ctx) { return ctx->at<uint32_t>(ctx->L.acc) + std::max<int64_t>(ctx->L.n, 1); }
 
-// Orders the state by cell key: the sorted keys (radix sort only) and, after launch_group, the
-// source index of every sorted position.
-hipError_t order_state(mpsph_ctx *ctx, hipStream_t st, const uint32_t **skeys, const uint32_t **perm, LaunchHook *hk) {
+// Orders the state by search cell: the slots of every cell and the search table.
+hipError_t order_state(mpsph_ctx *ctx, hipStream_t st, LaunchHook *hk) {
   const Layout &L = ctx->L;
-  const int n = (int)L.n;
-  if (!L.counted)
-    return radix_sort(ctx->at<uint32_t>(L.s_key), ctx->at<uint32_t>(L.k0), ctx->at<uint32_t>(L.v0),
-                      ctx->at<uint32_t>(L.k1), ctx->at<uint32_t>(L.v1), ctx->at<uint32_t>(L.hist), n, L.key_bits, st,
-                      skeys, perm, hk);
-  *skeys = nullptr;
-  *perm = perm_of(ctx);
-  return cell_order(ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.counts),
-                    ctx->at<uint32_t>(L.sums), ctx->at<uint32_t>(L.cstart), slots_of(ctx), n, L.ncells, st, hk);
+  return cell_order(ctx->at<uint32_t>(L.s_cell), ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.counts),
+                    ctx->at<uint32_t>(L.sums), ctx->at<uint32_t>(L.cstart), slots_of(ctx), (int)L.n, L.scells, st, hk);
 }
+
+bool dbg_context(const mpsph_ctx *ctx) { return ctx->dom[0].p.debug != 0; }
 
 // Whether the viscous pass closes the step (not the persistent launches: their blocks are not co-resident).
 bool fused_end(const mpsph_ctx *ctx) { return ctx->L.fused && ctx->variant != MPSPH_PAIRS_PERSISTENT; }
@@ -2373,35 +2371,17 @@ StepEnd step_end(mpsph_ctx *ctx, int d0) {
   return StepEnd{d0, ctx->at<uint32_t>(L.domdone), ctx->at<double>(L.metrics) + (size_t)d0 * 32, ctx->at<int64_t>(L.stepctr)};
 }
 
-// The cell counts the integrator and the load write (null: radix sort).
-uint32_t *counts_of(mpsph_ctx *ctx) { return ctx->L.counted ? ctx->at<uint32_t>(ctx->L.counts) : nullptr; }
-
-// Kernels of one step for one dimension group.
+// The gather of one dimension group.
 template <int D>
-void launch_group(mpsph_ctx *ctx, const Group &gr, const uint32_t *skeys, const uint32_t *perm, int nreset,
-                  hipStream_t st, EventHook *hk) {
+void launch_group(mpsph_ctx *ctx, const Group &gr, int nreset, hipStream_t st, EventHook *hk) {
   const Layout &L = ctx->L;
-  const int n = (int)L.n;
-  const DomDev *doms = ctx->at<DomDev>(L.doms) + gr.d0;
   if (hk) hk->begin("reorder_field");
-  if (L.counted) {
-    const int nt = std::max(gr.i1 - gr.i0, nreset);
-    reorder_cells<D><<<(nt + kBlock - 1) / kBlock, kBlock, 0, st>>>(
-        doms, gr.nd, gr.i0, gr.i1, nreset, slots_of(ctx), ctx->at<uint32_t>(L.cstart), ctx->at<uint32_t>(L.s_key),
-        ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.w_key),
-        ctx->at<float4>(L.w_pos), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), perm_of(ctx),
-        ctx->at<uint32_t>(L.dtslots));
-    if (hk) hk->end();
-    return;
-  }
-  const int nthr = std::max(gr.i1 - gr.i0 + (gr.i1 == n ? 1 : 0), nreset);
-  reorder_field<D><<<(nthr + kBlock - 1) / kBlock, kBlock, 0, st>>>(
-      doms, gr.nd, gr.i0, gr.i1, n, L.ncells, nreset, skeys, perm, ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct),
-      ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos), ctx->at<uint32_t>(L.w_jaux),
-      ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart), ctx->at<uint32_t>(L.dtslots), ctx->at<uint4>(L.gaps),
-      ctx->at<uint32_t>(L.gcount));
-  fill_gaps<<<kGapBlocks, 256, 0, st>>>(ctx->at<uint4>(L.gaps), ctx->at<uint32_t>(L.gcount),
-                                        ctx->at<uint32_t>(L.gcount) + 1, ctx->at<uint32_t>(L.cstart));
+  const int nt = std::max(gr.i1 - gr.i0, nreset);
+  reorder_field<D><<<(nt + kBlock - 1) / kBlock, kBlock, 0, st>>>(
+      ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, gr.i0, gr.i1, nreset, slots_of(ctx), ctx->at<uint32_t>(L.cstart),
+      ctx->at<uint32_t>(L.s_cell), ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct),
+      ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos), ctx->at<float4>(L.w_fix),
+      ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), perm_of(ctx), ctx->at<uint32_t>(L.dtslots));
   if (hk) hk->end();
 }
 
@@ -2414,7 +2394,8 @@ void launch_pass1_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st) {
     if (ctx->variant == MPSPH_PAIRS_TILE) kern = dbg ? pass_density_force_tile<L_, true> : pass_density_force_tile<L_, false>;
   kern<<<gr.nb, kBlock, 0, st>>>(
       gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<int64_t>(L.stepctr), ctx->at<uint32_t>(L.w_key),
-      ctx->at<float4>(L.w_pos), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.cstart), ctx->at<float4>(L.acc),
+      ctx->at<float4>(L.w_pos), ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.cstart),
+      ctx->at<float4>(L.acc),
       dbg ? ctx->at<float>(L.rho) : nullptr, dbg ? ctx->at<float>(L.nn) : nullptr,
       dbg ? ctx->at<float>(L.aabs) : nullptr, ctx->at<uint32_t>(L.dtslots) + (size_t)gr.d0 * kDtSlots,
       ctx->at<double>(L.metrics) + (size_t)gr.d0 * 32, ctx->at<double>(L.partials));
@@ -2438,13 +2419,13 @@ void launch_pass1(mpsph_ctx *ctx, const Group &gr, hipStream_t st, EventHook *hk
 template <int D, int L_, bool PER>
 void launch_pass2_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st, float4 *at_o, float4 *v_o) {
   const Layout &L = ctx->L;
-  const bool dbg = ctx->dom[0].p.debug != 0;
   auto kern = fused_end(ctx) ? pass_viscous_integrate<D, L_, PER, true> : pass_viscous_integrate<D, L_, PER, false>;
   kern<<<gr.nb, kBlock, 0, st>>>(
       gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos),
-      ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart), ctx->at<float4>(L.acc),
+      ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),
+      ctx->at<float4>(L.acc),
       ctx->at<uint32_t>(L.dtslots) + (size_t)gr.d0 * kDtSlots, ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
-      ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), counts_of(ctx), at_o, v_o, dbg ? ctx->at<float4>(L.dr) : nullptr,
+      ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.s_cell), ctx->at<uint32_t>(L.counts), at_o, v_o,
       ctx->at<double>(L.partials), step_end(ctx, gr.d0));
 }
 
@@ -2480,8 +2461,8 @@ void launch_pass1_queue_l(mpsph_ctx *ctx, int b0, int nb2, int nb, hipStream_t s
   auto kern = dbg ? pass_density_force_queue<DM, L_, PER, true> : pass_density_force_queue<DM, L_, PER, false>;
   kern<<<queue_grid(ctx, nb), kBlock, 0, st>>>(
       b0, nb2, nb, ctx->at<uint32_t>(L.queue), ctx->at<DomDev>(L.doms), L.ndom, ctx->at<int64_t>(L.stepctr),
-      ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.cstart),
-      ctx->at<float4>(L.acc), dbg ? ctx->at<float>(L.rho) : nullptr, dbg ? ctx->at<float>(L.nn) : nullptr,
+      ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos), ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux),
+      ctx->at<uint32_t>(L.cstart), ctx->at<float4>(L.acc), dbg ? ctx->at<float>(L.rho) : nullptr, dbg ? ctx->at<float>(L.nn) : nullptr,
       dbg ? ctx->at<float>(L.aabs) : nullptr, ctx->at<uint32_t>(L.dtslots), ctx->at<double>(L.metrics),
       ctx->at<double>(L.partials));
 }
@@ -2492,10 +2473,10 @@ void launch_pass2_queue_l(mpsph_ctx *ctx, int b0, int nb2, int nb, hipStream_t s
   const bool dbg = ctx->dom[0].p.debug != 0;
   pass_viscous_integrate_queue<DM, L_, PER><<<queue_grid(ctx, nb), kBlock, 0, st>>>(
       b0, nb2, nb, ctx->at<uint32_t>(L.queue) + 16, ctx->at<DomDev>(L.doms), L.ndom, ctx->at<uint32_t>(L.w_key),
-      ctx->at<float4>(L.w_pos), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),
-      ctx->at<float4>(L.acc), ctx->at<uint32_t>(L.dtslots), ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
-      ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), counts_of(ctx), dbg ? ctx->at<float4>(L.at) : nullptr,
-      dbg ? ctx->at<float4>(L.v) : nullptr, dbg ? ctx->at<float4>(L.dr) : nullptr, ctx->at<double>(L.partials),
+      ctx->at<float4>(L.w_pos), ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id),
+      ctx->at<uint32_t>(L.cstart), ctx->at<float4>(L.acc), ctx->at<uint32_t>(L.dtslots), ctx->at<uint32_t>(L.s_key),
+      ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.s_cell), ctx->at<uint32_t>(L.counts),
+      dbg ? ctx->at<float4>(L.at) : nullptr, dbg ? ctx->at<float4>(L.v) : nullptr, ctx->at<double>(L.partials),
       step_end(ctx, 0));
 }
 
@@ -2549,14 +2530,13 @@ int enqueue(mpsph_ctx *ctx, int nsteps, hipStream_t st, EventHook *hk) {
   const int n = (int)L.n, ndom = L.ndom;
   for (int s = 0; s < nsteps; ++s) {
     if (n > 0) {
-      const uint32_t *skeys = nullptr, *perm = nullptr;
-      if (order_state(ctx, st, &skeys, &perm, hk) != hipSuccess)
+      if (order_state(ctx, st, hk) != hipSuccess)
         return fail(ctx, MPSPH_E_DEVICE);
       int nreset = ndom * kDtSlots;  // the first launch resets every domain's time-step slots
       for (const Group &gr : L.grp) {
         if (gr.i1 <= gr.i0) continue;
-        if (gr.D == 2) launch_group<2>(ctx, gr, skeys, perm, nreset, st, hk);
-        else launch_group<3>(ctx, gr, skeys, perm, nreset, st, hk);
+        if (gr.D == 2) launch_group<2>(ctx, gr, nreset, st, hk);
+        else launch_group<3>(ctx, gr, nreset, st, hk);
         nreset = 0;
       }
       if (ctx->variant == MPSPH_PAIRS_PERSISTENT) {
@@ -2643,6 +2623,7 @@ int replan(std::vector<Domain> &doms, int kdelta, int lanes, Layout *L, int kabs
   std::stable_sort(doms.begin(), doms.end(), [](const Domain &a, const Domain &b) { return a.uidx < b.uidx; });
   for (auto &dm : doms) {
     mpsph_params q = dm.p;
+    int shift = 0;
     if (kabs >= 1) {
       q.cell_log2 = kabs;
     } else if (q.cell_log2 < 0) {
@@ -2650,10 +2631,12 @@ int replan(std::vector<Domain> &doms, int kdelta, int lanes, Layout *L, int kabs
       int rc = derive(&q, dm.n, dm.s0, &r);
       if (rc) return rc;
       q.cell_log2 = std::min(std::max(r.k + kdelta, 1), q.dim == 3 ? 8 : 12);
+      shift = q.cell_log2 - r.k;   // the rows follow the cells of the candidate
     }
     int rc = derive(&q, dm.n, dm.s0, &dm.d);
     if (rc) return rc;
-    dm.ncells = (uint32_t)1u << (q.dim * dm.d.k + dm.d.xe);
+    dm.d.rb = std::min(search_rows_rule(&q, dm.s0, dm.d) - shift, dm.d.k);
+    count_cells_of(&dm);
   }
   return plan(doms, lanes, L);
 }
@@ -2741,8 +2724,8 @@ int reconfigure(mpsph_ctx *ctx, const std::vector<Domain> &base, int kdelta, int
 
 struct GradPlan {
   int nck = 0, ckpt = 0;
-  size_t ck0 = 0, ck_stride = 0, ck_key = 0, ck_off = 0, ck_ct = 0, ck_id = 0;
-  size_t tp0 = 0, tp_stride = 0, tp_perm = 0, tp_wkey = 0, tp_wpos = 0, tp_wjaux = 0, tp_acc = 0, tp_at = 0,
+  size_t ck0 = 0, ck_stride = 0, ck_key = 0, ck_off = 0, ck_ct = 0, ck_id = 0, ck_cell = 0;
+  size_t tp0 = 0, tp_stride = 0, tp_perm = 0, tp_wkey = 0, tp_wpos = 0, tp_wfix = 0, tp_wjaux = 0, tp_acc = 0, tp_at = 0,
          tp_v = 0, tp_cstart = 0, tp_dts = 0;
   size_t xbar = 0, xacc = 0, abv = 0, vtb = 0, abar = 0, fbar = 0, sbar = 0, e = 0, dtc = 0, pa = 0, pb = 0,
          cpart = 0, cbar = 0, scal = 0, mback = 0;
@@ -2771,6 +2754,7 @@ GradPlan grad_plan(int64_t n, uint32_t ncells, int nck, int ckpt, int nb1, int n
   P.ck_off = ctake(nn * 16);
   P.ck_ct = ctake(nn * 4);
   P.ck_id = ctake(nn * 4);
+  P.ck_cell = ctake(nn * 4);
   P.ck_stride = c;
   P.ck0 = take(P.ck_stride * nck);
   size_t t = 0;
@@ -2782,6 +2766,7 @@ GradPlan grad_plan(int64_t n, uint32_t ncells, int nck, int ckpt, int nb1, int n
   P.tp_perm = ttake(nn * 4);
   P.tp_wkey = ttake(nn * 4);
   P.tp_wpos = ttake(nn * 16);
+  P.tp_wfix = ttake(nn * 16);
   P.tp_wjaux = ttake(nn * 4);
   P.tp_acc = ttake(nn * 16);
   P.tp_at = ttake(nn * 16);
@@ -2828,6 +2813,7 @@ struct GradRun {
     TapeView v;
     v.wkey = reinterpret_cast<const uint32_t *>(b + P.tp_wkey);
     v.wpos = reinterpret_cast<const float4 *>(b + P.tp_wpos);
+    v.wfix = reinterpret_cast<const float4 *>(b + P.tp_wfix);
     v.wjaux = reinterpret_cast<const uint32_t *>(b + P.tp_wjaux);
     v.cstart = reinterpret_cast<const uint32_t *>(b + P.tp_cstart);
     v.perm = reinterpret_cast<const uint32_t *>(b + P.tp_perm);
@@ -2845,18 +2831,18 @@ int copy_state(GradRun &R, int k, bool save) {
   const Layout &L = ctx->L;
   const size_t n = (size_t)L.n;
   char *c = R.ck(k);
-  const size_t off_ws[4] = {L.s_key, L.s_off, L.s_ct, L.s_id};
-  const size_t off_ck[4] = {R.P.ck_key, R.P.ck_off, R.P.ck_ct, R.P.ck_id};
-  const size_t sz[4] = {n * 4, n * 16, n * 4, n * 4};
-  for (int a = 0; a < 4; ++a) {
+  const size_t off_ws[5] = {L.s_key, L.s_off, L.s_ct, L.s_id, L.s_cell};
+  const size_t off_ck[5] = {R.P.ck_key, R.P.ck_off, R.P.ck_ct, R.P.ck_id, R.P.ck_cell};
+  const size_t sz[5] = {n * 4, n * 16, n * 4, n * 4, n * 4};
+  for (int a = 0; a < 5; ++a) {
     void *ws = ctx->ws + off_ws[a];
     void *cp = c + off_ck[a];
     HIP_OK(hipMemcpyAsync(save ? cp : ws, save ? ws : cp, sz[a], hipMemcpyDeviceToDevice, R.st));
   }
   // a restored state's cell counts: those of the state it replaces go
-  if (!save && L.counted) {
-    HIP_OK(hipMemsetAsync(ctx->at<uint32_t>(L.counts), 0, cell_count_words(L.ncells) * 4, R.st));
-    HIP_OK(count_cells(ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.counts), (int)L.n, R.st));
+  if (!save) {
+    HIP_OK(hipMemsetAsync(ctx->at<uint32_t>(L.counts), 0, cell_count_words(L.scells) * 4, R.st));
+    HIP_OK(count_cells(ctx->at<uint32_t>(L.s_cell), ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.counts), (int)L.n, R.st));
   }
   return MPSPH_OK;
 }
@@ -2867,23 +2853,25 @@ int record_step(GradRun &R, int m) {
   mpsph_ctx *ctx = R.ctx;
   const Layout &L = ctx->L;
   const int n = (int)L.n;
-  const uint32_t *skeys = nullptr, *perm = nullptr;
-  if (order_state(ctx, R.st, &skeys, &perm, nullptr) != hipSuccess)
+  if (order_state(ctx, R.st, nullptr) != hipSuccess)
     return fail(ctx, MPSPH_E_DEVICE);
   char *b = R.tp(m);
-  launch_group<D>(ctx, *R.gr, skeys, perm, kDtSlots, R.st, nullptr);
-  HIP_OK(hipMemcpyAsync(b + R.P.tp_perm, perm, (size_t)n * 4, hipMemcpyDeviceToDevice, R.st));
+  launch_group<D>(ctx, *R.gr, kDtSlots, R.st, nullptr);
+  HIP_OK(hipMemcpyAsync(b + R.P.tp_perm, perm_of(ctx), (size_t)n * 4, hipMemcpyDeviceToDevice, R.st));
   launch_pass1<D>(ctx, *R.gr, R.st, nullptr);
   launch_pass2<D>(ctx, *R.gr, R.st, nullptr, reinterpret_cast<float4 *>(b + R.P.tp_at),
                   reinterpret_cast<float4 *>(b + R.P.tp_v));
   launch_step_end(ctx, R.st, nullptr);
   HIP_OK(hipGetLastError());
   const size_t nn = (size_t)n;
+  if (dbg_context(ctx))   // the debug exports of v and of the drift refer to the recomputed step
+    HIP_OK(hipMemcpyAsync(ctx->at<float4>(L.v), b + R.P.tp_v, nn * 16, hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_wkey, ctx->at<uint32_t>(L.w_key), nn * 4, hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_wpos, ctx->at<float4>(L.w_pos), nn * 16, hipMemcpyDeviceToDevice, R.st));
+  HIP_OK(hipMemcpyAsync(b + R.P.tp_wfix, ctx->at<float4>(L.w_fix), nn * 16, hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_wjaux, ctx->at<uint32_t>(L.w_jaux), nn * 4, hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_acc, ctx->at<float4>(L.acc), nn * 16, hipMemcpyDeviceToDevice, R.st));
-  HIP_OK(hipMemcpyAsync(b + R.P.tp_cstart, ctx->at<uint32_t>(L.cstart), ((size_t)L.ncells + 1) * 4,
+  HIP_OK(hipMemcpyAsync(b + R.P.tp_cstart, ctx->at<uint32_t>(L.cstart), ((size_t)L.scells + 1) * 4,
                         hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_dts, ctx->at<uint32_t>(L.dtslots), kDtSlots * 4, hipMemcpyDeviceToDevice, R.st));
   return MPSPH_OK;
@@ -2897,12 +2885,11 @@ int loss_backward(GradRun &R, double lam) {
   const Domain &dm = ctx->dom[0];
   const int n = (int)L.n;
   const DomDev *dom = ctx->at<DomDev>(L.doms);
-  const uint32_t *skeys = nullptr, *perm = nullptr;
-  if (order_state(ctx, R.st, &skeys, &perm, nullptr) != hipSuccess)
+  if (order_state(ctx, R.st, nullptr) != hipSuccess)
     return fail(ctx, MPSPH_E_DEVICE);
-  launch_group<D>(ctx, *R.gr, skeys, perm, kDtSlots, R.st, nullptr);
+  launch_group<D>(ctx, *R.gr, kDtSlots, R.st, nullptr);
   const int nbp = R.nbp;
-  loss_density<D, MPSPH_ADJ_LANES><<<nbp, kBlock, 0, R.st>>>(dom, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos),
+  loss_density<D, MPSPH_ADJ_LANES><<<nbp, kBlock, 0, R.st>>>(dom, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_fix),
                                                        ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.cstart),
                                                        R.at<float>(R.P.e), R.at<double>(R.P.pb));
   loss_value<<<1, 256, 0, R.st>>>(R.at<double>(R.P.pb), nbp, 1.0 / n, lam, R.at<double>(R.P.scal) + 1);
@@ -2910,14 +2897,14 @@ int loss_backward(GradRun &R, double lam) {
   const double Lh = dm.p.tau * dm.d.lip;
   const double kl = dm.p.kappa * Lh;
   const float reach = kl < 0.95 ? (float)(dm.p.kappa / (1.0 - kl) * (1.0 + 1e-4)) : 1e30f;
-  loss_grad<D, MPSPH_ADJ_LANES><<<nbp, kBlock, 0, R.st>>>(dom, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos),
+  loss_grad<D, MPSPH_ADJ_LANES><<<nbp, kBlock, 0, R.st>>>(dom, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_fix),
                                                     ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.cstart),
                                                     R.at<float>(R.P.e), (float)(2.0 / n), (float)(lam / n), reach,
                                                     R.at<float4>(R.P.xacc), R.at<float>(R.P.sbar));
   TapeView tv{};
   tv.wkey = ctx->at<uint32_t>(L.w_key);
   tv.wpos = ctx->at<float4>(L.w_pos);
-  tv.perm = perm;
+  tv.perm = perm_of(ctx);
   adj_field<D><<<R.nb1, kBlock, 0, R.st>>>(dom, tv, R.at<float4>(R.P.xacc), R.at<float>(R.P.sbar),
                                            R.at<float4>(R.P.xbar), R.at<double>(R.P.cpart));
   if (dm.p.field == MPSPH_RBF_EXP && dm.p.n_rbf > 0)
@@ -2976,7 +2963,7 @@ int grad_run(mpsph_ctx *ctx, int nsteps, int ckpt, double lam, double *loss_out,
   R.nbp = (int)(((int64_t)n * MPSPH_ADJ_LANES + kBlock - 1) / kBlock);
   const int nseg = nsteps > 0 ? (nsteps + ckpt - 1) / ckpt : 0;
   const int seg_len = std::min(ckpt, std::max(nsteps, 1));
-  R.P = grad_plan(n, L.ncells, nseg + 1, seg_len, R.nb1, R.nbp);
+  R.P = grad_plan(n, L.scells, nseg + 1, seg_len, R.nb1, R.nbp);
   if (ctx->gbytes < R.P.bytes) {
     if (ctx->gmem) (void)hipFree(ctx->gmem);
     ctx->gmem = nullptr;
@@ -3300,7 +3287,7 @@ int mpsph_load(mpsph_ctx *ctx, const float *d_pos, const int32_t *d_colour, cons
     auto kern = gr.D == 2 ? load_kernel<2> : load_kernel<3>;
     kern<<<(gr.i1 - gr.i0 + kBlock - 1) / kBlock, kBlock, 0, ctx->stream>>>(
         ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, gr.i0, gr.i1, d_pos, d_colour, d_type, ctx->at<uint32_t>(L.s_key),
-        ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), counts_of(ctx), ctx->at<int>(L.bad));
+        ctx->at<float4>(L.s_off), ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.s_cell), ctx->at<uint32_t>(L.counts), ctx->at<int>(L.bad));
     HIP_OK(hipGetLastError());
   }
   int bad = 0;
@@ -3409,15 +3396,27 @@ int mpsph_debug_fields(mpsph_ctx *ctx, int32_t which, float *d_out) {
   if (which == MPSPH_F_A_ABS) sc = ctx->at<float>(L.aabs);
   if (which == MPSPH_F_AT) vec = ctx->at<float4>(L.at);
   if (which == MPSPH_F_V) vec = ctx->at<float4>(L.v);
-  if (which == MPSPH_F_DR) vec = ctx->at<float4>(L.dr);
-  if (which == MPSPH_F_VT) {
-    // v~ = a dt1 / 2 (Eq. 26 after the velocity reset) with the domain's dt1; fixed particles
-    // carry a = 0
-    std::vector<double> m((size_t)L.ndom * 32);
+  if (which == MPSPH_F_DR) vec = ctx->at<float4>(L.v);
+  if (which == MPSPH_F_VT || which == MPSPH_F_DR) {
     std::vector<float> vs(L.ndom);
-    HIP_OK(hipMemcpyAsync(m.data(), ctx->at<double>(L.metrics), m.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_OK(hipStreamSynchronize(ctx->stream));
-    for (int d = 0; d < L.ndom; ++d) vs[d] = (float)(0.5 * m[(size_t)d * 32 + 16]);
+    if (which == MPSPH_F_VT) {
+      // v~ = a dt1 / 2 (Eq. 26 after the velocity reset) with the domain's dt1; fixed particles
+      // carry a = 0
+      std::vector<double> m((size_t)L.ndom * 32);
+      HIP_OK(hipMemcpyAsync(m.data(), ctx->at<double>(L.metrics), m.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
+      HIP_OK(hipStreamSynchronize(ctx->stream));
+      for (int d = 0; d < L.ndom; ++d) vs[d] = (float)(0.5 * m[(size_t)d * 32 + 16]);
+    } else {
+      // the drift is v dt2, the product the integrator forms (Eq. 28)
+      std::vector<float> slots((size_t)L.ndom * kDtSlots);
+      HIP_OK(hipMemcpyAsync(slots.data(), ctx->at<float>(L.dtslots), slots.size() * 4, hipMemcpyDeviceToHost, ctx->stream));
+      HIP_OK(hipStreamSynchronize(ctx->stream));
+      for (int d = 0; d < L.ndom; ++d) {
+        const float *sl = slots.data() + (size_t)d * kDtSlots;
+        const float d1 = *std::min_element(sl, sl + kDtSlots);
+        vs[d] = (std::isfinite(d1) ? d1 : 0.f) * (float)dt2_factor(&ctx->dom[d].p);
+      }
+    }
     HIP_OK(hipMemcpyAsync(ctx->at<float>(L.vscale), vs.data(), vs.size() * 4, hipMemcpyHostToDevice, ctx->stream));
     vscale = ctx->at<float>(L.vscale);
   }
@@ -3450,9 +3449,16 @@ int mpsph_debug_cells(mpsph_ctx *ctx, uint32_t *d_key, uint32_t *d_cell_start, i
     for (int i = 0; i < n; ++i) outk[id[i]] = k[i];
     HIP_OK(hipMemcpyAsync(d_key, outk.data(), 4 * (size_t)n, hipMemcpyHostToDevice, ctx->stream));
   }
-  if (d_cell_start)
-    HIP_OK(hipMemcpyAsync(d_cell_start, ctx->at<uint32_t>(L.cstart), 4 * ((size_t)L.ncells + 1),
-                          hipMemcpyDeviceToDevice, ctx->stream));
+  if (d_cell_start) {
+    // lower bound of every cell in the sorted keys, from the counts (the search order is another)
+    std::vector<uint32_t> k(n), start((size_t)L.ncells + 1, 0u);
+    HIP_OK(hipMemcpyAsync(k.data(), ctx->at<uint32_t>(L.w_key), 4 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
+    HIP_OK(hipStreamSynchronize(ctx->stream));
+    for (int i = 0; i < n; ++i) ++start[(size_t)k[i] + 1];
+    for (size_t c = 0; c < (size_t)L.ncells; ++c) start[c + 1] += start[c];
+    HIP_OK(hipMemcpyAsync(d_cell_start, start.data(), 4 * start.size(), hipMemcpyHostToDevice, ctx->stream));
+    HIP_OK(hipStreamSynchronize(ctx->stream));
+  }
   HIP_OK(hipStreamSynchronize(ctx->stream));
   return MPSPH_OK;
 }
@@ -3469,8 +3475,8 @@ int mpsph_debug_pairs(mpsph_ctx *ctx, int64_t cap, uint32_t *d_i, uint32_t *d_j,
                           : (gr.periodic ? dump_pairs<3, true> : dump_pairs<3, false>);
     // two lanes per particle
     kern<<<(int)((2 * (int64_t)(gr.i1 - gr.i0) + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
-        ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, gr.i0, gr.i1, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos),
-        ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),
+        ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, gr.i0, gr.i1, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_fix),
+        ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),
         (unsigned long long)cap, d_i, d_j, cnt);
     HIP_OK(hipGetLastError());
   }
@@ -3501,6 +3507,8 @@ int mpsph_set_field_coeff(mpsph_ctx *ctx, int32_t domain, const double *coeff) {
     dm.p.rbf_coeff = dm.rbf_coeff.data();
     return MPSPH_E_UNSUPPORTED;
   }
+  nd.rb = dm.d.rb;   // the search grid stays too
+  nd.xb = dm.d.xb;
   dm.d = nd;
   const Layout &L = ctx->L;
   const DomDev dd = domain_device(dm, ctx->at<int>(L.rbf_c), ctx->at<float>(L.rbf_o), ctx->at<float>(L.rbf_k),

@@ -69,6 +69,17 @@ struct GridDev {
   int seeded;        // features seeded explicitly: reflect instead of project-and-retag
   uint32_t ly, lz;   // 3D row tiles of 2^ly x 2^lz rows in the cell key (see row_index)
   uint32_t xe;       // x sub-cells per cell in the cell key: 2^xe
+  // search grid: the order of the sorted arrays and the table the pair scan reads.  Rows of 2^rb cells
+  // (rb < 0: several rows per cell) along y and z, x at 2^xb sub-cells per cell.
+  int rb;
+  uint32_t skr;      // rows per axis 2^skr = 2^(k - rb)
+  uint32_t xb;
+  uint32_t sly, slz; // 3D search rows in tiles of 2^sly x 2^slz (search_row)
+  float rowinv;      // rows per cell, 2^-rb
+  float fx, rfx;     // x sub-cells per cell and per row width
+  // fixed-point coordinates: multiples of 2^-fb cells, modulo 2^32 (any separation met is below 2^31)
+  int fb;
+  float funit;       // 2^-fb
 };
 
 // Target size field in cell units: s_cell(x) = s(x) / cs.
@@ -165,6 +176,7 @@ struct DomDev {
   FieldDev f;
   StepDev sp;
   uint32_t cellbase;
+  uint32_t sbase;    // first cell of the domain in the search table
   int off, n;        // internal particle range (domains grouped by dimension, 2D first)
   int uoff;          // first row of the domain in the caller's colour / type arrays
   int64_t xoff;      // first float of the domain in the caller's position arrays (rows of dim floats)
@@ -223,13 +235,10 @@ __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcp
 __device__ __forceinline__ float fast_rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sqrtf(x); }  // x >= 0; sqrt(0) = 0
 
-// Flags word of a particle in the sorted order: colour in bits 0-15, x (sub-)cell in bits 16-27
-// (16-23 in 3D), type in bits 30-31.  The pair loops test the fields in place: colours with one
-// 16-bit compare of the low halves, the type (the top field) with one compare of the whole word,
-// and a 3D x cell converts from its byte in one instruction.
-__device__ __forceinline__ uint32_t pack_aux(uint32_t cx, uint32_t type, uint32_t colour) {
-  return colour | (cx << 16) | (type << 30);
-}
+// Flags word of a particle in the sorted order: colour in bits 0-15, type in bits 30-31.  The pair
+// loops test the fields in place: colours with one 16-bit compare of the low halves, the type (the
+// top field) with one compare of the whole word.
+__device__ __forceinline__ uint32_t pack_aux(uint32_t type, uint32_t colour) { return colour | (type << 30); }
 __device__ __forceinline__ int aux_type(uint32_t aux) { return (int)(aux >> 30); }
 __device__ __forceinline__ uint32_t aux_colour(uint32_t aux) { return aux & 0xFFFFu; }
 __device__ __forceinline__ bool colour_differs(uint32_t a, uint32_t b) { return (uint16_t)a != (uint16_t)b; }
@@ -331,6 +340,28 @@ __device__ __forceinline__ void unpack_key(uint32_t key, const GridDev &g, int *
     c[1] = (int)((yh << g.ly) | yl);
     c[2] = (int)((zh << g.lz) | zl);
   }
+}
+
+// Key of a position in the search grid, x fastest, 3D rows numbered in tiles as in the cell key.
+// Every part is exact: integer shifts and power-of-two scalings of offsets in [0, 1).
+__device__ __forceinline__ uint32_t search_row(int ry, int rz, const GridDev &g) {
+  const uint32_t y = (uint32_t)ry, z = (uint32_t)rz;
+  return (y & ((1u << g.sly) - 1u)) | ((z & ((1u << g.slz) - 1u)) << g.sly) | ((y >> g.sly) << (g.sly + g.slz)) |
+         ((z >> g.slz) << (g.skr + g.slz));
+}
+__device__ __forceinline__ int row_of(int c, float o, const GridDev &g) {
+  return g.rb >= 0 ? c >> g.rb : (c << -g.rb) | (int)(o * g.rowinv);
+}
+template <int D>
+__device__ __forceinline__ uint32_t search_key(const int *c, const float *o, const GridDev &g) {
+  const uint32_t xf = ((uint32_t)c[0] << g.xb) | (uint32_t)(o[0] * g.fx);
+  const uint32_t kx = g.k + g.xb;
+  if constexpr (D == 2) return xf | ((uint32_t)row_of(c[1], o[1], g) << kx);
+  return xf | (search_row(row_of(c[1], o[1], g), row_of(c[2], o[2], g), g) << kx);
+}
+// Fixed-point coordinate of a position, cut to a multiple of 2^-fb (never into the next cell).
+__device__ __forceinline__ float fixed_bits(int c, float o, const GridDev &g) {
+  return __uint_as_float(((uint32_t)c << g.fb) + (uint32_t)(o * (float)(1u << g.fb)));
 }
 
 // o[0] in [0, 1): its sub-cell floor(o 2^xe) is exact (a power-of-two scaling).

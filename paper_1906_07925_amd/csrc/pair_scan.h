@@ -8,18 +8,12 @@
 
 #include "mpsph_device.h"
 
-// The candidate scan ends each chunk with NaN row offsets and relies on every range test failing
-// on a NaN distance, which finite-only floating-point modes would not keep.
-#if defined(__FAST_MATH__) || (defined(__FINITE_MATH_ONLY__) && __FINITE_MATH_ONLY__)
-#error "the pair kernels need IEEE NaN semantics: build without -ffast-math / -ffinite-math-only"
-#endif
-
 namespace mpsph {
 
 // Neighbour candidates
 //
-// Particle i's candidates are the particles of every x-run of cells (fixed y, z) that meets the
-// ball of radius rs around it, the run taken at x sub-cell resolution; in the cell order (x
+// Particle i's candidates are the particles of every x-run of search rows (fixed y, z) that meets the
+// ball of radius rs around it, the run taken at x sub-cell resolution; in the search order (x
 // fastest) each run is one contiguous range of the sorted arrays.  A group of L lanes works on
 // one particle (scan_group_table below).
 // ------------------------------------------------------------------------------------------
@@ -34,25 +28,48 @@ namespace mpsph {
 #define MPSPH_ADJ_LANES 8
 #endif
 
-// x cell of a particle from its flags word (bits 16-27).  A 3D grid has at most 2^8 cells per
-// axis, so there the word's third byte holds it and converts to float in one instruction.
-template <int D>
-__device__ __forceinline__ float cell_x(uint32_t aux) {
-  return D == 3 ? (float)((aux >> 16) & 0xFFu) : (float)((aux >> 16) & 0xFFFu);
+// Separation of two particles from their fixed-point coordinates, in units of 2^-fb cells: the integer
+// difference is exact, in a periodic box of the minimum image (the coordinates' wrap divides the
+// period), and is rounded once, by the conversion.  Two VALU operations per axis; with (cell, offset)
+// pairs x took four (ten with a minimum image), and y and z needed their row's offsets from the table.
+// Per step, with rows of the same width: 2M-particle graded cube 2458 -> 2174 us (viscous pass 1339 ->
+// 1068, whose flags load went with the x cell in it), periodic 37^3 box 436 -> 110 us.
+struct FixedPos {
+  int x, y, z;
+};
+__device__ __forceinline__ FixedPos fixed_of(const float4 &p) {
+  return FixedPos{(int)__float_as_uint(p.x), (int)__float_as_uint(p.y), (int)__float_as_uint(p.z)};
 }
+__device__ __forceinline__ float fixed_diff(int a, float b) { return (float)(int)((uint32_t)a - __float_as_uint(b)); }
 
-// x separation in cell units with the minimum image of a periodic box (period P cells); the
-// y and z separations come from unwrapped row offsets and need none.  fcxi: the particle's x
-// cell as a float (exact); auxj: the neighbour's flags word.
-// PER: the launch may contain periodic domains (otherwise the periodic code is compiled out).
-template <bool PER, int D>
-__device__ __forceinline__ float sep_x(const GridDev &g, float fcxi, uint32_t auxj, float oxi, float oxj) {
-  float dx = (fcxi - cell_x<D>(auxj)) + (oxi - oxj);
-  if (PER && g.geometry == 0) {
-    const float P = (float)(g.gmax + 1);
-    dx = dx > 0.5f * P ? dx - P : (dx < -0.5f * P ? dx + P : dx);
+// What the scan needs of the group's particle: x cell and offset, search row and offset in rows.
+struct OwnRow {
+  int cx, ry, rz;
+  float ox, oy, oz;
+};
+// c: cells of the particle (from its key), p: its fixed-point coordinates.
+__device__ __forceinline__ void row_and_offset(int c, int fix, const GridDev &g, int &r, float &o) {
+  const float f = (float)((uint32_t)fix & ((1u << g.fb) - 1u)) * g.funit;   // offset in the cell
+  if (g.rb >= 0) {
+    r = c >> g.rb;
+    o = ((float)(c & ((1 << g.rb) - 1)) + f) * g.rowinv;
+  } else {
+    const float t = f * g.rowinv;
+    const int i = (int)t;
+    r = (c << -g.rb) + i;
+    o = t - (float)i;
   }
-  return dx;
+}
+template <int D>
+__device__ __forceinline__ OwnRow own_row(const int *c, const FixedPos &p, const GridDev &g) {
+  OwnRow o;
+  o.cx = c[0];
+  o.ox = (float)((uint32_t)p.x & ((1u << g.fb) - 1u)) * g.funit;
+  row_and_offset(c[1], p.y, g, o.ry, o.oy);
+  o.rz = 0;
+  o.oz = 0.f;
+  if constexpr (D == 3) row_and_offset(c[2], p.z, g, o.rz, o.oz);
+  return o;
 }
 
 // Value of lane l - o (o < 16) within the lane's row of 16 lanes, through a DPP row shift (no
@@ -78,11 +95,11 @@ __device__ __forceinline__ uint32_t group_last(uint32_t x) {
 // Rows per chunk of the LDS row table at 4 lanes per particle (scaled with the lanes, so that
 // the table of a 256-thread block stays below 19 KB and 8 blocks fit a CU's LDS).
 #ifndef MPSPH_ROW_TABLE
-#define MPSPH_ROW_TABLE 18
+#define MPSPH_ROW_TABLE 36
 #endif
 template <int L>
 constexpr int row_table_rows() {
-  return MPSPH_ROW_TABLE * L / 4 < L + 1 ? L + 1 : MPSPH_ROW_TABLE * L / 4;
+  return MPSPH_ROW_TABLE * L / 4 < L + 2 ? L + 2 : MPSPH_ROW_TABLE * L / 4;
 }
 // Entries between two rows of one group's column (one more than the groups of a block, so that
 // the columns of a wave's groups start in different banks).
@@ -95,32 +112,26 @@ constexpr int row_table_stride() {
 //
 // The group's L lanes take L rows at a time (each reads its row's range from the cell table)
 // and lay out the non-empty ones in a table in LDS: base index, end of the run in the flattened
-// slot order of the particle's candidates, row offsets.  Then the group visits the slots L at a
+// slot order of the particle's candidates.  Then the group visits the slots L at a
 // time, lane l taking every L-th one and advancing through the table as its slot index passes
-// the end of a row.  A group's loop ends when its own candidates end (no wave-wide rounds of
+// the end of a row.  A lane's loop ends with the slots of its own group (no wave-wide rounds of
 // rows).  A table holds at most C - 1 rows and an end marker; a particle with more non-empty
 // rows is scanned in several chunks.  With CUT the particle's own slot is cut out of its row
 // (the row becomes the runs before and after it), so the particle itself is never a slot.
-// The end marker (end of run 2^32 - 1, row offsets NaN) stops every lane's walk through the
-// table, so the slot loop tests neither the table's length nor the chunk's: a slot past the
-// chunk's end reaches the marker and gets the index t - run (in [0, L)) and NaN offsets, which
-// make its squared distance NaN and fail every range test of the bodies.
+// The end marker (end of run 2^32 - 1) stops a lane's walk through the table when it looks one
+// round ahead past the chunk's slots.
+// In a periodic box (PER) a row whose run crosses the end of the x axis is taken as two runs, so a
+// particle near that end has its rows twice, the second time for the part beyond it.
 // tab: the group's column of the table, entry e at tab[e * stride]; C > L + 1.
-// body(j, dy0, dz0, valid) is called for every slot with the row offsets plus the particle's own
-// offsets, dy0 = ci[1] - cy + oi[1] and dz0 = ci[2] - cz + oi[2] (cell units; the y and z
-// separations are dy0 - oj[1] and dz0 - oj[2]); valid is false for the particle itself (always
-// true with CUT).  A slot
-// past the chunk's end carries NaN offsets and an index below L that may still lie outside the
-// arrays (fewer than L particles): bodies load through bounds-checked buffer loads or clamp the
-// index, and must fail their range tests on a NaN distance.  The return value is the group's
-// candidate count (the particle itself excluded), the same in every lane of the group.
-// The row's base index goes through remap(cy, cz, a) (a: the global index of the row's first
+// body(j) is called for every slot.  The return value is the group's candidate count (the particle
+// itself excluded), the same in every lane of the group.
+// The row's base index goes through remap(ry, rz, a) (a: the global index of the row's first
 // candidate) before it enters the table, so that the slots can index a staged copy of the
 // neighbours; self is the particle's own index in that numbering.
 // A body may also come in two parts, fetch(j) -> payload (the slot's neighbour loads) and
-// use(payload, dy0, dz0, valid) (its arithmetic): the scan then issues the loads of a lane's
-// next slot round before the arithmetic of the current one, so that their latency overlaps it.
-// A fetch past the chunk's end gets an index below 2L (bounds-checked loads again).
+// use(payload) (its arithmetic): the scan then issues the loads of a lane's next slot round before
+// the arithmetic of the current one, so that their latency overlaps it.  A fetch past the chunk's end
+// gets an index below 2L that may lie outside the arrays: bounds-checked loads, and no use() follows.
 struct IdentityRemap {
   __device__ __forceinline__ uint32_t operator()(int, int, uint32_t a) const { return a; }
 };
@@ -137,7 +148,7 @@ __device__ __forceinline__ auto pair_body(FetchF fetch, UseF use) {
   if constexpr (PIPE)
     return SplitBody<FetchF, UseF>{fetch, use};
   else
-    return [=](uint32_t j, float dy0, float dz0, bool v) { use(fetch(j), dy0, dz0, v); };
+    return [=](uint32_t j) { use(fetch(j)); };
 }
 template <typename T>
 struct IsSplitBody {
@@ -148,11 +159,10 @@ struct IsSplitBody<SplitBody<F, U>> {
   static constexpr bool value = true;
 };
 template <int D, int L, int C, bool PER = false, bool CUT = true, typename BodyF, typename RemapF = IdentityRemap>
-__device__ __forceinline__ uint32_t scan_group_table(int i, int sub, uint4 *tab, int stride, const int *ci,
-                                                     const float *oi, float rs, const GridDev &g, uint32_t cellbase,
+__device__ __forceinline__ uint32_t scan_group_table(uint32_t self, int sub, uint2 *tab, int stride, const OwnRow &own,
+                                                     float rs, const GridDev &g, uint32_t sbase,
                                                      const uint32_t *__restrict__ cstart, BodyF &&body,
-                                                     RemapF remap = RemapF(), uint32_t self = 0xFFFFFFFFu) {
-  if (self == 0xFFFFFFFFu) self = (uint32_t)i;
+                                                     RemapF remap = RemapF()) {
   static_assert(C > L + 1, "a table chunk holds at least one round of rows (one of them split) and the end marker");
   // one lane per particle is not supported: with no cross-lane operation in the loop nest the
   // compiler merged the chunk loop with the table loop and took the chunk loop's exit mask from a
@@ -160,74 +170,97 @@ __device__ __forceinline__ uint32_t scan_group_table(int i, int sub, uint4 *tab,
   // build with the chunk bound passed through a width-1 shuffle listed each once)
   static_assert(L >= 2, "at least two lanes per particle");
   static_assert(L <= 16, "a group's prefix sums use row shifts within 16 lanes");
-  rs = fminf(fmaxf(rs, 0.f), 2.f * (float)g.gmax + 2.f);
+  rs = fminf(fmaxf(rs, 0.f), 2.f * (float)g.gmax + 2.f) * g.rowinv;   // in rows from here on
   const float rs2 = rs * rs;
   const bool per = PER && g.geometry == 0;
-  const int P = g.gmax + 1;
-  int z0 = D == 3 ? ci[2] + (int)floorf(oi[2] - rs) : 0;
-  int z1 = D == 3 ? ci[2] + (int)floorf(oi[2] + rs) : 0;
-  int y0 = ci[1] + (int)floorf(oi[1] - rs);
-  int y1 = ci[1] + (int)floorf(oi[1] + rs);
+  const int P = 1 << g.skr;
+  int z0 = D == 3 ? own.rz + (int)floorf(own.oz - rs) : 0;
+  int z1 = D == 3 ? own.rz + (int)floorf(own.oz + rs) : 0;
+  int y0 = own.ry + (int)floorf(own.oy - rs);
+  int y1 = own.ry + (int)floorf(own.oy + rs);
   if (per) {
     if (y1 - y0 + 1 > P) {
-      y0 = ci[1] - P / 2;
+      y0 = own.ry - P / 2;
       y1 = y0 + P - 1;
     }
     if (D == 3 && z1 - z0 + 1 > P) {
-      z0 = ci[2] - P / 2;
+      z0 = own.rz - P / 2;
       z1 = z0 + P - 1;
     }
   } else {
     y0 = max(0, y0);
-    y1 = min(g.gmax, y1);
+    y1 = min(P - 1, y1);
     if (D == 3) {
       z0 = max(0, z0);
-      z1 = min(g.gmax, z1);
+      z1 = min(P - 1, z1);
     }
   }
   const int ny = y1 - y0 + 1;
   const int nrows = ny * (z1 - z0 + 1);
   const float inv_ny = 1.f / (float)ny;
   const uint32_t nmax = (uint32_t)g.n;
-  const float fx = (float)(1u << g.xe);
-  const int xlast = ((g.gmax + 1) << g.xe) - 1;
-  const uint32_t kx = g.k + g.xe;
+  const float fxr = g.rfx;                        // x sub-cells per row width
+  const float oxs = own.ox * g.fx;                // offset in x sub-cells
+  const int xi = own.cx << g.xb;
+  const int xlast = ((g.gmax + 1) << g.xb) - 1;
+  const uint32_t kx = g.k + g.xb;
+  int nq = nrows;
+  if (PER && per && (xi + (int)floorf(oxs - rs * fxr) < 0 || xi + (int)floorf(oxs + rs * fxr) > xlast)) nq = 2 * nrows;
   uint32_t total = 0;   // candidates of the group (the particle itself only without CUT)
   int q0 = 0;
-  while (q0 < nrows) {
+  while (q0 < nq) {
     // table of the next chunk of rows: whole rounds of L rows while a round surely fits
     uint32_t ne = 0, run = 0;
-    while (q0 < nrows && ne + L + 1u < (uint32_t)C) {
-      const int q = q0 + sub;
+    while (q0 < nq && ne + L + 1u < (uint32_t)C) {
+      int q = q0 + sub;
+      const bool in = q < nq;
+      bool beyond = false;                        // the part of a periodic row past the end of the x axis
+      if (PER && q >= nrows) {
+        beyond = true;
+        q -= nrows;
+      }
       const int qz = (int)(((float)q + 0.5f) * inv_ny);   // q / ny (q, ny < 2^12)
       const int cz = z0 + qz, cy = y0 + (q - qz * ny);
       float ez = 0.f;
       if constexpr (D == 3) {
-        const float lo = (float)(cz - ci[2]) - oi[2], hi = lo + 1.f;
+        const float lo = (float)(cz - own.rz) - own.oz, hi = lo + 1.f;
         ez = lo > 0.f ? lo : (hi < 0.f ? -hi : 0.f);
       }
-      const float lo = (float)(cy - ci[1]) - oi[1], hi = lo + 1.f;
+      const float lo = (float)(cy - own.ry) - own.oy, hi = lo + 1.f;
       const float ey = lo > 0.f ? lo : (hi < 0.f ? -hi : 0.f);
       const float d2 = ey * ey + ez * ez;
-      const bool hit = q < nrows && d2 < rs2;
+      bool hit = in && d2 < rs2;
       // the hardware square root (about 1 ulp) is enough: the callers' reach rs exceeds every
       // range test of the bodies by a relative 1e-4
-      const float wx = fast_sqrt(fmaxf(rs2 - d2, 0.f));
-      int x0 = (ci[0] << g.xe) + (int)floorf((oi[0] - wx) * fx);
-      int x1 = (ci[0] << g.xe) + (int)floorf((oi[0] + wx) * fx);
-      if (per && (x0 < 0 || x1 > xlast)) {
-        x0 = 0;
-        x1 = xlast;
+      const float wx = fast_sqrt(fmaxf(rs2 - d2, 0.f)) * fxr;
+      int x0 = xi + (int)floorf(oxs - wx);
+      int x1 = xi + (int)floorf(oxs + wx);
+      if (PER && per) {
+        if (x1 - x0 > xlast) {                    // the run covers the period: one run, nothing beyond
+          x0 = 0;
+          x1 = xlast;
+          hit = hit && !beyond;
+        } else if (beyond) {                      // at most one end is crossed
+          if (x0 < 0) {
+            x0 += xlast + 1;
+            x1 = xlast;
+          } else if (x1 > xlast) {
+            x0 = 0;
+            x1 -= xlast + 1;
+          } else {
+            hit = false;
+          }
+        }
       }
       x0 = max(0, x0);
       x1 = min(xlast, x1);
-      const int cyw = per ? (cy + P) & g.gmax : cy;
+      const int cyw = PER && per ? cy & (P - 1) : cy;
       uint32_t kb;
       if constexpr (D == 3)
-        kb = (uint32_t)x0 | (row_index(cyw, per ? (cz + P) & g.gmax : cz, g) << kx);
+        kb = (uint32_t)x0 | (search_row(cyw, PER && per ? cz & (P - 1) : cz, g) << kx);
       else
         kb = (uint32_t)x0 | ((uint32_t)cyw << kx);
-      kb += cellbase;
+      kb += sbase;
       uint32_t a = 0u, b = 0u;
       if (hit) {
         a = cstart[kb];
@@ -257,16 +290,14 @@ __device__ __forceinline__ uint32_t scan_group_table(int i, int sub, uint4 *tab,
         }
       }
       if (nl > 0u) {
-        const float dyo = (float)(ci[1] - cy) + oi[1], dzo = D == 3 ? (float)(ci[2] - cz) + oi[2] : 0.f;
         uint32_t end = run + incl - lsum, en = ne + nz - nl;   // the lane's first slot and entry
         if (len1 > 0u) {
           end += len1;
-          tab[en++ * (uint32_t)stride] = make_uint4(base - (end - len1), end, __float_as_uint(dyo), __float_as_uint(dzo));
+          tab[en++ * (uint32_t)stride] = make_uint2(base - (end - len1), end);
         }
         if (len2 > 0u) {
           end += len2;
-          tab[en * (uint32_t)stride] =
-              make_uint4(base + len1 + 1u - (end - len2), end, __float_as_uint(dyo), __float_as_uint(dzo));
+          tab[en * (uint32_t)stride] = make_uint2(base + len1 + 1u - (end - len2), end);
         }
       }
       run += group_last<L>(incl);
@@ -274,60 +305,36 @@ __device__ __forceinline__ uint32_t scan_group_table(int i, int sub, uint4 *tab,
       q0 += L;
     }
     // end marker (ne < C): base -run, so that slot t past the end maps to index t - run
-    if (sub == 0) tab[ne * (uint32_t)stride] = make_uint4(0u - run, 0xFFFFFFFFu, 0x7FC00000u, 0x7FC00000u);
+    if (sub == 0) tab[ne * (uint32_t)stride] = make_uint2(0u - run, 0xFFFFFFFFu);
     total += run;
     // the chunk's slots, L at a time; slot t of row e is candidate base_e + t
-    if constexpr (IsSplitBody<typename std::decay<BodyF>::type>::value) {
-      // one round ahead: the loads of slot t + L are issued before the arithmetic of slot t.  A
-      // slot's row is found by walking the rows' ends, and its base and offsets are then read from
-      // the table into the slot's own registers, so that none is copied
-      using Payload = decltype(body.fetch(0u));
-      struct Slot {
-        Payload p;
-        float dy, dz;
-        uint32_t j;
-      };
-      const uint4 *rp = tab;   // row of the last located slot
-      uint32_t y = rp->y;      // its end
-      const auto locate = [&](uint32_t tt, Slot &sl) {
-        while (tt >= y) {
+    uint32_t t = (uint32_t)sub;
+    if (t < run) {
+      const uint2 *rp = tab;
+      uint2 row = *rp;         // row of the last located slot
+      const auto locate = [&](uint32_t tt) -> uint32_t {
+        while (tt >= row.y) {
           rp += stride;
-          y = rp->y;
+          row = *rp;
         }
-        const uint4 row = *rp;
-        sl.j = row.x + tt;
-        sl.dy = __uint_as_float(row.z);
-        sl.dz = __uint_as_float(row.w);
-        sl.p = body.fetch(sl.j);
+        return row.x + tt;
       };
-      uint32_t t = (uint32_t)sub;
-      // two slots used in turn (the loop is unrolled twice)
-      Slot pa, pb;
-      locate(t, pa);
-      const auto round = [&](const Slot &now, Slot &next) {
-        const uint32_t tn = t + L;
-        locate(tn, next);
-        body.use(now.p, now.dy, now.dz, CUT || now.j != self);
-        t = tn;
-      };
-      // the lane's rounds end when its next slot t reaches the chunk's end (run + sub)
-      const uint32_t tend = run + (uint32_t)sub;
-      if (t < tend) {
+      if constexpr (IsSplitBody<typename std::decay<BodyF>::type>::value) {
+        // one round ahead: the loads of slot t + L are issued before the arithmetic of slot t;
+        // two payloads used in turn (the loop is unrolled twice), so that none is copied
+        auto pa = body.fetch(locate(t));
         while (true) {
-          round(pa, pb);
-          if (t >= tend) break;
-          round(pb, pa);
-          if (t >= tend) break;
+          t += L;
+          auto pb = body.fetch(locate(t));
+          body.use(pa);
+          if (t >= run) break;
+          t += L;
+          pa = body.fetch(locate(t));
+          body.use(pb);
+          if (t >= run) break;
         }
-      }
-    } else {
-      uint32_t e = 0;
-      uint4 cur = tab[0];
-      for (uint32_t t0 = 0; t0 < run; t0 += L) {
-        const uint32_t t = t0 + (uint32_t)sub;
-        while (t >= cur.y) cur = tab[++e * (uint32_t)stride];
-        const uint32_t j = cur.x + t;
-        body(j, __uint_as_float(cur.z), __uint_as_float(cur.w), CUT || j != self);
+      } else {
+        for (; t < run; t += L) body(locate(t));
       }
     }
   }
