@@ -138,7 +138,7 @@ __global__ __launch_bounds__(kBlock) void reorder_field(
     uint32_t *__restrict__ wkey, float4 *__restrict__ wpos, float4 *__restrict__ wfix, uint32_t *__restrict__ wjaux,
     uint32_t *__restrict__ wid, uint32_t *__restrict__ perm, uint32_t *__restrict__ dtslots) {
   const int t = blockIdx.x * kBlock + threadIdx.x;
-  if (t < nreset) dtslots[t] = kInfBits;
+  if (t < nreset) dtslots[t * kDtStride] = kInfBits;
   const int i = i0 + t;
   if (i >= i1) return;
   const uint32_t s = slots[i];
@@ -557,7 +557,7 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
                                    [&](int s, double x) {
     if (s < 12) out[s] = x;
     else if (s == 12) out[P_IFCP] = x;
-    else if (x < INFINITY) atomic_min_pos(&dtslots[d * kDtSlots + (lb & (kDtSlots - 1))], (float)x);   // one atomic per block
+    else if (x < INFINITY) atomic_min_pos(&dtslots[d * kDtWords + (lb & (kDtSlots - 1)) * kDtStride], (float)x);   // one atomic per block
   });
 }
 
@@ -619,7 +619,7 @@ __device__ __forceinline__ double slot_identity(int s) { return s == P_ELRMIN ? 
 __device__ __forceinline__ void close_domain_step(const DomDev &dd, const uint32_t *dtslots, double *md, double pairs,
                                                   double cand, double ifc, double ifcp, int64_t *stepctr) {
   float d1 = INFINITY;
-  for (int s = 0; s < kDtSlots; ++s) d1 = fminf(d1, __uint_as_float(dtslots[s]));
+  for (int s = 0; s < kDtSlots; ++s) d1 = fminf(d1, __uint_as_float(dtslots[s * kDtStride]));
   md[16] = d1 < INFINITY ? (double)d1 : 0.0;
   md[17] = d1 < INFINITY ? (double)(d1 * dd.sp.dt2_factor) : 0.0;
   // running totals since the last load (exact integers below 2^53)
@@ -714,7 +714,7 @@ __device__ __forceinline__ void close_step(const StepEnd &fin, const DomDev &dd,
   }
   __syncthreads();
   if (threadIdx.x == 0)
-    close_domain_step(dd, dtslots + d * kDtSlots, md, red[P_PAIRS], red[P_CAND], red[P_IFC], red[P_IFCP],
+    close_domain_step(dd, dtslots + d * kDtWords, md, red[P_PAIRS], red[P_CAND], red[P_IFC], red[P_IFCP],
                       fin.d0 + d == 0 ? fin.stepctr : nullptr);
 }
 
@@ -752,7 +752,7 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
   // dt1 is published in LDS and read again after the pair sum, so that no copy of it stays live
   // across the pair loop
   __shared__ float sdt1;
-  const float dt1 = read_dt1(dtslots + d * kDtSlots);
+  const float dt1 = read_dt1(dtslots + d * kDtWords);
   if (threadIdx.x == 0) sdt1 = dt1;
   __syncthreads();
   if (li < doms[d].n) {
@@ -2182,7 +2182,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   L.stepctr = take(8);
   L.bad = take(4);
   L.counts = take(cell_count_words(L.scells) * 4);
-  L.dtslots = take((size_t)L.ndom * kDtSlots * 4);
+  L.dtslots = take((size_t)L.ndom * kDtWords * 4);
   L.domdone = take((size_t)L.ndom * 4);
   L.paircount = take(8);
   L.queue = take(32 * 4);                   // work queues of the persistent pair passes (2 x 16 words)
@@ -2397,7 +2397,7 @@ void launch_pass1_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st) {
       ctx->at<float4>(L.w_pos), ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.cstart),
       ctx->at<float4>(L.acc),
       dbg ? ctx->at<float>(L.rho) : nullptr, dbg ? ctx->at<float>(L.nn) : nullptr,
-      dbg ? ctx->at<float>(L.aabs) : nullptr, ctx->at<uint32_t>(L.dtslots) + (size_t)gr.d0 * kDtSlots,
+      dbg ? ctx->at<float>(L.aabs) : nullptr, ctx->at<uint32_t>(L.dtslots) + (size_t)gr.d0 * kDtWords,
       ctx->at<double>(L.metrics) + (size_t)gr.d0 * 32, ctx->at<double>(L.partials));
 }
 
@@ -2424,7 +2424,7 @@ void launch_pass2_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st, float4 *at_
       gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos),
       ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),
       ctx->at<float4>(L.acc),
-      ctx->at<uint32_t>(L.dtslots) + (size_t)gr.d0 * kDtSlots, ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
+      ctx->at<uint32_t>(L.dtslots) + (size_t)gr.d0 * kDtWords, ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
       ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.s_cell), ctx->at<uint32_t>(L.counts), at_o, v_o,
       ctx->at<double>(L.partials), step_end(ctx, gr.d0));
 }
@@ -2772,7 +2772,7 @@ GradPlan grad_plan(int64_t n, uint32_t ncells, int nck, int ckpt, int nb1, int n
   P.tp_at = ttake(nn * 16);
   P.tp_v = ttake(nn * 16);
   P.tp_cstart = ttake(((size_t)ncells + 1) * 4);
-  P.tp_dts = ttake(kDtSlots * 4);
+  P.tp_dts = ttake(kDtWords * 4);
   P.tp_stride = t;
   P.tp0 = take(P.tp_stride * ckpt);
   P.xbar = take(nn * 16);
@@ -2873,7 +2873,7 @@ int record_step(GradRun &R, int m) {
   HIP_OK(hipMemcpyAsync(b + R.P.tp_acc, ctx->at<float4>(L.acc), nn * 16, hipMemcpyDeviceToDevice, R.st));
   HIP_OK(hipMemcpyAsync(b + R.P.tp_cstart, ctx->at<uint32_t>(L.cstart), ((size_t)L.scells + 1) * 4,
                         hipMemcpyDeviceToDevice, R.st));
-  HIP_OK(hipMemcpyAsync(b + R.P.tp_dts, ctx->at<uint32_t>(L.dtslots), kDtSlots * 4, hipMemcpyDeviceToDevice, R.st));
+  HIP_OK(hipMemcpyAsync(b + R.P.tp_dts, ctx->at<uint32_t>(L.dtslots), kDtWords * 4, hipMemcpyDeviceToDevice, R.st));
   return MPSPH_OK;
 }
 
@@ -3408,12 +3408,12 @@ int mpsph_debug_fields(mpsph_ctx *ctx, int32_t which, float *d_out) {
       for (int d = 0; d < L.ndom; ++d) vs[d] = (float)(0.5 * m[(size_t)d * 32 + 16]);
     } else {
       // the drift is v dt2, the product the integrator forms (Eq. 28)
-      std::vector<float> slots((size_t)L.ndom * kDtSlots);
+      std::vector<float> slots((size_t)L.ndom * kDtWords);
       HIP_OK(hipMemcpyAsync(slots.data(), ctx->at<float>(L.dtslots), slots.size() * 4, hipMemcpyDeviceToHost, ctx->stream));
       HIP_OK(hipStreamSynchronize(ctx->stream));
       for (int d = 0; d < L.ndom; ++d) {
-        const float *sl = slots.data() + (size_t)d * kDtSlots;
-        const float d1 = *std::min_element(sl, sl + kDtSlots);
+        float d1 = INFINITY;
+        for (int q = 0; q < kDtSlots; ++q) d1 = std::min(d1, slots[(size_t)d * kDtWords + q * kDtStride]);
         vs[d] = (std::isfinite(d1) ? d1 : 0.f) * (float)dt2_factor(&ctx->dom[d].p);
       }
     }

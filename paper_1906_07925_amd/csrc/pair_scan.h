@@ -383,7 +383,7 @@ __device__ __forceinline__ float group_min(float x) {
 
 // First time step (Eq. 29 with v = 0): minimum over the domain's slots, every lane gets it.
 __device__ __forceinline__ float read_dt1(const uint32_t *slots) {
-  float v = __uint_as_float(slots[threadIdx.x & (kDtSlots - 1)]);
+  float v = __uint_as_float(slots[(threadIdx.x & (kDtSlots - 1)) * kDtStride]);
   for (int off = kWave / 2; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off, kWave));
   v = v < INFINITY ? v : 0.f;
   // the same value in every lane: held as a wave-uniform (scalar) value
