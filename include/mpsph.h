@@ -262,7 +262,7 @@ MPSPH_API int mpsph_load(mpsph_ctx *ctx, const float *d_pos, const int32_t *d_co
 
 /* Sets the cell exponent (cells per axis 2^cell_log2 for every domain; -1: the library's size
  * rule, or the value given at creation) and the lanes per particle of the pair kernels (2, 4
- * or 8; 4 at creation).  The workspace is re-planned (a library-owned workspace grows when
+ * or 8; a context that was never configured uses 4 in 2D and 8 in 3D).  The workspace is re-planned (a library-owned workspace grows when
  * needed); the loaded state is dropped, so call mpsph_load next.  Errors: MPSPH_E_INVALID,
  * MPSPH_E_STATE, MPSPH_E_UNSUPPORTED (grid too large), MPSPH_E_NOMEM (does not fit a caller
  * workspace; the context is unchanged). */

@@ -1053,11 +1053,17 @@ __device__ __forceinline__ void queue_done(uint32_t *q) {
   }
 }
 
-template <int DM, int L, bool PER, bool DBG>
+// Row-table entries of a launch that serves 2D blocks at L lanes and 3D blocks at L3.
+template <int L, int L3>
+constexpr int queue_table() {
+  constexpr int a = row_table_rows<L>() * row_table_stride<L>(), b = row_table_rows<L3>() * row_table_stride<L3>();
+  return a > b ? a : b;
+}
+template <int DM, int L, int L3, bool PER, bool DBG>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_density_force_queue(int b0, int nb2, int nb,
                                                                                         uint32_t *queue,
                                                                                         MPSPH_PASS1_PARAMS) {
-  __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ __align__(16) uint2 rowtab[queue_table<L, L3>()];
   __shared__ int sitem;
   for (;;) {
     __syncthreads();   // the previous block's LDS (row table, reductions) is no longer read
@@ -1067,19 +1073,19 @@ __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_density_forc
     if (it >= nb) break;
     if constexpr (DM == 5) {
       if (it < nb2) density_force_block<2, L, PER, DBG, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
-      else density_force_block<3, L, PER, DBG, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
+      else density_force_block<3, L3, PER, DBG, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
     } else {
-      density_force_block<DM, L, PER, DBG, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
+      density_force_block<DM, DM == 3 ? L3 : L, PER, DBG, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
     }
   }
   if (threadIdx.x == 0) queue_done(queue);
 }
 
-template <int DM, int L, bool PER>
+template <int DM, int L, int L3, bool PER>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_integrate_queue(int b0, int nb2, int nb,
                                                                                             uint32_t *queue,
                                                                                             MPSPH_PASS2_PARAMS) {
-  __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
+  __shared__ __align__(16) uint2 rowtab[queue_table<L, L3>()];
   __shared__ int sitem;
   for (;;) {
     __syncthreads();   // the previous block's LDS (row table, reductions) is no longer read
@@ -1089,9 +1095,9 @@ __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_inte
     if (it >= nb) break;
     if constexpr (DM == 5) {
       if (it < nb2) viscous_integrate_block<2, L, PER, false>(b0 + it, rowtab, MPSPH_PASS2_ARGS);
-      else viscous_integrate_block<3, L, PER, false>(b0 + it, rowtab, MPSPH_PASS2_ARGS);
+      else viscous_integrate_block<3, L3, PER, false>(b0 + it, rowtab, MPSPH_PASS2_ARGS);
     } else {
-      viscous_integrate_block<DM, L, PER, false>(b0 + it, rowtab, MPSPH_PASS2_ARGS);
+      viscous_integrate_block<DM, DM == 3 ? L3 : L, PER, false>(b0 + it, rowtab, MPSPH_PASS2_ARGS);
     }
   }
   if (threadIdx.x == 0) queue_done(queue);
@@ -2062,7 +2068,9 @@ struct Layout {
   uint32_t ncells = 0;  // cells of all domains (exported cell table)
   uint32_t scells = 0;  // cells of the search table
   int nblocks_pair = 0, nrows = 0;
-  int lanes = MPSPH_LANES;  // lanes per particle in the forward pair kernels
+  // lanes per particle in the forward pair kernels of 2D and of 3D domains
+  int lanes = MPSPH_LANES, lanes3 = MPSPH_LANES_3D;
+  int lanes_of(int dim) const { return dim == 3 ? lanes3 : lanes; }
   int64_t chunk = 1;  // block partials per first-level reduction row
   bool fused = false; // the viscous pass closes the step (StepEnd)
   size_t n_rbf = 0;
@@ -2078,7 +2086,12 @@ struct Layout {
 int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
   Layout L;
   L.ndom = (int)doms.size();
-  L.lanes = lanes;
+  int64_t all = 0;
+  for (const auto &dm : doms) all += dm.n;
+  // lanes 0: a context that was never configured; the wider groups only where the thread indices allow them
+  L.lanes = lanes > 0 ? lanes : MPSPH_LANES;
+  L.lanes3 = lanes > 0 ? lanes : (all * MPSPH_LANES_3D < ((int64_t)1 << 31) ? MPSPH_LANES_3D : MPSPH_LANES);
+  const int most = std::max(L.lanes, doms.empty() || std::none_of(doms.begin(), doms.end(), [](const Domain &d) { return d.p.dim == 3; }) ? 0 : L.lanes3);
   int64_t uoff = 0, xoff = 0;
   for (int d = 0; d < L.ndom; ++d) {
     doms[d].uidx = d;
@@ -2110,7 +2123,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     dm.cellbase = (uint32_t)cells;
     dm.sbase = (uint32_t)scells;
     dm.blk0 = (int)blocks;
-    dm.nblk = std::max(1, (int)((dm.n * lanes + kBlock - 1) / kBlock));   // an empty domain's one block closes its step
+    dm.nblk = std::max(1, (int)((dm.n * L.lanes_of(dm.p.dim) + kBlock - 1) / kBlock));   // an empty domain's one block closes its step
     dm.rbf0 = nrbf;
     dm.gphi0 = ngphi;
     dm.gs0 = ngs;
@@ -2122,7 +2135,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     blocks += dm.nblk;
     nrbf += (size_t)dm.p.n_rbf;
     // thread indices of the pair kernels (particles x lanes) stay below 2^31
-    if (n > ((int64_t)1 << 30) || n * lanes >= ((int64_t)1 << 31) || cells > ((uint64_t)1 << 28) ||
+    if (n > ((int64_t)1 << 30) || n * most >= ((int64_t)1 << 31) || cells > ((uint64_t)1 << 28) ||
         blocks > ((int64_t)1 << 30))
       return MPSPH_E_UNSUPPORTED;
     g.nd += 1;
@@ -2404,7 +2417,7 @@ void launch_pass1_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st) {
 template <int D>
 void launch_pass1(mpsph_ctx *ctx, const Group &gr, hipStream_t st, EventHook *hk) {
   if (hk) hk->begin("pass_density_force");
-  const int sel = ctx->L.lanes * 2 + (gr.periodic ? 1 : 0);
+  const int sel = ctx->L.lanes_of(D) * 2 + (gr.periodic ? 1 : 0);
   switch (sel) {
     case 4: launch_pass1_l<D, 2, false>(ctx, gr, st); break;
     case 5: launch_pass1_l<D, 2, true>(ctx, gr, st); break;
@@ -2437,7 +2450,7 @@ void launch_pass2(mpsph_ctx *ctx, const Group &gr, hipStream_t st, EventHook *hk
   float4 *at_o = at_rec ? at_rec : (dbg ? ctx->at<float4>(L.at) : nullptr);
   float4 *v_o = v_rec ? v_rec : (dbg ? ctx->at<float4>(L.v) : nullptr);
   if (hk) hk->begin("pass_viscous_integrate");
-  const int sel = L.lanes * 2 + (gr.periodic ? 1 : 0);
+  const int sel = L.lanes_of(D) * 2 + (gr.periodic ? 1 : 0);
   switch (sel) {
     case 4: launch_pass2_l<D, 2, false>(ctx, gr, st, at_o, v_o); break;
     case 5: launch_pass2_l<D, 2, true>(ctx, gr, st, at_o, v_o); break;
@@ -2454,11 +2467,11 @@ void launch_pass2(mpsph_ctx *ctx, const Group &gr, hipStream_t st, EventHook *hk
 constexpr int kQueueBlocksPerCU = 8;   // blocks of the pair kernels resident per CU (8 waves per SIMD)
 int queue_grid(const mpsph_ctx *ctx, int nb) { return std::max(1, std::min(nb, ctx->cus * kQueueBlocksPerCU)); }
 
-template <int DM, int L_, bool PER>
+template <int DM, int L_, int L3_, bool PER>
 void launch_pass1_queue_l(mpsph_ctx *ctx, int b0, int nb2, int nb, hipStream_t st) {
   const Layout &L = ctx->L;
   const bool dbg = ctx->dom[0].p.debug != 0;
-  auto kern = dbg ? pass_density_force_queue<DM, L_, PER, true> : pass_density_force_queue<DM, L_, PER, false>;
+  auto kern = dbg ? pass_density_force_queue<DM, L_, L3_, PER, true> : pass_density_force_queue<DM, L_, L3_, PER, false>;
   kern<<<queue_grid(ctx, nb), kBlock, 0, st>>>(
       b0, nb2, nb, ctx->at<uint32_t>(L.queue), ctx->at<DomDev>(L.doms), L.ndom, ctx->at<int64_t>(L.stepctr),
       ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos), ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux),
@@ -2467,11 +2480,11 @@ void launch_pass1_queue_l(mpsph_ctx *ctx, int b0, int nb2, int nb, hipStream_t s
       ctx->at<double>(L.partials));
 }
 
-template <int DM, int L_, bool PER>
+template <int DM, int L_, int L3_, bool PER>
 void launch_pass2_queue_l(mpsph_ctx *ctx, int b0, int nb2, int nb, hipStream_t st) {
   const Layout &L = ctx->L;
   const bool dbg = ctx->dom[0].p.debug != 0;
-  pass_viscous_integrate_queue<DM, L_, PER><<<queue_grid(ctx, nb), kBlock, 0, st>>>(
+  pass_viscous_integrate_queue<DM, L_, L3_, PER><<<queue_grid(ctx, nb), kBlock, 0, st>>>(
       b0, nb2, nb, ctx->at<uint32_t>(L.queue) + 16, ctx->at<DomDev>(L.doms), L.ndom, ctx->at<uint32_t>(L.w_key),
       ctx->at<float4>(L.w_pos), ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id),
       ctx->at<uint32_t>(L.cstart), ctx->at<float4>(L.acc), ctx->at<uint32_t>(L.dtslots), ctx->at<uint32_t>(L.s_key),
@@ -2482,17 +2495,22 @@ void launch_pass2_queue_l(mpsph_ctx *ctx, int b0, int nb2, int nb, hipStream_t s
 
 template <int DM>
 void launch_queue_dm(mpsph_ctx *ctx, int pass, int b0, int nb2, int nb, bool per, hipStream_t st) {
-  const int sel = ctx->L.lanes * 2 + (per ? 1 : 0);
-#define MPSPH_QUEUE_CASE(LN, P)                                 \
-  if (pass == 1) launch_pass1_queue_l<DM, LN, P>(ctx, b0, nb2, nb, st); \
-  else launch_pass2_queue_l<DM, LN, P>(ctx, b0, nb2, nb, st);
-  switch (sel) {
-    case 4: MPSPH_QUEUE_CASE(2, false) break;
-    case 5: MPSPH_QUEUE_CASE(2, true) break;
-    case 16: MPSPH_QUEUE_CASE(8, false) break;
-    case 17: MPSPH_QUEUE_CASE(8, true) break;
-    case 9: MPSPH_QUEUE_CASE(4, true) break;
-    default: MPSPH_QUEUE_CASE(4, false)
+  const Layout &L = ctx->L;
+#define MPSPH_QUEUE_CASE(LN, LN3)                                                  \
+  if (pass == 1 && per) launch_pass1_queue_l<DM, LN, LN3, true>(ctx, b0, nb2, nb, st); \
+  else if (pass == 1) launch_pass1_queue_l<DM, LN, LN3, false>(ctx, b0, nb2, nb, st);  \
+  else if (per) launch_pass2_queue_l<DM, LN, LN3, true>(ctx, b0, nb2, nb, st);         \
+  else launch_pass2_queue_l<DM, LN, LN3, false>(ctx, b0, nb2, nb, st);
+  if constexpr (DM == 5) {
+    if (L.lanes != L.lanes3) {   // never configured
+      MPSPH_QUEUE_CASE(MPSPH_LANES, MPSPH_LANES_3D)
+      return;
+    }
+  }
+  switch (L.lanes_of(DM)) {
+    case 2: MPSPH_QUEUE_CASE(2, 2) break;
+    case 8: MPSPH_QUEUE_CASE(8, 8) break;
+    default: MPSPH_QUEUE_CASE(4, 4)
   }
 #undef MPSPH_QUEUE_CASE
 }
@@ -2613,7 +2631,7 @@ int build_domains(int32_t ndom, const mpsph_params *params, const int64_t *n, st
   doms->resize(ndom);
   for (int d = 0; d < ndom; ++d)
     if ((rc = make_domain(&params[d], n[d], &(*doms)[d])) != MPSPH_OK) return rc;
-  return plan(*doms, MPSPH_LANES, L);
+  return plan(*doms, 0, L);
 }
 
 // Re-derives every domain's cell grid -- the cell exponent of the size rule plus kdelta for

@@ -17,12 +17,17 @@ namespace mpsph {
 // fastest) each run is one contiguous range of the sorted arrays.  A group of L lanes works on
 // one particle (scan_group_table below).
 // ------------------------------------------------------------------------------------------
-// Lanes per particle of the pair kernels of a context that is not tuned (mpsph_configure and
-// mpsph_autotune choose 2, 4 or 8), and of the adjoint's pair kernels.  Measured: 8 lanes are the
-// fastest on the 2M-particle graded cube, 4 on the RBF cube's forward steps (8 lanes: 4 % slower)
-// and equal on the 64-domain batch; the adjoint's pair kernels run faster at 8.
+// Lanes per particle of the pair kernels of a context that was never configured (mpsph_configure and
+// mpsph_autotune choose 2, 4 or 8), and of the adjoint's pair kernels.  Measured per step at 4 / 8 lanes:
+// 3D 8192 particles 77 / 70 us, 20,011 87 / 74, 100,003 157 / 142, 10^6 775 / 695, 2M 2316 / 2184; 2D 4096
+// 47 / 46, 262,144 125 / 137.  A 2D particle has 20 neighbours: at 8 lanes its slots are three rounds and
+// the row table and the epilogue of twice the blocks cost more than the shorter loops save.  (16 lanes:
+// 8192 particles 65, 100,003 151, 10^6 835 us.)
 #ifndef MPSPH_LANES
 #define MPSPH_LANES 4
+#endif
+#ifndef MPSPH_LANES_3D
+#define MPSPH_LANES_3D 8
 #endif
 #ifndef MPSPH_ADJ_LANES
 #define MPSPH_ADJ_LANES 8

@@ -231,7 +231,7 @@ class Relaxer:
         self.nfloat = sum(k * d for k, d in zip(ns, self.dims))   # floats of a position array
         made = [make_params(sp, s0=z, cell_log2=cell_log2, debug=debug) for sp, z in zip(specs, s0s)]
         self.params = (Params * self.ndom)(*[m[0] for m in made])
-        self.lanes = 4
+        self.lanes = 8 if 3 in self.dims else 4   # of the 3D domains, where a batch has both
         self._keep = [m[1] for m in made]
         if stream is None:
             stream = torch.cuda.current_stream()
