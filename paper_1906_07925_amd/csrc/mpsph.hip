@@ -607,32 +607,35 @@ __device__ __forceinline__ int type_from_faces(int nf, int d) {
   return nf <= 0 ? 0 : (nf == 1 ? 1 : (nf == 2 ? (d == 3 ? 2 : 3) : 3));
 }
 
-// Combine partials slot by slot: sums, or min / max for the slots that hold extrema.
-__device__ __forceinline__ double combine_slot(int s, double a, double b) {
-  return (s == P_EMAX || s == P_ELRMAX) ? fmax(a, b) : (s == P_ELRMIN ? fmin(a, b) : a + b);
-}
-__device__ __forceinline__ double slot_identity(int s) { return s == P_ELRMIN ? INFINITY : 0.0; }
+// Combines partials of one slot: sums, or min / max for the slots that hold extrema.  All three are formed
+// and one is selected: as branches, which diverge over the slots of a wave, the step's end took 8 us.
+struct SlotOp {
+  bool mx, mn;
+  __device__ __forceinline__ explicit SlotOp(int s) : mx(s == P_EMAX || s == P_ELRMAX), mn(s == P_ELRMIN) {}
+  __device__ __forceinline__ double identity() const { return mn ? INFINITY : 0.0; }
+  __device__ __forceinline__ double operator()(double a, double b) const {
+    const double sum = a + b, hi = fmax(a, b), lo = fmin(a, b);
+    return mx ? hi : (mn ? lo : sum);
+  }
+};
 
-// End of a domain's step by one thread, after the slots 0..15 of its metrics block md are known: 16: dt1,
-// 17: dt2, 18..20: running totals of pairs, candidates and steps, then the automatic t0.  stepctr
-// (may be null) is the context's step counter, advanced with its first domain.
-__device__ __forceinline__ void close_domain_step(const DomDev &dd, const uint32_t *dtslots, double *md, double pairs,
-                                                  double cand, double ifc, double ifcp, int64_t *stepctr) {
-  float d1 = INFINITY;
-  for (int s = 0; s < kDtSlots; ++s) d1 = fminf(d1, __uint_as_float(dtslots[s * kDtStride]));
-  md[16] = d1 < INFINITY ? (double)d1 : 0.0;
-  md[17] = d1 < INFINITY ? (double)(d1 * dd.sp.dt2_factor) : 0.0;
+// End of a domain's step by one thread, after the slots 0..15 of its metrics block md are known (red): 16: dt1,
+// 17: dt2, 18..20: running totals of pairs, candidates and steps (tot: their old values), then the
+// automatic t0.  stepctr (may be null) is the context's step counter, advanced with its first domain.
+__device__ __forceinline__ void close_domain_step(const StepDev &sp, float d1, const double *tot, double *md,
+                                                  const double *red, int64_t *stepctr) {
+  md[16] = (double)d1;
+  md[17] = (double)(d1 * sp.dt2_factor);
   // running totals since the last load (exact integers below 2^53)
-  md[18] += pairs;
-  md[19] += cand;
-  md[20] += 1.0;
+  md[18] = tot[0] + red[P_PAIRS];
+  md[19] = tot[1] + red[P_CAND];
+  md[20] = tot[2] + 1.0;
   // automatic t0 (reading of the paper's "topology static for some iterations"): the
   // interface-pair count and the number of particles with an interface pair stay within
   // t0_tol of a reference for t0_window steps; otherwise the reference restarts here
-  const StepDev &sp = dd.sp;
   if (sp.auto_t0 && !(md[kAutoT0] > 0.0)) {
-    const double t = md[20] - 1.0;  // index of this step since the load
-    const double I = ifc * 0.5, P = ifcp;
+    const double t = tot[2];  // index of this step since the load
+    const double I = red[P_IFC] * 0.5, P = red[P_IFCP];
     const double tol = (double)sp.t0_tol;
     if (t == 0.0 || fabs(I - md[kAutoT0 + 1]) > tol * md[kAutoT0 + 1] ||
         fabs(P - md[kAutoT0 + 2]) > tol * md[kAutoT0 + 2]) {
@@ -647,7 +650,7 @@ __device__ __forceinline__ void close_domain_step(const DomDev &dd, const uint32
 }
 
 // The step's end: the block partials of each domain reduced to its metrics block, its step closed.
-// Contexts whose domains all have at most kFusedChunk pair-kernel blocks close it inside the viscous
+// Contexts whose domains all have at most kFusedBlocks pair-kernel blocks close it inside the viscous
 // pass: the last block of a domain to finish reduces the domain's partials.  The others launch
 // finalize after it, one block per reduction row; the last row of a domain reduces the domain's rows.
 // (The viscous pass of larger grids gains nothing from closing the step: every block waits about
@@ -684,38 +687,65 @@ __device__ __forceinline__ bool last_to_finish(uint32_t *counter, uint32_t total
   return last;
 }
 
-// Rows [0, n) of kNumPartials slots combined in a fixed order; the result of slot s in thread s < kNumPartials.
-// red: kBlock doubles of LDS, free after the next barrier.
+// Rows [0, n) of kNumPartials slots combined in a fixed order; the result of slot s in the threads with
+// threadIdx.x mod kNumPartials = s.  red: kBlock / kWave * kNumPartials doubles of LDS.
+// SAME: rows that other blocks of the same launch wrote.
+template <bool SAME>
 __device__ __forceinline__ double combine_rows(const double *rows, int n, double *red) {
+  static_assert(kNumPartials == 16, "slot and row of a lane");
   const int s = threadIdx.x & (kNumPartials - 1), r0 = threadIdx.x / kNumPartials;
-  double acc = slot_identity(s);
-#pragma unroll 4
-  for (int r = r0; r < n; r += kBlock / kNumPartials) acc = combine_slot(s, acc, agent_load(&rows[(size_t)r * kNumPartials + s]));
-  red[threadIdx.x] = acc;
+  constexpr int kAhead = 8;      // rows in flight per thread
+  const SlotOp op(s);
+  double acc = op.identity();
+#pragma unroll 1
+  for (int r = r0; r < n; r += kAhead * (kBlock / kNumPartials)) {
+    double v[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int rr = r + q * (kBlock / kNumPartials);
+      const double *p = &rows[(size_t)min(rr, n - 1) * kNumPartials + s];
+      const double x = SAME ? agent_load(p) : *p;
+      v[q] = rr < n ? x : op.identity();
+    }
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) acc = op(acc, v[q]);
+  }
+  acc = op(acc, __shfl_xor(acc, 16, kWave));
+  acc = op(acc, __shfl_xor(acc, 32, kWave));
+  if ((threadIdx.x & (kWave - 1)) < kNumPartials) red[threadIdx.x / kWave * kNumPartials + s] = acc;
   __syncthreads();
   acc = red[s];
-#pragma unroll 1
-  for (int q = 1; q < kBlock / kNumPartials; ++q) acc = combine_slot(s, acc, red[q * kNumPartials + s]);
+#pragma unroll
+  for (int w = 1; w < kBlock / kWave; ++w) acc = op(acc, red[w * kNumPartials + s]);
   return acc;
+}
+
+// Closes the domain's step from its `total` partial rows (called by every thread of one block).
+// red: kEndDoubles doubles of LDS, not in use by any wave.
+constexpr int kEndDoubles = (kBlock / kWave + 1) * kNumPartials + 1;
+template <bool SAME>
+__device__ __forceinline__ void reduce_domain(const StepEnd &fin, const DomDev &dd, int d, const double *rows, int total,
+                                              const uint32_t *dtslots, double *red) {
+  double *md = fin.metrics + (size_t)d * 32;
+  // loads that the sums do not depend on first
+  const float d1 = read_dt1(dtslots + d * kDtWords);
+  const double tot[3] = {md[18], md[19], md[20]};
+  const double x = combine_rows<SAME>(rows, total, red);
+  double *out = red + kBlock / kWave * kNumPartials;
+  if (threadIdx.x < kNumPartials) {
+    md[threadIdx.x] = x;
+    out[threadIdx.x] = x;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) close_domain_step(dd.sp, d1, tot, md, out, fin.d0 + d == 0 ? fin.stepctr : nullptr);
 }
 
 // One of the `total` partial rows of domain d (at rows) is stored, by agent-scope stores of the first
 // wave; the last one to get here closes the domain's step.  Called by every thread of the block.
-// red: kBlock + 1 doubles of LDS, not in use by any wave.
 __device__ __forceinline__ void close_step(const StepEnd &fin, const DomDev &dd, int d, const double *rows, int total,
                                            const uint32_t *dtslots, double *red) {
-  if (!last_to_finish(fin.domdone + fin.d0 + d, (uint32_t)total, reinterpret_cast<uint32_t *>(red + kBlock))) return;
-  const double x = combine_rows(rows, total, red);
-  double *md = fin.metrics + (size_t)d * 32;
-  __syncthreads();
-  if (threadIdx.x < kNumPartials) {
-    md[threadIdx.x] = x;
-    red[threadIdx.x] = x;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0)
-    close_domain_step(dd, dtslots + d * kDtWords, md, red[P_PAIRS], red[P_CAND], red[P_IFC], red[P_IFCP],
-                      fin.d0 + d == 0 ? fin.stepctr : nullptr);
+  if (!last_to_finish(fin.domdone + fin.d0 + d, (uint32_t)total, reinterpret_cast<uint32_t *>(red + kEndDoubles - 1))) return;
+  reduce_domain<true>(fin, dd, d, rows, total, dtslots, red);
 }
 
 // Pass 2: viscous acceleration (Eq. 20 with rho = rho_t, Eq. 22)
@@ -1004,7 +1034,7 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
   }
   // block sums through LDS, after the epilogue's values
   constexpr size_t kEpBytes = (size_t)3 * P * sizeof(float), kRedBytes = (size_t)(P + 1) * 3 * sizeof(double);
-  constexpr size_t kEndBytes = (size_t)(kBlock + 1) * sizeof(double);
+  constexpr size_t kEndBytes = (size_t)kEndDoubles * sizeof(double);
   static_assert((kEpBytes + 15) / 16 * 16 + (kRedBytes > kEndBytes ? kRedBytes : kEndBytes) <=
                     (size_t)row_table_rows<L>() * row_table_stride<L>() * sizeof(uint2),
                 "the epilogue and the reductions fit in the row table");
@@ -1156,10 +1186,15 @@ __global__ __launch_bounds__(kBlock) void dump_pairs(const DomDev *__restrict__ 
 __global__ __launch_bounds__(kBlock) void finalize(const DomDev *__restrict__ doms, const int4 *__restrict__ groups,
                                                    const double *__restrict__ partials, double *__restrict__ rows,
                                                    const uint32_t *__restrict__ dtslots, StepEnd fin) {
-  __shared__ double red[kBlock + 1];
+  __shared__ double red[kEndDoubles];
   const int4 gr = groups[blockIdx.x];
   const DomDev &dd = doms[gr.x];
-  const double x = combine_rows(partials + (size_t)gr.y * kNumPartials, gr.z - gr.y, red);
+  const double *first = partials + (size_t)gr.y * kNumPartials;
+  if (dd.nrow == 1) {
+    reduce_domain<false>(fin, dd, gr.x, first, gr.z - gr.y, dtslots, red);
+    return;
+  }
+  const double x = combine_rows<false>(first, gr.z - gr.y, red);
   if (threadIdx.x < kNumPartials) agent_store(&rows[(size_t)blockIdx.x * kNumPartials + threadIdx.x], x);
   __syncthreads();
   close_step(fin, dd, gr.x, rows + (size_t)dd.row0 * kNumPartials, dd.nrow, dtslots, red);
@@ -2045,9 +2080,9 @@ struct Domain {
   }
 };
 
-// Most pair-kernel blocks of a domain whose step the viscous pass closes; fewest block partials per
-// reduction row otherwise (8 loads in turn per thread).
-constexpr int64_t kFusedChunk = 128;
+// Most pair-kernel blocks of a domain whose step the viscous pass closes (at 256 its end, 9.4 us longer, is no
+// cheaper than finalize), and the fewest block partials per reduction row otherwise.
+constexpr int64_t kFusedBlocks = 128, kRowBlocks = 256;
 
 // Domains of one dimension occupy consecutive internal domain, particle and block ranges.
 struct Group {
@@ -2187,9 +2222,9 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     g.periodic |= dm.p.geometry == MPSPH_PERIODIC;
   }
   // first-level reduction: rows of at most `chunk` block partials, never straddling domains
-  const int64_t chunk = std::max<int64_t>(kFusedChunk, (blocks + kReduceBlocks - 1) / kReduceBlocks);
+  const int64_t chunk = std::max<int64_t>(kRowBlocks, (blocks + kReduceBlocks - 1) / kReduceBlocks);
   L.fused = n > 0;
-  for (const auto &dm : doms) L.fused = L.fused && dm.nblk <= kFusedChunk;
+  for (const auto &dm : doms) L.fused = L.fused && dm.nblk <= kFusedBlocks;
   int rows = 0;
   for (auto &dm : doms) {
     dm.row0 = rows;

@@ -490,19 +490,17 @@ __device__ __forceinline__ void block_reduce_lds(const double (&v)[NP], int k, u
     const bool live = s < NP;
     const bool mn = live && ((minmask >> s) & 1u), mx = live && ((maxmask >> s) & 1u);
     const double *row = lds + (live ? s : 0) * kStride + q * kPer;
+    // sum, maximum and minimum are all formed and one is selected: the slots of a wave would take
+    // three branches one after the other
+    const auto join = [&](double a, double b) {
+      const double sum = a + b, hi = fmax(a, b), lo = fmin(a, b);
+      return mx ? hi : (mn ? lo : sum);
+    };
     double x = row[0];
-    if (mn) {
-      for (int t = 1; t < kPer; ++t) x = fmin(x, row[t]);
-    } else if (mx) {
-      for (int t = 1; t < kPer; ++t) x = fmax(x, row[t]);
-    } else {
-      for (int t = 1; t < kPer; ++t) x += row[t];
-    }
+#pragma unroll 8
+    for (int t = 1; t < kPer; ++t) x = join(x, row[t]);
 #pragma unroll
-    for (int off = 1; off < 4; off <<= 1) {
-      const double y = __shfl_xor(x, off, kWave);
-      x = mn ? fmin(x, y) : (mx ? fmax(x, y) : x + y);
-    }
+    for (int off = 1; off < 4; off <<= 1) x = join(x, __shfl_xor(x, off, kWave));
     if (live && q == 0) emit(s, x);
   }
 }
