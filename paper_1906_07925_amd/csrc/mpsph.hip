@@ -327,7 +327,11 @@ __device__ bool stage_tile(TileLds *T, bool active, int sub, const OwnRow &own, 
 // neighbours of the TILE variant (unused otherwise).  With PIPE the scan issues the neighbour
 // loads of a lane's next slot before the arithmetic of the current one (same arithmetic, same
 // order: the results do not depend on it).  The default passes take it; the persistent and staged
-// variants keep the one-round body.
+// variants keep the one-round body.  K2: kappa = 2 (the paper's) in every domain of the launch; the sums
+// are the same bit for bit, without the tests that a shorter cut-off needs.  The pass is bound by
+// the vector instructions and neighbour loads of its pair loop: with this and the wave-uniform loop of
+// the scan, 1018 -> 976 us on the 2^21-particle cube; whole steps 695 -> 675 us (relaxed 2^20-particle
+// cube), 125 -> 116 us (annulus of 2^18 particles), 69 us instead of 74 (seeded ball of 20000).
 #define MPSPH_PASS1_PARAMS                                                                                   \
   const DomDev *__restrict__ doms, int ndom, const int64_t *__restrict__ stepctr,                            \
       const uint32_t *__restrict__ wkey, const float4 *__restrict__ wpos, const float4 *__restrict__ wfix,    \
@@ -336,7 +340,7 @@ __device__ bool stage_tile(TileLds *T, bool active, int sub, const OwnRow &own, 
       const double *__restrict__ metrics, double *__restrict__ partials
 #define MPSPH_PASS1_ARGS \
   doms, ndom, stepctr, wkey, wpos, wfix, wjaux, cstart, acc, rho_out, nn_out, aabs_out, dtslots, metrics, partials
-template <int D, int L, bool PER, bool DBG, bool TILE, bool PIPE>
+template <int D, int L, bool PER, bool DBG, bool TILE, bool PIPE, bool K2>
 __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileLds *tile, MPSPH_PASS1_PARAMS) {
   const int d = domain_of_block(doms, ndom, lb);
   const GridDev g = doms[d].g;
@@ -385,17 +389,16 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
     // P = p0 / rho_t^2 = p0 tau^-2d h^2d and -dW/dr / r = 5 alpha 2^(d+2) (h_i + h_j)^-(d+2) (1 - q/2)^3
     // for the pair's h_ij: the pair sum takes h^2d and (h_i + h_j)^-(d+2), and the factors
     // common to every pair are applied once to the group's total.  Separations are in fixed-point
-    // units: squared distances are compared in them, the distance itself is converted to cells
+    // units, the distance is converted to cells
     const float Phi = powd<D>(hi * hi);
     const float fscale = sp.p0c * powd<D>(sp.inv_tau * sp.inv_tau) * (5.f * sp.alpha) * (D == 3 ? 32.f : 16.f) * g.funit;
     const float ihi = fast_rcp(hi);
-    const float units = (float)(1u << g.fb);
-    const float rci = sp.kappa * hi * units, rci2 = rci * rci;
+    const float rci = sp.kappa * hi;
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
-    const float kh = 0.5f * sp.kappa * units;
+    const float kh = 0.5f * sp.kappa;
     const float unit = g.funit;
     const float opb = 1.f + sigma;
-    float wsum = 0.f, ax = 0.f, ay = 0.f, az = 0.f, A = 0.f, nn2 = INFINITY;
+    float wsum = 0.f, ax = 0.f, ay = 0.f, az = 0.f, A = 0.f, nn = INFINITY;
     uint32_t npair = 0, nifc = 0;
     const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
     const auto pair = [&](const float4 pj, const uint32_t aj) {
@@ -406,12 +409,10 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
         dz = fixed_diff(xi.z, pj.z);
         r2 += dz * dz;
       }
+      const float r = fast_sqrt(r2) * unit;
       const float hs = hi + pj.w;                   // 2 h_ij
-      const float hij = kh * hs;                    // kappa h_ij in units
-      const bool dens = r2 < rci2;
-      const bool inter = r2 < hij * hij;
-      // the counts and the nearest distance in every lane, so that the branch below is taken
-      // only for the kernel sums
+      const bool inter = r < (K2 ? hs : kh * hs);   // kappa h_ij
+      // the counts in every lane, so that the branch below is taken only for the force
       const bool diff = colour_differs(aj, ai);
       const bool feel = inter && type_at_least(aj, ti);
       nifc += (inter && diff) ? 1u : 0u;
@@ -420,16 +421,25 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
       // the compares, where each becomes one add-with-carry of the compare's lane mask instead
       // of a select and an add after the branch
       asm volatile("" : "+v"(npair), "+v"(nifc));
-      if (inter && r2 < nn2) nn2 = r2;
+      const float q = r * ihi;
+      if constexpr (K2) {
+        // the kernel's support ends at the cut-off: its factor clamped to [0, 1] (an output modifier)
+        // is zero beyond, without a test
+        const float u = __builtin_amdgcn_fmed3f(fmaf(-0.5f, q, 1.f), 0.f, 1.f), u2 = u * u;
+        wsum = fmaf(u2 * u2, fmaf(2.f, q, 1.f), wsum);
+      } else {
+        const float u = fmaf(-0.5f, q, 1.f), u2 = u * u;
+        if (r < rci) wsum = fmaf(u2 * u2, fmaf(2.f, q, 1.f), wsum);
+      }
+      // the nearest distance counts for normal particles, which feel every type; the debug export
+      // has it for all
+      if constexpr (DBG) {
+        if (inter) nn = fminf(nn, r);
+      }
       // coincident particles (two particles clamped into one corner) need no test: their separation
       // is zero and the force factor finite
-      if (!(dens || feel)) return;
-      const float r = fast_sqrt(r2) * unit;
-      if (dens) {
-        const float q = r * ihi, u = fmaf(-0.5f, q, 1.f), u2 = u * u;
-        wsum += u2 * u2 * fmaf(2.f, q, 1.f);
-      }
       if (!feel) return;
+      if constexpr (!DBG) nn = fminf(nn, r);
       const float hj2 = pj.w * pj.w;
       // (P_i + P_j) (-dW/dr / r) over the common factor fscale (>= 0)
       const float s = (diff ? opb : 1.f) * powd_add<D>(hj2, Phi) * kernel_slope_factor<D>(r, fast_rcp(hs));
@@ -465,8 +475,8 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
     gx = fscale * group_sum<L>(ax);
     gy = fscale * group_sum<L>(ay);
     if constexpr (D == 3) gz = fscale * group_sum<L>(az);
-    if constexpr (DBG) gA = fscale * units * group_sum<L>(A);
-    gn = group_min<L>(nn2) * (unit * unit);
+    if constexpr (DBG) gA = fscale * (float)(1u << g.fb) * group_sum<L>(A);
+    gn = group_min<L>(nn);
     gp = group_sum_u<L>(npair);
     gi = group_sum_u<L>(nifc);
     gc = ncand;
@@ -506,7 +516,7 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
     const float oi[3] = {pi.x, pi.y, pi.z};
     const int ti = aux_type(wjaux[ip]);
     const float hi = pi.w, ihi = fast_rcp(hi), si = hi * sp.inv_tau, rci = sp.kappa * hi;
-    const float wsum = ep[0 * P + p], nn2 = ep[4 * P + p];
+    const float wsum = ep[0 * P + p], nn = ep[4 * P + p];
     const uint32_t npair = __float_as_uint(ep[5 * P + p]), nifc = __float_as_uint(ep[6 * P + p]);
     const uint32_t ncand = __float_as_uint(ep[7 * P + p]);
     const float ihd = D == 3 ? ihi * ihi * ihi : ihi * ihi;
@@ -519,7 +529,7 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
     const float ehat = sp.nu_coeff * rci * am / powd<D>(si);  // rho_t nu_coeff r_c |a|
     acc[ip] = make_float4(a[0], a[1], D == 3 ? a[2] : 0.f, ehat);
     if (rho_out) rho_out[ip] = rho;
-    if (nn_out) nn_out[ip] = sqrtf(nn2);
+    if (nn_out) nn_out[ip] = nn;
     if constexpr (DBG) {
       if (aabs_out) aabs_out[ip] = ep[8 * P + p];
     }
@@ -530,8 +540,8 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
       red[P_E2] = e * e;
       red[P_EMAX] = fabs(e);
       red[P_NNORM] = 1.0;
-      if (nn2 < INFINITY) {
-        const double elr = (double)fast_sqrt(nn2) / (double)si;
+      if (nn < INFINITY) {
+        const double elr = (double)nn / (double)si;
         red[P_ELR] = elr;
         red[P_ELR2] = elr * elr;
         red[P_ELRMIN] = elr;
@@ -562,10 +572,10 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
 }
 
 // The pass over the logical blocks b0 + [0, gridDim.x) (one dimension group).
-template <int D, int L, bool PER, bool DBG>
+template <int D, int L, bool PER, bool DBG, bool K2>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_density_force(int b0, MPSPH_PASS1_PARAMS) {
   __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  density_force_block<D, L, PER, DBG, false, true>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, nullptr, MPSPH_PASS1_ARGS);
+  density_force_block<D, L, PER, DBG, false, true, K2>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, nullptr, MPSPH_PASS1_ARGS);
 }
 
 // The staged copy limits a CU to 4 blocks (4 waves per SIMD), which the register budget follows.
@@ -574,7 +584,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     int b0, MPSPH_PASS1_PARAMS) {
   __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   __shared__ TileLds tile;
-  density_force_block<3, L, false, DBG, true, false>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, &tile, MPSPH_PASS1_ARGS);
+  density_force_block<3, L, false, DBG, true, false, false>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, &tile, MPSPH_PASS1_ARGS);
 }
 
 
@@ -769,7 +779,7 @@ __device__ __forceinline__ void close_step(const StepEnd &fin, const DomDev &dd,
   doms, ndom, wkey, wpos, wfix, wjaux, wid, cstart, acc, dtslots, skey, soff, sct, sid, cell, counts, at_out, v_out, partials, \
       fin
 // One logical block lb of the pass; PIPE as for density_force_block, END: the pass closes the step.
-template <int D, int L, bool PER, bool PIPE, bool END = false>
+template <int D, int L, bool PER, bool PIPE, bool END = false, bool K2 = false>
 __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, MPSPH_PASS2_PARAMS) {
   const int d = domain_of_block(doms, ndom, lb);
   const GridDev g = doms[d].g;
@@ -804,7 +814,7 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
       const float4 acci = acc[i];
       const float ei = (0.5f * dt1) * acci.w;
       const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
-      const float kh = 0.5f * sp.kappa * (float)(1u << g.fb);   // distances are compared in fixed-point units
+      const float kh = 0.5f * sp.kappa;
       const float unit = g.funit;
       // with eta_i = 0 every harmonic-mean viscosity of particle i vanishes: nothing to sum
       if (ei > 0.f) {
@@ -826,11 +836,10 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
             const float dz = fixed_diff(xi.z, pj.z);
             r2 += dz * dz;
           }
-          const float hs = hi + pj.w;   // 2 h_ij
-          const float hij = kh * hs;
-          // the particle itself and coincident particles have r^2 = 0 exactly
-          if (!(r2 > 0.f && r2 < hij * hij && type_at_least(nb.a, ti))) return;
           const float r = fast_sqrt(r2) * unit;
+          const float hs = hi + pj.w;   // 2 h_ij
+          // the particle itself and coincident particles have r = 0 exactly
+          if (!(r > 0.f && r < (K2 ? hs : kh * hs) && type_at_least(nb.a, ti))) return;
           // e_j          const float r = fast_sqrt(r2);
           // e_j / (e_i + e_j): half the harmonic mean e_i e_j / (e_i + e_j) over e_i, which
           // multiplies the sum once; e_i > 0 here and e_j >= 0, so the sum is positive
@@ -1051,10 +1060,10 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
   }
 }
 
-template <int D, int L, bool PER, bool END>
+template <int D, int L, bool PER, bool END, bool K2>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_integrate(int b0, MPSPH_PASS2_PARAMS) {
   __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  viscous_integrate_block<D, L, PER, true, END>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, MPSPH_PASS2_ARGS);
+  viscous_integrate_block<D, L, PER, true, END, K2>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, MPSPH_PASS2_ARGS);
 }
 
 
@@ -1102,10 +1111,10 @@ __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_density_forc
     const int it = __builtin_amdgcn_readfirstlane(sitem);   // the same in every lane
     if (it >= nb) break;
     if constexpr (DM == 5) {
-      if (it < nb2) density_force_block<2, L, PER, DBG, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
-      else density_force_block<3, L3, PER, DBG, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
+      if (it < nb2) density_force_block<2, L, PER, DBG, false, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
+      else density_force_block<3, L3, PER, DBG, false, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
     } else {
-      density_force_block<DM, DM == 3 ? L3 : L, PER, DBG, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
+      density_force_block<DM, DM == 3 ? L3 : L, PER, DBG, false, false, false>(b0 + it, rowtab, nullptr, MPSPH_PASS1_ARGS);
     }
   }
   if (threadIdx.x == 0) queue_done(queue);
@@ -1158,7 +1167,7 @@ __global__ __launch_bounds__(kBlock) void dump_pairs(const DomDev *__restrict__ 
   const FixedPos xi = fixed_of(pi);
   const float hi = pi.w;
   const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
-  const float kh = 0.5f * sp.kappa * (float)(1u << g.fb);
+  const float kh = 0.5f * sp.kappa;
   const uint32_t idi = wid[i];
   __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   scan_group_table<D, L, row_table_rows<L>(), PER>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(),
@@ -1170,8 +1179,7 @@ __global__ __launch_bounds__(kBlock) void dump_pairs(const DomDev *__restrict__ 
       const float dz = fixed_diff(xi.z, pj.z);
       r2 += dz * dz;
     }
-    const float hij = kh * (hi + pj.w);
-    if (!(r2 < hij * hij)) return;
+    if (!(fast_sqrt(r2) * g.funit < kh * (hi + pj.w))) return;
     const unsigned long long k = atomicAdd(count, 1ull);
     if (k < cap) {
       out_i[k] = idi;
@@ -2088,6 +2096,7 @@ constexpr int64_t kFusedBlocks = 128, kRowBlocks = 256;
 struct Group {
   int D = 0;
   bool periodic = false;  // some domain of the group is a periodic box
+  bool kappa2 = true;     // every domain's cut-off is the kernel's support, kappa = 2
   int d0 = 0, nd = 0;   // internal domains
   int i0 = 0, i1 = 0;   // internal particles
   int b0 = 0, nb = 0;   // pair-kernel blocks
@@ -2220,6 +2229,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     g.i1 = (int)n;
     g.nb += dm.nblk;
     g.periodic |= dm.p.geometry == MPSPH_PERIODIC;
+    g.kappa2 &= dm.p.kappa == 2.0;
   }
   // first-level reduction: rows of at most `chunk` block partials, never straddling domains
   const int64_t chunk = std::max<int64_t>(kRowBlocks, (blocks + kReduceBlocks - 1) / kReduceBlocks);
@@ -2538,7 +2548,8 @@ template <int D, int L_, bool PER>
 void launch_pass1_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st) {
   const Layout &L = ctx->L;
   const bool dbg = ctx->dom[0].p.debug != 0;
-  auto kern = dbg ? pass_density_force<D, L_, PER, true> : pass_density_force<D, L_, PER, false>;
+  auto kern = dbg ? pass_density_force<D, L_, PER, true, false>
+                  : (gr.kappa2 ? pass_density_force<D, L_, PER, false, true> : pass_density_force<D, L_, PER, false, false>);
   if constexpr (D == 3 && !PER)
     if (ctx->variant == MPSPH_PAIRS_TILE) kern = dbg ? pass_density_force_tile<L_, true> : pass_density_force_tile<L_, false>;
   kern<<<gr.nb, kBlock, 0, st>>>(
@@ -2568,7 +2579,8 @@ void launch_pass1(mpsph_ctx *ctx, const Group &gr, hipStream_t st, EventHook *hk
 template <int D, int L_, bool PER>
 void launch_pass2_l(mpsph_ctx *ctx, const Group &gr, hipStream_t st, float4 *at_o, float4 *v_o) {
   const Layout &L = ctx->L;
-  auto kern = fused_end(ctx) ? pass_viscous_integrate<D, L_, PER, true> : pass_viscous_integrate<D, L_, PER, false>;
+  auto kern = fused_end(ctx) ? (gr.kappa2 ? pass_viscous_integrate<D, L_, PER, true, true> : pass_viscous_integrate<D, L_, PER, true, false>)
+                             : (gr.kappa2 ? pass_viscous_integrate<D, L_, PER, false, true> : pass_viscous_integrate<D, L_, PER, false, false>);
   kern<<<gr.nb, kBlock, 0, st>>>(
       gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_pos),
       ctx->at<float4>(L.w_fix), ctx->at<uint32_t>(L.w_jaux), ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),

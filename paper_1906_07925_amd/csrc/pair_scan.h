@@ -136,7 +136,7 @@ constexpr int row_table_stride() {
 // A body may also come in two parts, fetch(j) -> payload (the slot's neighbour loads) and
 // use(payload) (its arithmetic): the scan then issues the loads of a lane's next slot round before
 // the arithmetic of the current one, so that their latency overlaps it.  A fetch past the chunk's end
-// gets an index below 2L that may lie outside the arrays: bounds-checked loads, and no use() follows.
+// gets an index that may lie outside the arrays: bounds-checked loads, and no use() follows.
 struct IdentityRemap {
   __device__ __forceinline__ uint32_t operator()(int, int, uint32_t a) const { return a; }
 };
@@ -314,33 +314,38 @@ __device__ __forceinline__ uint32_t scan_group_table(uint32_t self, int sub, uin
     total += run;
     // the chunk's slots, L at a time; slot t of row e is candidate base_e + t
     uint32_t t = (uint32_t)sub;
-    if (t < run) {
-      const uint2 *rp = tab;
-      uint2 row = *rp;         // row of the last located slot
-      const auto locate = [&](uint32_t tt) -> uint32_t {
-        while (tt >= row.y) {
-          rp += stride;
-          row = *rp;
-        }
-        return row.x + tt;
-      };
-      if constexpr (IsSplitBody<typename std::decay<BodyF>::type>::value) {
-        // one round ahead: the loads of slot t + L are issued before the arithmetic of slot t;
-        // two payloads used in turn (the loop is unrolled twice), so that none is copied
+    const uint2 *rp = tab;
+    uint2 row = *rp;           // row of the last located slot
+    const auto locate = [&](uint32_t tt) -> uint32_t {
+      while (tt >= row.y) {
+        rp += stride;
+        row = *rp;
+      }
+      return row.x + tt;
+    };
+    if constexpr (IsSplitBody<typename std::decay<BodyF>::type>::value) {
+      // one round ahead: the loads of slot t + L are issued before the arithmetic of slot t; two
+      // payloads used in turn (the loop is unrolled twice), so that none is copied.  The wave runs the
+      // rounds of its longest group: as a loop that each lane left by itself, the exit's merge of the
+      // two payloads made every other round wait for all loads before it issued the next ones
+      bool v = t < run;
+      if (__builtin_amdgcn_ballot_w64(v)) {
         auto pa = body.fetch(locate(t));
         while (true) {
           t += L;
           auto pb = body.fetch(locate(t));
-          body.use(pa);
-          if (t >= run) break;
+          if (v) body.use(pa);
+          v = t < run;
+          if (!__builtin_amdgcn_ballot_w64(v)) break;
           t += L;
           pa = body.fetch(locate(t));
-          body.use(pb);
-          if (t >= run) break;
+          if (v) body.use(pb);
+          v = t < run;
+          if (!__builtin_amdgcn_ballot_w64(v)) break;
         }
-      } else {
-        for (; t < run; t += L) body(locate(t));
       }
+    } else {
+      for (; t < run; t += L) body(locate(t));
     }
   }
   return CUT ? total : (total > 0u ? total - 1u : 0u);
