@@ -373,12 +373,12 @@ MPSPH_API int mpsph_set_field_coeff(mpsph_ctx *ctx, int32_t domain, const double
  * viscous pass (Eq. 20-22), the velocity and drift (Eq. 26-28) and the wall clamp (Eq. 32).
  * Pair sets, type masks and re-tagging are held fixed (piecewise constant).
  * Memory: the states at every ckpt_every-th step are kept, and a segment of ckpt_every steps is
- * recomputed with its per-step record (about 80 bytes per particle and step plus the cell table);
+ * recomputed with its per-step record (about 110 bytes per particle and step plus the cell table);
  * the library allocates this device memory on first use and keeps it until mpsph_destroy.
  * Outputs (each may be NULL): *loss_out (host), grad_coeff_out[n_rbf] = dL/dc_k (host, only for
  * MPSPH_RBF_EXP fields), d_grad_pos = dL/dx of the positions at the call (device, n x dim
- * float32, load order, domain units).  Debug exports after the call refer to a recomputed
- * step, not to the last one.  Single-domain contexts with a box region and a uniform or RBF
+ * float32, load order, domain units).  Debug exports after the call refer to the last
+ * step of the first ckpt_every steps, not to the run's last one.  Single-domain contexts with a box region and a uniform or RBF
  * field.  Synchronises.  Errors: MPSPH_E_INVALID (nsteps < 0, ckpt_every < 1), MPSPH_E_STATE,
  * MPSPH_E_UNSUPPORTED (batched context, other region or field, seeded features), MPSPH_E_NOMEM. */
 MPSPH_API int mpsph_grad(mpsph_ctx *ctx, int32_t nsteps, int32_t ckpt_every, double lambda, double *loss_out,

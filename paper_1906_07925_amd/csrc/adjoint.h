@@ -77,32 +77,58 @@ __device__ __forceinline__ void inv_pows(float ih, float &p2, float &p3) {
   }
 }
 
-// Field spacing s(X) with its gradient (cell units) for the uniform and RBF fields.
+// The RBF table of a field, entry m in lane m of the wave (kMaxRbf of them at most).  Read from there
+// by readlane into scalar registers: 7 loads per wave instead of 7 for every Gaussian.
+struct RbfTable {
+  int c[3];
+  float o[3], k;
+};
+static_assert(kMaxRbf <= kWave, "one table entry per lane");
 template <int D>
-__device__ __forceinline__ float field_grad(const FieldDev &f, const int *c, const float *o, float *grad) {
-#pragma unroll
-  for (int a = 0; a < 3; ++a) grad[a] = 0.f;
-  if (f.kind != 3) return f.s0;
-  float e = 0.f, gx[3] = {0.f, 0.f, 0.f};
-  for (int m = 0; m < f.n_rbf; ++m) {
-    float dv[3], r2 = 0.f;
+__device__ __forceinline__ RbfTable rbf_table(const FieldDev &f, int nr) {
+  RbfTable r{};
+  const int m = threadIdx.x & (kWave - 1);
+  if (m < nr) {
 #pragma unroll
     for (int a = 0; a < D; ++a) {
-      dv[a] = (float)(c[a] - f.rbf_c[m * 3 + a]) + (o[a] - f.rbf_o[m * 3 + a]);
-      r2 += dv[a] * dv[a];
+      r.c[a] = f.rbf_c[m * 3 + a];
+      r.o[a] = f.rbf_o[m * 3 + a];
     }
-    const float t = f.rbf_k[m] * __expf(-r2 * f.e2);
-    e += t;
-#pragma unroll
-    for (int a = 0; a < D; ++a) gx[a] -= 2.f * f.e2 * t * dv[a];
+    r.k = f.rbf_k[m];
   }
-  const float s = f.s0 * __expf(e);
-#pragma unroll
-  for (int a = 0; a < D; ++a) grad[a] = s * gx[a];
-  return s;
+  return r;
 }
 
-// Minimum of non-negative floats over the block into *dst: one atomic per block.
+// Gaussians [m0, m0 + kRbfChunk) of the RBF field at X, zero past the last one, with their share of
+// the exponent e and of its gradient ge.  By whole waves.
+constexpr int kRbfChunk = 32;
+template <int D>
+__device__ __forceinline__ void rbf_chunk(const RbfTable &r, float e2, int m0, int nr, const int *c, const float *o,
+                                          float *gauss, float &e, float *ge) {
+#pragma unroll
+  for (int t = 0; t < kRbfChunk; ++t) {
+    const int m = m0 + t;
+    gauss[t] = 0.f;
+    if (m < nr) {   // uniform
+      float dv[3], r2 = 0.f;
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        dv[a] = (float)(c[a] - __builtin_amdgcn_readlane(r.c[a], m)) +
+                (o[a] - __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r.o[a]), m)));
+        r2 += dv[a] * dv[a];
+      }
+      gauss[t] = __expf(-r2 * e2);
+      const float k = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r.k), m)) * gauss[t];
+      e += k;
+#pragma unroll
+      for (int a = 0; a < D; ++a) ge[a] -= 2.f * e2 * k * dv[a];
+    }
+  }
+}
+
+// Minimum of non-negative floats over the block into *dst: one atomic per block.  The callers
+// spread their blocks over the kDtSlots lines of a slot array: device-wide atomics on one line
+// take 12 ns each (262,144 particles: the drift adjoint 17.6 us on one address, 8.3 on 16 lines).
 __device__ __forceinline__ void block_min_atomic(float v, uint32_t *dst) {
   __shared__ float wmin[kBlock / kWave];
   for (int off = kWave / 2; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off, kWave));
@@ -115,10 +141,12 @@ __device__ __forceinline__ void block_min_atomic(float v, uint32_t *dst) {
   }
 }
 
-// Resets the per-step scalars: minimum time-step bits, index attaining it.
-__global__ void adj_init(uint32_t *minbits, uint32_t *argmin) {
-  *minbits = kInfBits;
-  *argmin = 0xffffffffu;
+// Minimum over the slots, as bits; every lane of the wave takes part and gets it.
+__device__ __forceinline__ uint32_t slots_min(const uint32_t *slots) {
+  uint32_t m = slots[(threadIdx.x & (kDtSlots - 1)) * kDtStride];
+#pragma unroll
+  for (int o = kDtSlots / 2; o > 0; o >>= 1) m = min(m, (uint32_t)__shfl_xor((int)m, o, kWave));
+  return __builtin_amdgcn_readfirstlane(m);
 }
 
 // Drift and velocity adjoint, one thread per particle (sorted order of the step).
@@ -129,7 +157,7 @@ template <int D>
 __global__ __launch_bounds__(kBlock) void adj_drift(const DomDev *__restrict__ dom, TapeView tp,
                                                     const float4 *__restrict__ xbar_next, float4 *__restrict__ xacc,
                                                     float4 *__restrict__ abv, float4 *__restrict__ vtb,
-                                                    float *__restrict__ dtc, uint32_t *__restrict__ minbits,
+                                                    float *__restrict__ dtc, uint32_t *__restrict__ minslots,
                                                     double *__restrict__ partials) {
   const int i = blockIdx.x * kBlock + threadIdx.x;
   const GridDev &g = dom->g;
@@ -173,7 +201,7 @@ __global__ __launch_bounds__(kBlock) void adj_drift(const DomDev *__restrict__ d
     }
     project_feature<D>(g, ti, ci, oi, ab);
     xacc[i] = make_float4(xd[0], xd[1], xd[2], 0.f);
-    abv[i] = make_float4(ab[0], ab[1], ab[2], 0.f);
+    abv[i] = make_float4(ab[0], ab[1], ab[2], __int_as_float(ti));   // the type for the viscous pass
     vtb[i] = make_float4(dt2 * db[0], dt2 * db[1], dt2 * db[2], 0.f);
     part[0] = t2;
     // candidate of the first time step (as in the forward pass, from the stored a)
@@ -182,20 +210,22 @@ __global__ __launch_bounds__(kBlock) void adj_drift(const DomDev *__restrict__ d
     if (ti != 3 && am2 > 0.f) c1 = sp.c_acc * fast_sqrt(sp.kappa * pi.w * fast_rsq(am2));   // as the density pass
     dtc[i] = c1;
   }
-  block_min_atomic(c1, minbits);
-  block_reduce_write<1>(part, ops, partials + (size_t)blockIdx.x * kNumPartials);
+  block_min_atomic(c1, minslots + (blockIdx.x & (kDtSlots - 1)) * kDtStride);
+  block_reduce_write<1>(part, ops, partials + blockIdx.x);
 }
 
 // Viscous adjoint, L lanes per particle.  Gathers over the neighbours j of k the terms of the
 // pairs (k, j) and (j, k) of A~ = sum M K (v~_k - v~_j):
 //   v~bar_k += K (M_kj Abar_k - M_jk Abar_j),  Kbar = (M_kj Abar_k - M_jk Abar_j).(v~_k - v~_j)
 // and Kbar's share of eta_k, s_k, X_k; then eta -> v~, s; a-bar = T1/2 v~bar; T1-bar partials.
+// fbar receives Pi a-bar, the adjoint of the force before the mapping but for the share of the
+// time step in the particle attaining T1 (adj_time_step).
 template <int D, int L>
 __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const DomDev *__restrict__ dom, TapeView tp,
                                                    const float4 *__restrict__ abv, const float4 *__restrict__ vtb,
                                                    float4 *__restrict__ xacc, float *__restrict__ sbar,
-                                                   float4 *__restrict__ abar, const float *__restrict__ dtc,
-                                                   const uint32_t *__restrict__ minbits, uint32_t *__restrict__ argmin,
+                                                   float4 *__restrict__ fbar, const float *__restrict__ dtc,
+                                                   const uint32_t *__restrict__ minslots, uint32_t *__restrict__ argmin,
                                                    double *__restrict__ partials) {
   const int lb = xcd_block(blockIdx.x, gridDim.x);
   const GridDev &g = dom->g;
@@ -207,6 +237,7 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
   // pair terms instead of being held in registers across the pair loop
   __shared__ float4 gdat[kBlock / L][2];
   const float dt1 = read_dt1(tp.dts);
+  const uint32_t tmin = slots_min(minslots);
   const float hdt = 0.5f * dt1;
   double part[1] = {0.0};
   const int ops[1] = {0};
@@ -237,20 +268,18 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
     const float kh = 0.5f * sp.kappa, a5 = 5.f * sp.alpha, a75 = 7.5f * sp.alpha;
     if (ei > 0.f) {
-      const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n), raux = buf_res(tp.wjaux, 4, (uint32_t)g.n);
+      const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n);
       const BufRes racc = buf_res(tp.acc, 16, (uint32_t)g.n), rabv = buf_res(abv, 16, (uint32_t)g.n);
       struct Nb {
-        float4 p, a4, ab;
-        uint32_t a;
+        float4 p, a4, ab;   // ab.w: the neighbour's type
       };
       // the neighbour's loads (bounds-checked: slots past the arrays read zeros) are issued one
       // slot round ahead of the pair's arithmetic
       const auto fetch = [&](uint32_t jr) {
-        return Nb{buf_f4(rpos, jr), buf_f4(racc, jr), buf_f4(rabv, jr), buf_u32(raux, jr)};
+        return Nb{buf_f4(rpos, jr), buf_f4(racc, jr), buf_f4(rabv, jr)};
       };
       const auto use = [&](const Nb &nb) {
         const float4 pj = nb.p, aj4 = nb.a4, abj = nb.ab;
-        const uint32_t aj = nb.a;
         const float dx = fixed_diff(xi.x, pj.x) * unit;
         const float dy = fixed_diff(xi.y, pj.y) * unit;
         float dz = 0.f;
@@ -261,7 +290,7 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
         }
         const float hij = kh * (hi + pj.w);
         if (!(r2 > 0.f && r2 < hij * hij)) return;
-        const int tj = aux_type(aj);
+        const int tj = __float_as_int(abj.w);
         const float ej = hdt * aj4.w;
         if (!(ej > 0.f)) return;  // eta_j = 0: the pair's K and every derivative of it vanish
         const float mkj = tj >= ti ? 1.f : 0.f, mjk = ti >= tj ? 1.f : 0.f;
@@ -310,8 +339,10 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
       // the particle's own data again, through an index the compiler cannot tie to i, so that
       // neither values nor addresses stay live across the pair loop
       const int io = __shfl(i, (int)(threadIdx.x & (kWave - 1)));
-      const float si = tp.wpos[io].w * sp.inv_tau;
-      const int ti = aux_type(tp.wjaux[io]);
+      const float4 po = tp.wpos[io];
+      const float si = po.w * sp.inv_tau;
+      const uint32_t xo = tp.wjaux[io];
+      const int ti = aux_type(xo);
       const float4 ai = tp.acc[io];
       const float vti[3] = {hdt * ai.x, hdt * ai.y, hdt * ai.z};
       const float4 vd = vtb[io];
@@ -336,64 +367,62 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
           t1 += 0.5 * (double)av[a] * (double)vt[a];
         }
       }
-      abar[io] = make_float4(ab[0], ab[1], ab[2], 0.f);
+      int co[3];
+      unpack_key<D>(tp.wkey[io], g, co);
+      const float oo[3] = {po.x, po.y, po.z};
+      project_feature<D>(g, ti, co, oo, ab);
+      fbar[io] = make_float4(ab[0], ab[1], ab[2], __uint_as_float(xo));   // the flags for the force adjoint
       sbar[io] = sb;
       const float4 x0 = xacc[io];
       xacc[io] = make_float4(x0.x + xb[0], x0.y + xb[1], x0.z + xb[2], 0.f);
-      if (__float_as_uint(dtc[io]) == *minbits) atomicMin(argmin, (uint32_t)io);
+      if (__float_as_uint(dtc[io]) == tmin) atomicMin(argmin, (uint32_t)io);
       part[0] = t1;
     }
   }
-  block_reduce_write<1, L>(part, ops, partials + (size_t)lb * kNumPartials);   // first lanes of the groups
+  block_reduce_write<1, L>(part, ops, partials + lb);   // first lanes of the groups
 }
 
-// Sum of the time-step adjoints: out[0] = T1-bar + f T2-bar (fixed order, one block).
-__global__ __launch_bounds__(256) void adj_sum_dt(const double *__restrict__ pa, int na, const double *__restrict__ pb,
-                                                   int nb, float f, double *__restrict__ out) {
-  __shared__ double red[256];
-  double x = 0.0, y = 0.0;
-  for (int b = threadIdx.x; b < na; b += 256) x += pa[(size_t)b * kNumPartials];
-  for (int b = threadIdx.x; b < nb; b += 256) y += pb[(size_t)b * kNumPartials];
-  red[threadIdx.x] = y + (double)f * x;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = red[0];
-}
-
-// Adjoint of the force after the mapping: F-bar = Pi (a-bar + [k attains T1] dT1/da T1-bar);
-// the particle attaining T1 also receives dT1/ds T1-bar.
+// Time-step adjoint, one block: T1-bar + f T2-bar from the partials (fixed order), and its share in
+// the particle that attains T1: F-bar += Pi dT1/da T1-bar, s-bar += dT1/ds T1-bar.  Bound by the latency
+// of its loads; the partials lie one after the other (8,192 of them 5 us; 14 us at kNumPartials doubles
+// apart in a block of 256).
+constexpr int kTimeStepThreads = 1024;
 template <int D>
-__global__ __launch_bounds__(kBlock) void adj_fbar(const DomDev *__restrict__ dom, TapeView tp,
-                                                   const float4 *__restrict__ abar, const double *__restrict__ t1bar,
-                                                   const uint32_t *__restrict__ argmin, float *__restrict__ sbar,
-                                                   float4 *__restrict__ fbar) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  const float dt1 = read_dt1(tp.dts);
-  if (i >= dom->n) return;
+__global__ __launch_bounds__(kTimeStepThreads) void adj_time_step(const DomDev *__restrict__ dom, TapeView tp,
+                                                                  const double *__restrict__ pa, int na,
+                                                                  const double *__restrict__ pb, int nb, float f,
+                                                                  const uint32_t *__restrict__ argmin,
+                                                                  float *__restrict__ sbar, float4 *__restrict__ fbar) {
+  __shared__ double red[kTimeStepThreads / kWave];
+  const float dt1 = read_dt1(tp.dts);   // by whole waves
+  double x = 0.0, y = 0.0;
+#pragma unroll 4
+  for (int b = threadIdx.x; b < na; b += kTimeStepThreads) x += pa[b];
+#pragma unroll 8
+  for (int b = threadIdx.x; b < nb; b += kTimeStepThreads) y += pb[b];
+  y += (double)f * x;
+#pragma unroll
+  for (int o = kWave / 2; o > 0; o >>= 1) y += __shfl_xor(y, o, kWave);
+  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = y;
+  __syncthreads();
+  const uint32_t i = *argmin;
+  if (threadIdx.x != 0 || i >= (uint32_t)dom->n) return;   // no particle with a force: no time step to adjoin
+  double t1bar = red[0];
+#pragma unroll
+  for (int w = 1; w < kTimeStepThreads / kWave; ++w) t1bar += red[w];
   const GridDev &g = dom->g;
   int ci[3];
   unpack_key<D>(tp.wkey[i], g, ci);
-  const float4 pi = tp.wpos[i];
+  const float4 pi = tp.wpos[i], a4 = tp.acc[i], f0 = fbar[i];
   const float oi[3] = {pi.x, pi.y, pi.z};
-  const int ti = aux_type(tp.wjaux[i]);
-  const float4 ab4 = abar[i];
-  float f[3] = {ab4.x, ab4.y, ab4.z};
-  if ((uint32_t)i == *argmin) {
-    // T1 = c_acc sqrt(kappa h / |a|): dT1/da = -T1 a / (2 |a|^2), dT1/ds = T1 / (2 s)
-    const float tb = (float)*t1bar;
-    const float4 a4 = tp.acc[i];
-    const float am2 = a4.x * a4.x + a4.y * a4.y + (D == 3 ? a4.z * a4.z : 0.f);
-    const float c = -0.5f * dt1 * tb / am2;
-    f[0] = fmaf(c, a4.x, f[0]);
-    f[1] = fmaf(c, a4.y, f[1]);
-    if constexpr (D == 3) f[2] = fmaf(c, a4.z, f[2]);
-    sbar[i] += 0.5f * dt1 * tb / (pi.w * dom->sp.inv_tau);
-  }
-  project_feature<D>(g, ti, ci, oi, f);
-  fbar[i] = make_float4(f[0], f[1], f[2], 0.f);
+  const float tb = (float)t1bar;
+  // T1 = c_acc sqrt(kappa h / |a|): dT1/da = -T1 a / (2 |a|^2), dT1/ds = T1 / (2 s)
+  const float am2 = a4.x * a4.x + a4.y * a4.y + (D == 3 ? a4.z * a4.z : 0.f);
+  const float c = -0.5f * dt1 * tb / am2;
+  float ff[3] = {c * a4.x, c * a4.y, D == 3 ? c * a4.z : 0.f};
+  project_feature<D>(g, aux_type(tp.wjaux[i]), ci, oi, ff);
+  fbar[i] = make_float4(f0.x + ff[0], f0.y + ff[1], f0.z + ff[2], f0.w);
+  sbar[i] += 0.5f * dt1 * tb / (pi.w * dom->sp.inv_tau);
 }
 
 // Force adjoint, L lanes per particle: for every neighbour j, with W = M_kj Fbar_k - M_jk Fbar_j
@@ -427,18 +456,17 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   const float kh = 0.5f * sp.kappa, a5 = 5.f * sp.alpha, a75 = 7.5f * sp.alpha;
   const float opb = 1.f + sigma_of(sp, tstep);   // surface tension of the step (Eq. 24-25)
   float xb[3] = {0.f, 0.f, 0.f}, sb = 0.f;
-  const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n), raux = buf_res(tp.wjaux, 4, (uint32_t)g.n);
+  const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n);
   const BufRes rfb = buf_res(fbar, 16, (uint32_t)g.n);
   struct Nb {
-    float4 p, f;
-    uint32_t a;
+    float4 p, f;   // f.w: the neighbour's type and colour
   };
   // the neighbour's loads (bounds-checked: slots past the arrays read zeros) are issued one slot
   // round ahead of the pair's arithmetic
-  const auto fetch = [&](uint32_t jr) { return Nb{buf_f4(rpos, jr), buf_f4(rfb, jr), buf_u32(raux, jr)}; };
+  const auto fetch = [&](uint32_t jr) { return Nb{buf_f4(rpos, jr), buf_f4(rfb, jr)}; };
   const auto use = [&](const Nb &nb) {
     const float4 pj = nb.p, fj = nb.f;
-    const uint32_t aj = nb.a;
+    const uint32_t aj = __float_as_uint(fj.w);
     const float dx = fixed_diff(xi.x, pj.x) * unit;
     const float dy = fixed_diff(xi.y, pj.y) * unit;
     float dz = 0.f;
@@ -486,18 +514,30 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
 
 // Field adjoint and hand-over to the previous step, one thread per particle:
 //   X-bar_k += s-bar_k grad s(X_k),  c-bar_m += s-bar_k ds/dc_m = s-bar_k s_k G_m(X_k),
-// X-bar written at the particle's index in the previous state order (perm), per-block partial
-// sums of c-bar to cpart[block * kMaxRbf + m].
+// X-bar written at the particle's index in the previous state order (perm).  Each wave keeps its
+// sums of c-bar in row cpart[row * kMaxRbf + m], added to over the steps of the sweep (set by the
+// loss, the first of them).  Also clears the time-step slots for the step that is reversed next.
+// One wave per block: 8,192 particles are 128 CUs' work instead of 32 blocks'.  Bound by the
+// latency of the Gaussians and of the reduction, which halves the sums a lane holds at each exchange
+// (32 exchanges for 32 sums instead of 192): with the table in lanes 21 -> 8.7 us at
+// 8,192 particles, 38 -> 23 us at 262,144.
 template <int D>
-__global__ __launch_bounds__(kBlock) void adj_field(const DomDev *__restrict__ dom, TapeView tp,
-                                                    const float4 *__restrict__ xacc, const float *__restrict__ sbar,
-                                                    float4 *__restrict__ xbar_prev, double *__restrict__ cpart) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
+__global__ __launch_bounds__(kWave) void adj_field(const DomDev *__restrict__ dom, TapeView tp,
+                                                   const float4 *__restrict__ xacc, const float *__restrict__ sbar,
+                                                   float4 *__restrict__ xbar_prev, double *__restrict__ cpart, int first,
+                                                   uint32_t *__restrict__ minslots, uint32_t *__restrict__ argmin) {
+  const int lane = threadIdx.x, i = blockIdx.x * kWave + lane;
   const GridDev &g = dom->g;
   const FieldDev &f = dom->f;
+  if (blockIdx.x == 0) {
+    if (lane < kDtSlots) minslots[lane * kDtStride] = kInfBits;
+    if (lane == kDtSlots) *argmin = 0xffffffffu;
+  }
   const bool act = i < dom->n;
   int ci[3] = {0, 0, 0};
-  float oi[3] = {0.f, 0.f, 0.f}, sb = 0.f, gs[3] = {0.f, 0.f, 0.f}, sv = 0.f;
+  float oi[3] = {0.f, 0.f, 0.f}, sb = 0.f;
+  float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint32_t to = 0u;
   if (act) {
     unpack_key<D>(tp.wkey[i], g, ci);
     const float4 pi = tp.wpos[i];
@@ -505,51 +545,66 @@ __global__ __launch_bounds__(kBlock) void adj_field(const DomDev *__restrict__ d
     oi[1] = pi.y;
     oi[2] = pi.z;
     sb = sbar[i];
-    sv = field_grad<D>(f, ci, oi, gs);
-    const float4 x = xacc[i];
-    xbar_prev[tp.perm[i]] = make_float4(fmaf(sb, gs[0], x.x), fmaf(sb, gs[1], x.y), fmaf(sb, gs[2], x.z), 0.f);
+    x = xacc[i];
+    to = tp.perm[i];
   }
-  if (f.kind != 3) return;  // block-uniform: no coefficient gradient for other fields
-  const int ops[16] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (int m0 = 0; m0 < f.n_rbf; m0 += 16) {
-    double v[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-      const int m = m0 + t;
-      float c = 0.f;
-      if (act && m < f.n_rbf) {
-        float r2 = 0.f;
-#pragma unroll
-        for (int a = 0; a < D; ++a) {
-          const float dv = (float)(ci[a] - f.rbf_c[m * 3 + a]) + (oi[a] - f.rbf_o[m * 3 + a]);
-          r2 += dv * dv;
-        }
-        c = sb * sv * __expf(-r2 * f.e2);
-      }
-      v[t] = (double)c;
+  const int nr = f.kind == 3 ? f.n_rbf : 0;   // other fields: no gradient, no coefficients
+  float gauss[kRbfChunk], e = 0.f, ge[3] = {0.f, 0.f, 0.f};
+  const RbfTable tab = rbf_table<D>(f, nr);
+  for (int m0 = 0; m0 < nr; m0 += kRbfChunk) rbf_chunk<D>(tab, f.e2, m0, nr, ci, oi, gauss, e, ge);
+  const float w = sb * (f.s0 * __expf(e));
+  if (act) xbar_prev[to] = make_float4(fmaf(w, ge[0], x.x), fmaf(w, ge[1], x.y), fmaf(w, ge[2], x.z), 0.f);
+  for (int m0 = 0; m0 < nr; m0 += kRbfChunk) {
+    if (nr > kRbfChunk) {   // the first loop left the last chunk's
+      float e1 = 0.f, g1[3] = {0.f, 0.f, 0.f};
+      rbf_chunk<D>(tab, f.e2, m0, nr, ci, oi, gauss, e1, g1);
     }
-    block_reduce_write<16>(v, ops, cpart + (size_t)blockIdx.x * kMaxRbf + m0);
-    __syncthreads();
+    // the first exchange passes the FP32 terms, sums are FP64
+    double v[kRbfChunk / 2];
+    const bool upper = (lane & (kWave / 2)) != 0;
+#pragma unroll
+    for (int t = 0; t < kRbfChunk / 2; ++t) {
+      const float lo = w * gauss[t], hi = w * gauss[t + kRbfChunk / 2];
+      v[t] = (double)(upper ? hi : lo) + (double)__shfl_xor(upper ? lo : hi, kWave / 2, kWave);
+    }
+    int m = m0 + (upper ? kRbfChunk / 2 : 0);
+#pragma unroll
+    for (int h = kRbfChunk / 4, o = kWave / 4; h > 0; h >>= 1, o >>= 1) {
+      const bool up = (lane & o) != 0;
+#pragma unroll
+      for (int t = 0; t < h; ++t) {
+        const double keep = up ? v[t + h] : v[t], give = up ? v[t] : v[t + h];
+        v[t] = keep + __shfl_xor(give, o, kWave);
+      }
+      m += up ? h : 0;
+    }
+#pragma unroll
+    for (int o = kWave / 2 / kRbfChunk; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, kWave);
+    if ((lane & (kWave / kRbfChunk - 1)) == 0 && m < nr) {
+      double *c = cpart + (size_t)blockIdx.x * kMaxRbf + m;
+      *c = first ? v[0] : *c + v[0];
+    }
   }
 }
 
-// c-bar[m] += sum over blocks of cpart[b][m]: one block per coefficient, each thread summing
-// every 256th block partial in order, then a fixed tree over the threads (deterministic).
+// c-bar[m] = sum over the rows of cpart[row][m]: one block per coefficient, each thread summing
+// every 256th row in order, then a fixed tree over the threads (deterministic).
 constexpr int kCoeffSumThreads = 256;
-__global__ __launch_bounds__(kCoeffSumThreads) void adj_sum_coeff(const double *__restrict__ cpart, int nblocks,
+__global__ __launch_bounds__(kCoeffSumThreads) void adj_sum_coeff(const double *__restrict__ cpart, int rows,
                                                                   int n_rbf, double *__restrict__ cbar) {
   __shared__ double red[kCoeffSumThreads];
   const int m = blockIdx.x;
   if (m >= n_rbf) return;  // block-uniform
   double s = 0.0;
-  for (int b = threadIdx.x; b < nblocks; b += kCoeffSumThreads) s += cpart[(size_t)b * kMaxRbf + m];
+#pragma unroll 4
+  for (int b = threadIdx.x; b < rows; b += kCoeffSumThreads) s += cpart[(size_t)b * kMaxRbf + m];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int off = kCoeffSumThreads / 2; off > 0; off >>= 1) {
     if (threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
     __syncthreads();
   }
-  if (threadIdx.x == 0) cbar[m] += red[0];
+  if (threadIdx.x == 0) cbar[m] = red[0];
 }
 
 // Loss, first pass (L lanes per particle, sorted order of the final state):
@@ -583,10 +638,14 @@ __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict_
     const float kh = 0.5f * sp.kappa;
     float ws = 0.f, wi = 0.f;
     const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
-    scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
-                                                 0u, cstart, [&](uint32_t jr) {
-      const float4 pj = buf_f4(rpos, jr);
-      const uint32_t aj = buf_u32(raux, jr);
+    struct Nb {
+      float4 p;
+      uint32_t a;
+    };
+    const auto fetch = [&](uint32_t jr) { return Nb{buf_f4(rpos, jr), buf_u32(raux, jr)}; };
+    const auto use = [&](const Nb &nb) {
+      const float4 pj = nb.p;
+      const uint32_t aj = nb.a;
       const float dx = fixed_diff(xi.x, pj.x) * unit;
       const float dy = fixed_diff(xi.y, pj.y) * unit;
       float r2 = dx * dx + dy * dy;
@@ -604,7 +663,9 @@ __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict_
         const float q = r * sp.kappa * fast_rcp(hij), u = fmaf(-0.5f, q, 1.f);
         wi += u * u * u * u * fmaf(2.f, q, 1.f);
       }
-    });
+    };
+    scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
+                                                0u, cstart, pair_body<true>(fetch, use));
     ws = group_sum<L>(ws);
     wi = group_sum<L>(wi);
     if (sub == 0) {
@@ -615,7 +676,7 @@ __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict_
       part[1] = (double)wi;
     }
   }
-  block_reduce_write<2, L>(part, ops, partials + (size_t)lb * kNumPartials);   // first lanes of the groups
+  block_reduce_write<2, L>(part, ops, partials + 2 * (size_t)lb);   // first lanes of the groups
 }
 
 // Loss, gradient pass: with ebar = 2 e / n and the interface weight cl = lambda / n,
@@ -650,11 +711,15 @@ __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ d
   const float kh = 0.5f * sp.kappa;
   float xb[3] = {0.f, 0.f, 0.f}, sb = 0.f;
   const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
-  scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
-                                                 0u, cstart, [&](uint32_t jr) {
-    const int j = (int)jr;
-    const float4 pj = buf_f4(rpos, jr);
-    const uint32_t aj = buf_u32(raux, jr);
+  const BufRes re = buf_res(e, 4, (uint32_t)g.n);
+  struct Nb {
+    float4 p;
+    uint32_t a, e;
+  };
+  const auto fetch = [&](uint32_t jr) { return Nb{buf_f4(rpos, jr), buf_u32(raux, jr), buf_u32(re, jr)}; };
+  const auto use = [&](const Nb &nb) {
+    const float4 pj = nb.p;
+    const uint32_t aj = nb.a;
     const float dx = fixed_diff(xi.x, pj.x) * unit;
     const float dy = fixed_diff(xi.y, pj.y) * unit;
     float dz = 0.f;
@@ -675,7 +740,7 @@ __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ d
     const float ihj = fast_rcp(pj.w), qj = r * ihj;
     if (qj < sp.kappa) {
       const float u = fmaf(-0.5f, qj, 1.f);
-      cx += ebar_scale * e[j] * A * u * u * u * ihj * ihj;
+      cx += ebar_scale * __uint_as_float(nb.e) * A * u * u * u * ihj * ihj;
     }
     const float hij = kh * (hi + pj.w);
     if (colour_differs(aj, ai) && r2 < hij * hij) {
@@ -687,7 +752,9 @@ __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ d
     xb[0] = fmaf(cx, dx, xb[0]);
     xb[1] = fmaf(cx, dy, xb[1]);
     if constexpr (D == 3) xb[2] = fmaf(cx, dz, xb[2]);
-  });
+  };
+  scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
+                                              0u, cstart, pair_body<true>(fetch, use));
 #pragma unroll
   for (int a = 0; a < 3; ++a) xb[a] = group_sum<L>(xb[a]);
   sb = group_sum<L>(sb);
@@ -697,19 +764,21 @@ __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ d
   }
 }
 
+constexpr int kLossThreads = 1024;
 // Loss value from the first loss pass's partials: sum e^2 / n + lambda sum_ifc / (2 n).
-__global__ __launch_bounds__(256) void loss_value(const double *__restrict__ pb, int nb, double inv_n, double lam,
+__global__ __launch_bounds__(kLossThreads) void loss_value(const double *__restrict__ pb, int nb, double inv_n, double lam,
                                                   double *__restrict__ out) {
-  __shared__ double r0[256], r1[256];
+  __shared__ double r0[kLossThreads], r1[kLossThreads];
   double x = 0.0, y = 0.0;
-  for (int b = threadIdx.x; b < nb; b += 256) {
-    x += pb[(size_t)b * kNumPartials];
-    y += pb[(size_t)b * kNumPartials + 1];
+#pragma unroll 4
+  for (int b = threadIdx.x; b < nb; b += kLossThreads) {
+    x += pb[2 * (size_t)b];
+    y += pb[2 * (size_t)b + 1];
   }
   r0[threadIdx.x] = x;
   r1[threadIdx.x] = y;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
+  for (int w = kLossThreads / 2; w > 0; w >>= 1) {
     if (threadIdx.x < w) {
       r0[threadIdx.x] += r0[threadIdx.x + w];
       r1[threadIdx.x] += r1[threadIdx.x + w];
@@ -719,8 +788,34 @@ __global__ __launch_bounds__(256) void loss_value(const double *__restrict__ pb,
   if (threadIdx.x == 0) out[0] = r0[0] * inv_n + lam * 0.5 * r1[0] * inv_n;
 }
 
-// Sets the device step counter (the recomputation of a segment restarts at its first step).
-__global__ void set_step(int64_t *stepctr, int64_t t) { *stepctr = t; }
+// State arrays of a run (a checkpoint or the context's).
+struct StateView {
+  uint32_t *key;
+  float4 *off;
+  uint32_t *ct, *id, *cell;
+};
+
+// Copies a state, and the metrics where both pointers are given.  A state that becomes the context's
+// (counts given, all zero on entry) has its particles counted by cell again, as the load does it, and
+// the step counter set to t.  One launch: a copy of each array costs 3 us of its own at 8,192
+// particles.
+__global__ __launch_bounds__(kBlock) void copy_state(StateView to, StateView from, int n, double *__restrict__ m_to,
+                                                     const double *__restrict__ m_from, uint32_t *__restrict__ counts,
+                                                     int64_t *__restrict__ stepctr, int64_t t) {
+  const int i = blockIdx.x * kBlock + threadIdx.x;
+  if (m_to && i < 32) m_to[i] = m_from[i];
+  if (counts && i == 0) *stepctr = t;
+  if (i >= n) return;
+  // all loads before the first store, which the compiler could not move them across
+  const uint32_t cell = from.cell[i], key = from.key[i], ct = from.ct[i], id = from.id[i];
+  const float4 o = from.off[i];
+  const float w = counts ? __uint_as_float(atomicAdd(&counts[cell], 1u)) : o.w;
+  to.key[i] = key;
+  to.ct[i] = ct;
+  to.id[i] = id;
+  to.cell[i] = cell;
+  to.off[i] = make_float4(o.x, o.y, o.z, w);
+}
 
 // Positions adjoint of the first step's start state to the caller's layout (domain units).
 template <int D>

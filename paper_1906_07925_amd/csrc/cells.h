@@ -23,8 +23,9 @@ hipError_t count_cells(const uint32_t *keys, float4 *off, uint32_t *counts, int 
 
 // From the counts and arrival numbers: the cell table cstart[c] = particles in cells below c
 // (c <= ncells), and the particles grouped by cell, slots[s] for s in [cstart[c], cstart[c + 1])
-// naming those of cell c in an unspecified order.  Leaves counts all zero.  Enqueued on stream.
+// naming those of cell c in an unspecified order.  Leaves counts all zero, or with keep as they are.
+// Enqueued on stream.
 hipError_t cell_order(const uint32_t *keys, const float4 *off, uint32_t *counts, uint32_t *sums, uint32_t *cstart,
-                      uint32_t *slots, int n, uint32_t ncells, hipStream_t stream, LaunchHook *hook);
+                      uint32_t *slots, int n, uint32_t ncells, bool keep, hipStream_t stream, LaunchHook *hook);
 
 }  // namespace mpsph

@@ -140,7 +140,7 @@ hipError_t count_cells(const uint32_t *keys, float4 *off, uint32_t *counts, int 
 }
 
 hipError_t cell_order(const uint32_t *keys, const float4 *off, uint32_t *counts, uint32_t *sums, uint32_t *cstart,
-                      uint32_t *slots, int n, uint32_t ncells, hipStream_t stream, LaunchHook *hook) {
+                      uint32_t *slots, int n, uint32_t ncells, bool keep, hipStream_t stream, LaunchHook *hook) {
   const uint32_t tiles = (uint32_t)cell_sum_words(ncells);
   const uint4 *c4 = reinterpret_cast<const uint4 *>(counts);
   const bool self = tiles <= kSelfSumTiles;
@@ -150,7 +150,7 @@ hipError_t cell_order(const uint32_t *keys, const float4 *off, uint32_t *counts,
   if (hook) hook->end();
   if (hook) hook->begin("cell_place");
   cell_place<<<(n + 255) / 256, 256, 0, stream>>>(keys, off, cstart, reinterpret_cast<uint4 *>(counts),
-                                                  tiles * (kScanTile / 4), slots, n);
+                                                  keep ? 0u : tiles * (kScanTile / 4), slots, n);
   if (hook) hook->end();
   return hipGetLastError();
 }
