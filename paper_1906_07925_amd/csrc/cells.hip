@@ -5,6 +5,7 @@
 //   cell_sums   sums of tiles of kScanTile counts (large tables only)
 //   cell_scan   exclusive prefix of the counts = the cell table
 //   cell_place  every particle's index to slot cstart[key] + arrival; the counts back to zero
+// (cell_order_small does all of it in one block for small sets)
 // The arrival order inside a cell depends on timing; the gather that follows ranks each
 // particle among its cell's slots by index, so the final order is that of a stable sort by key.
 // Bound by launch latency up to ~10^5 particles and beyond by the table's bytes (12 per cell; at
@@ -131,6 +132,57 @@ __global__ __launch_bounds__(256) void cell_count(const uint32_t *__restrict__ k
   if (i < n) off[i].w = __uint_as_float(atomicAdd(&counts[keys[i]], 1u));
 }
 
+// Scan, place and clearing of a set whose table is one tile, in one block: a 16-byte load of the
+// counts per thread and up to kSmallItems particles.  Latency only: the particles' keys are loaded with
+// the counts, and what a second launch would cost (its start and the gap before it) is saved.
+constexpr int kSmallThreads = 1024, kSmallItems = 4;
+__global__ __launch_bounds__(kSmallThreads) void cell_order_small(const uint32_t *__restrict__ keys,
+                                                                  const float4 *__restrict__ off, uint4 *counts,
+                                                                  uint32_t *cstart, uint32_t *__restrict__ slots, uint32_t n,
+                                                                  uint32_t ncells, int keep) {
+  static_assert(kScanTile == 4 * kSmallThreads, "one load per thread");
+  __shared__ uint32_t lds[kSmallThreads / 64];
+  const uint32_t tid = threadIdx.x;
+  const int lane = tid & 63, w = tid >> 6;
+  const uint4 v = counts[tid];
+  uint32_t key[kSmallItems], arr[kSmallItems];
+#pragma unroll
+  for (int q = 0; q < kSmallItems; ++q) {
+    const uint32_t t = tid + (uint32_t)q * kSmallThreads;
+    if (t < n) {
+      key[q] = keys[t];
+      arr[q] = __float_as_uint(off[t].w);
+    }
+  }
+  if (!keep) counts[tid] = make_uint4(0u, 0u, 0u, 0u);
+  const uint32_t own = v.x + v.y + v.z + v.w;
+  const uint32_t incl = wave_inclusive(own, lane);
+  if (lane == 63) lds[w] = incl;
+  __syncthreads();
+  uint32_t run = incl - own;
+#pragma unroll
+  for (int ww = 0; ww < kSmallThreads / 64; ++ww) run += ww < w ? lds[ww] : 0u;
+  const uint32_t at = tid * 4u;
+  const uint4 u = make_uint4(run, run + v.x, run + v.x + v.y, run + v.x + v.y + v.z);
+  if (at + 4u <= ncells) {
+    *reinterpret_cast<uint4 *>(cstart + at) = u;
+  } else {
+    if (at < ncells) cstart[at] = u.x;
+    if (at + 1u < ncells) cstart[at + 1u] = u.y;
+    if (at + 2u < ncells) cstart[at + 2u] = u.z;
+  }
+  if (tid == 0) cstart[ncells] = n;
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kSmallItems; ++q) {
+    const uint32_t t = tid + (uint32_t)q * kSmallThreads;
+    if (t < n) {
+      const uint32_t to = cstart[key[q]] + arr[q];
+      if (to < n) slots[to] = t;
+    }
+  }
+}
+
 size_t cell_sum_words(uint32_t ncells) { return ((size_t)ncells + kScanTile - 1) / kScanTile; }
 size_t cell_count_words(uint32_t ncells) { return cell_sum_words(ncells) * kScanTile; }
 
@@ -144,6 +196,16 @@ hipError_t cell_order(const uint32_t *keys, const float4 *off, uint32_t *counts,
   const uint32_t tiles = (uint32_t)cell_sum_words(ncells);
   const uint4 *c4 = reinterpret_cast<const uint4 *>(counts);
   const bool self = tiles <= kSelfSumTiles;
+  // One block for up to 4,096 particles with a table of one tile: 3.4 us in place of two launches of 2.5
+  // and 1.8 us with a gap between them (a call of one step of 1,024 particles 94 -> 90.5 us).  With a table of 4
+  // tiles the block takes 6.3 us and a step is 1 us slower than with the two launches.
+  if (n > 0 && n <= kSmallThreads * kSmallItems && tiles == 1) {
+    if (hook) hook->begin("cell_scan");
+    cell_order_small<<<1, kSmallThreads, 0, stream>>>(keys, off, reinterpret_cast<uint4 *>(counts), cstart, slots, (uint32_t)n,
+                                                      ncells, keep ? 1 : 0);
+    if (hook) hook->end();
+    return hipGetLastError();
+  }
   if (hook) hook->begin("cell_scan");
   if (!self) cell_sums<<<tiles, kScanThreads, 0, stream>>>(c4, sums);
   cell_scan<<<tiles, kScanThreads, 0, stream>>>(c4, self ? nullptr : sums, cstart, ncells, (uint32_t)n);

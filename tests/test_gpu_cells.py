@@ -45,3 +45,10 @@ def test_cell_table_and_order(dim, n, k):
     (xa, ta), ma = out[0]
     (xb, tb), mb = out[1]
     assert torch.equal(xa, xb) and torch.equal(ta, tb) and ma == mb
+
+
+# tables of one tile, ordered by one block: a lone particle, a wave's edge, the most particles of the
+# block and one more (two launches again)
+@pytest.mark.parametrize("dim,n,k", [(2, 1, 3), (2, 65, 3), (2, 1023, 3), (2, 4095, 3), (2, 4096, 3), (2, 4097, 3), (3, 4096, 2)])
+def test_one_block_order(dim, n, k):
+    test_cell_table_and_order(dim, n, k)
