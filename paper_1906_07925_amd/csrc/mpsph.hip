@@ -332,6 +332,9 @@ __device__ bool stage_tile(TileLds *T, bool active, int sub, const OwnRow &own, 
 // the vector instructions and neighbour loads of its pair loop: with this and the wave-uniform loop of
 // the scan, 1018 -> 976 us on the 2^21-particle cube; whole steps 695 -> 675 us (relaxed 2^20-particle
 // cube), 125 -> 116 us (annulus of 2^18 particles), 69 us instead of 74 (seeded ball of 20000).
+// The issue of vector instructions is the bound: the kernel in u = 1 - q/2 alone and the nearest distance
+// by its bits (4 instructions of some 57 per candidate) took 976 to 956 us and 329 to 319 us on the cubes;
+// waiting for fewer loads in the scan changed nothing.
 #define MPSPH_PASS1_PARAMS                                                                                   \
   const DomDev *__restrict__ doms, int ndom, const int64_t *__restrict__ stepctr,                            \
       const uint32_t *__restrict__ wkey, const float4 *__restrict__ wpos, const float4 *__restrict__ wfix,    \
@@ -392,14 +395,14 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
     // units, the distance is converted to cells
     const float Phi = powd<D>(hi * hi);
     const float fscale = sp.p0c * powd<D>(sp.inv_tau * sp.inv_tau) * (5.f * sp.alpha) * (D == 3 ? 32.f : 16.f) * g.funit;
-    const float ihi = fast_rcp(hi);
+    const float mhh = -0.5f * fast_rcp(hi);
     const float rci = sp.kappa * hi;
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
     const float kh = 0.5f * sp.kappa;
     const float unit = g.funit;
     const float opb = 1.f + sigma;
-    float wsum = 0.f, ax = 0.f, ay = 0.f, az = 0.f, A = 0.f, nn = INFINITY;
-    uint32_t npair = 0, nifc = 0;
+    float wsum = 0.f, ax = 0.f, ay = 0.f, az = 0.f, A = 0.f;
+    uint32_t npair = 0, nifc = 0, nn = kInfBits;
     const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
     const auto pair = [&](const float4 pj, const uint32_t aj) {
       const float dx = fixed_diff(xi.x, pj.x), dy = fixed_diff(xi.y, pj.y);
@@ -421,25 +424,27 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
       // the compares, where each becomes one add-with-carry of the compare's lane mask instead
       // of a select and an add after the branch
       asm volatile("" : "+v"(npair), "+v"(nifc));
-      const float q = r * ihi;
+      // (1 - q/2)^4 (1 + 2q) = u^4 (5 - 4u) with u = 1 - q/2
+      const float u0 = fmaf(mhh, r, 1.f);
       if constexpr (K2) {
         // the kernel's support ends at the cut-off: its factor clamped to [0, 1] (an output modifier)
         // is zero beyond, without a test
-        const float u = __builtin_amdgcn_fmed3f(fmaf(-0.5f, q, 1.f), 0.f, 1.f), u2 = u * u;
-        wsum = fmaf(u2 * u2, fmaf(2.f, q, 1.f), wsum);
+        const float u = __builtin_amdgcn_fmed3f(u0, 0.f, 1.f), u2 = u * u;
+        wsum = fmaf(u2 * u2, fmaf(-4.f, u, 5.f), wsum);
       } else {
-        const float u = fmaf(-0.5f, q, 1.f), u2 = u * u;
-        if (r < rci) wsum = fmaf(u2 * u2, fmaf(2.f, q, 1.f), wsum);
+        const float u2 = u0 * u0;
+        if (r < rci) wsum = fmaf(u2 * u2, fmaf(-4.f, u0, 5.f), wsum);
       }
       // the nearest distance counts for normal particles, which feel every type; the debug export
       // has it for all
+      // (as bits, in whose order non-negative floats are: one instruction, fminf takes three)
       if constexpr (DBG) {
-        if (inter) nn = fminf(nn, r);
+        if (inter) nn = min(nn, __float_as_uint(r));
       }
       // coincident particles (two particles clamped into one corner) need no test: their separation
       // is zero and the force factor finite
       if (!feel) return;
-      if constexpr (!DBG) nn = fminf(nn, r);
+      if constexpr (!DBG) nn = min(nn, __float_as_uint(r));
       const float hj2 = pj.w * pj.w;
       // (P_i + P_j) (-dW/dr / r) over the common factor fscale (>= 0)
       const float s = (diff ? opb : 1.f) * powd_add<D>(hj2, Phi) * kernel_slope_factor<D>(r, fast_rcp(hs));
@@ -476,7 +481,7 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
     gy = fscale * group_sum<L>(ay);
     if constexpr (D == 3) gz = fscale * group_sum<L>(az);
     if constexpr (DBG) gA = fscale * (float)(1u << g.fb) * group_sum<L>(A);
-    gn = group_min<L>(nn);
+    gn = group_min<L>(__uint_as_float(nn));
     gp = group_sum_u<L>(npair);
     gi = group_sum_u<L>(nifc);
     gc = ncand;
@@ -840,7 +845,6 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
           const float hs = hi + pj.w;   // 2 h_ij
           // the particle itself and coincident particles have r = 0 exactly
           if (!(r > 0.f && r < (K2 ? hs : kh * hs) && type_at_least(nb.a, ti))) return;
-          // e_j          const float r = fast_sqrt(r2);
           // e_j / (e_i + e_j): half the harmonic mean e_i e_j / (e_i + e_j) over e_i, which
           // multiplies the sum once; e_i > 0 here and e_j >= 0, so the sum is positive
           const float eh = accj.w * fast_rcp(acci.w + accj.w);
