@@ -28,10 +28,10 @@
 
 // Waves per SIMD the viscous adjoint is compiled for; 0 leaves it to the compiler.  With the
 // particle's own data scoped to the pair loop and its per-group values in LDS, and the neighbour
-// loads issued one slot round ahead (four loads held for the next round), 5 waves (88 VGPRs in
+// loads issued one slot round ahead (three loads held for the next round), 5 waves (89 VGPRs in
 // 3D) need no scratch memory; at 6 waves it spills 10 registers.  Reverse sweep of the
-// 2^20-particle RBF cube over 50 steps: 106.7 ms at 5 waves, 109.4 ms at 6 with the spills,
-// 107.4 ms with one round of loads at 6 waves.
+// 2^20-particle RBF cube over 50 steps, with the pair terms in spacings: 106.7 ms at 5 waves, 109.4 ms at
+// 6 with the spills, 107.4 ms with one round of loads at 6 waves.
 #ifndef MPSPH_ADJ_WAVES
 #define MPSPH_ADJ_WAVES 5
 #endif
@@ -64,17 +64,23 @@ __device__ __forceinline__ float pow2d(float s) {  // s^(2d)
   return powd<D>(s * s);
 }
 
-// H^-(d+2) and H^-(d+3) from ih = 1/H.
+// The pair adjoints take the kernel's derivatives from one common factor, with 2H = h_i + h_j,
+// u = 1 - r / 2H and w = (2H)^-(d+3) u^2:
+//   g = C w u 2H / 2,  dg/dr = -(3/2) C w,  dg/dH = C w (3 - (d+5) u),  C = 5 alpha 2^(d+3),
+// and spacings as h^2d = tau^2d s^2d; every factor common to a particle's pairs is applied once to its
+// sums.  Bound by the issue of vector instructions: at 262,144 particles the
+// viscous adjoint took 161 us and the force adjoint 122 with g, dg/dr and dg/dH formed one by one in
+// spacings, 151 and 110 this way.
 template <int D>
-__device__ __forceinline__ void inv_pows(float ih, float &p2, float &p3) {
-  const float ih2 = ih * ih;
-  if constexpr (D == 3) {
-    p2 = ih2 * ih2 * ih;
-    p3 = ih2 * ih2 * ih2;
-  } else {
-    p2 = ih2 * ih2;
-    p3 = ih2 * ih2 * ih;
-  }
+__device__ __forceinline__ float slope_scale(float alpha) {
+  return (D == 3 ? 320.f : 160.f) * alpha;
+}
+
+// w from i = 1 / 2H and u.
+template <int D>
+__device__ __forceinline__ float slope_factor(float i, float u) {
+  const float i2 = i * i;
+  return (D == 3 ? i2 * i2 * i2 : i2 * i2 * i) * (u * u);
 }
 
 // The RBF table of a field, entry m in lane m of the wave (kMaxRbf of them at most).  Read from there
@@ -233,7 +239,7 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
   const int local = lb * kBlock + threadIdx.x;
   const int i = local / L, sub = local % L;
   __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  // per lane group, the particle's (v~, eta) and (a~-bar, d s^(2d)/ds): read from LDS by the
+  // per lane group, the particle's (a, e) and (a~-bar, d h^(2d)/dh): read from LDS by the
   // pair terms instead of being held in registers across the pair loop
   __shared__ float4 gdat[kBlock / L][2];
   const float dt1 = read_dt1(tp.dts);
@@ -244,9 +250,9 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
   if (i < dom->n && sub == 0) {
     const float4 ai = tp.acc[i];
     const float4 abi = abv[i];
-    const float si = tp.wpos[i].w * sp.inv_tau;
-    gdat[threadIdx.x / L][0] = make_float4(hdt * ai.x, hdt * ai.y, hdt * ai.z, hdt * ai.w);
-    gdat[threadIdx.x / L][1] = make_float4(abi.x, abi.y, abi.z, (2.f * (float)D) * pow2d<D>(si) / si);
+    const float hi = tp.wpos[i].w;
+    gdat[threadIdx.x / L][0] = ai;
+    gdat[threadIdx.x / L][1] = make_float4(abi.x, abi.y, abi.z, (2.f * (float)D) * pow2d<D>(hi) / hi);
   }
   __syncthreads();
   if (i < dom->n) {
@@ -261,13 +267,13 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
     const OwnRow own = own_row<D>(ci, xi, g);
     const float unit = g.funit;
     const int ti = aux_type(tp.wjaux[i]);
-    const float hi = pi.w, si = hi * sp.inv_tau;
-    const float s2di = pow2d<D>(si);
+    const float hi = pi.w;
+    const float h2di = pow2d<D>(hi);
     const float4 *gd = gdat[threadIdx.x / L];
     const float ei = gd[0].w;
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
-    const float kh = 0.5f * sp.kappa, a5 = 5.f * sp.alpha, a75 = 7.5f * sp.alpha;
-    if (ei > 0.f) {
+    const float kh = 0.5f * sp.kappa;
+    if (hdt * ei > 0.f) {
       const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n);
       const BufRes racc = buf_res(tp.acc, 16, (uint32_t)g.n), rabv = buf_res(abv, 16, (uint32_t)g.n);
       struct Nb {
@@ -280,46 +286,40 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
       };
       const auto use = [&](const Nb &nb) {
         const float4 pj = nb.p, aj4 = nb.a4, abj = nb.ab;
-        const float dx = fixed_diff(xi.x, pj.x) * unit;
-        const float dy = fixed_diff(xi.y, pj.y) * unit;
+        // separations in fixed-point units
+        const float dx = fixed_diff(xi.x, pj.x);
+        const float dy = fixed_diff(xi.y, pj.y);
         float dz = 0.f;
         float r2 = dx * dx + dy * dy;
         if constexpr (D == 3) {
-          dz = fixed_diff(xi.z, pj.z) * unit;
+          dz = fixed_diff(xi.z, pj.z);
           r2 += dz * dz;
         }
-        const float hij = kh * (hi + pj.w);
-        if (!(r2 > 0.f && r2 < hij * hij)) return;
-        const int tj = __float_as_int(abj.w);
-        const float ej = hdt * aj4.w;
-        if (!(ej > 0.f)) return;  // eta_j = 0: the pair's K and every derivative of it vanish
-        const float mkj = tj >= ti ? 1.f : 0.f, mjk = ti >= tj ? 1.f : 0.f;
-        const float4 vti = gd[0], abi = gd[1];
-        const float ds2i = abi.w;
-        const float wv[3] = {mkj * abi.x - mjk * abj.x, mkj * abi.y - mjk * abj.y, mkj * abi.z - mjk * abj.z};
         const float rinv = fast_rsq(r2);
-        const float r = r2 * rinv;
-        const float ih = sp.kappa * fast_rcp(hij);
-        const float q = r * ih, u = fmaf(-0.5f, q, 1.f);
-        float p2, p3;
-        inv_pows<D>(ih, p2, p3);
-        const float gg = a5 * p2 * u * u * u;
-        const float dgr = -a75 * p3 * u * u;
-        const float dgh = a5 * p3 * u * u * (1.5f * q - (float)(D + 2) * u);
-        const float sj = pj.w * sp.inv_tau;
-        const float S = s2di + pow2d<D>(sj);
-        const float esum = ei + ej;
-        const float iesum = fast_rcp(esum);
-        const float hm = 2.f * ei * ej * iesum;
-        const float K = -hm * S * gg;
+        const float r = r2 * rinv * unit;   // NaN at zero separation
+        const float hs = hi + pj.w;
+        const float ej = aj4.w;
+        // e_j = 0: the pair's K and every derivative of it vanish
+        if (!(r > 0.f && r < kh * hs && ej > 0.f)) return;
+        const int tj = __float_as_int(abj.w);
+        const float mkj = tj >= ti ? 1.f : 0.f, mjk = ti >= tj ? 1.f : 0.f;
+        const float4 ai = gd[0], abi = gd[1];
+        const float wv[3] = {mkj * abi.x - mjk * abj.x, mkj * abi.y - mjk * abj.y, mkj * abi.z - mjk * abj.z};
+        const float i2h = fast_rcp(hs);
+        const float u = fmaf(-r, i2h, 1.f);
+        const float w = slope_factor<D>(i2h, u), uh = u * hs;
+        const float sw = powd_add<D>(pj.w * pj.w, h2di) * w;
+        const float rat = ej * fast_rcp(ei + ej);
+        const float K = rat * (sw * uh);
         vb[0] = fmaf(K, wv[0], vb[0]);
         vb[1] = fmaf(K, wv[1], vb[1]);
         if constexpr (D == 3) vb[2] = fmaf(K, wv[2], vb[2]);
-        const float dvx = vti.x - hdt * aj4.x, dvy = vti.y - hdt * aj4.y, dvz = vti.z - hdt * aj4.z;
+        const float dvx = ai.x - aj4.x, dvy = ai.y - aj4.y, dvz = ai.z - aj4.z;
         const float kb = wv[0] * dvx + wv[1] * dvy + (D == 3 ? wv[2] * dvz : 0.f);
-        eb = fmaf(kb * (-S * gg) * 2.f * ej * ej, iesum * iesum, eb);
-        sb = fmaf(kb * (-hm), ds2i * gg + S * dgh * (0.5f * sp.tau), sb);
-        const float cx = kb * (-hm * S * dgr) * rinv;
+        const float m = kb * rat;
+        eb = fmaf(m, K, eb);
+        sb = fmaf(m, fmaf(abi.w, w * uh, sw * fmaf(-(float)(D + 5), u, 3.f)), sb);
+        const float cx = m * sw * rinv;
         xb[0] = fmaf(cx, dx, xb[0]);
         xb[1] = fmaf(cx, dy, xb[1]);
         if constexpr (D == 3) xb[2] = fmaf(cx, dz, xb[2]);
@@ -344,6 +344,15 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
       const uint32_t xo = tp.wjaux[io];
       const int ti = aux_type(xo);
       const float4 ai = tp.acc[io];
+      // the factors common to the particle's pairs
+      const float fe = -hdt * slope_scale<D>(sp.alpha) * pow2d<D>(sp.inv_tau), fv = fe * ai.w, fs = fv * hdt;
+      eb *= fe;
+      sb *= fs * sp.tau;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        vb[a] *= fv;
+        xb[a] *= -3.f * fs;
+      }
       const float vti[3] = {hdt * ai.x, hdt * ai.y, hdt * ai.z};
       const float4 vd = vtb[io];
       float vt[3] = {vd.x + vb[0], vd.y + vb[1], vd.z + vb[2]};
@@ -448,12 +457,12 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   const float unit = g.funit;
   const uint32_t ai = tp.wjaux[i];
   const int ti = aux_type(ai);
-  const float hi = pi.w, si = hi * sp.inv_tau;
-  const float Pi = sp.p0c * pow2d<D>(si);
-  const float dPi = (2.f * (float)D) * Pi / si;
+  const float hi = pi.w;
+  const float h2di = pow2d<D>(hi);
+  const float dh2di = (2.f * (float)D) * h2di / hi;
   const float4 fi = fbar[i];
   const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
-  const float kh = 0.5f * sp.kappa, a5 = 5.f * sp.alpha, a75 = 7.5f * sp.alpha;
+  const float kh = 0.5f * sp.kappa, unit3 = -3.f * unit;
   const float opb = 1.f + sigma_of(sp, tstep);   // surface tension of the step (Eq. 24-25)
   float xb[3] = {0.f, 0.f, 0.f}, sb = 0.f;
   const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n);
@@ -467,38 +476,32 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   const auto use = [&](const Nb &nb) {
     const float4 pj = nb.p, fj = nb.f;
     const uint32_t aj = __float_as_uint(fj.w);
-    const float dx = fixed_diff(xi.x, pj.x) * unit;
-    const float dy = fixed_diff(xi.y, pj.y) * unit;
+    // separations in fixed-point units
+    const float dx = fixed_diff(xi.x, pj.x);
+    const float dy = fixed_diff(xi.y, pj.y);
     float dz = 0.f;
     float r2 = dx * dx + dy * dy;
     if constexpr (D == 3) {
-      dz = fixed_diff(xi.z, pj.z) * unit;
+      dz = fixed_diff(xi.z, pj.z);
       r2 += dz * dz;
     }
-    const float hij = kh * (hi + pj.w);
-    if (!(r2 > 0.f && r2 < hij * hij)) return;
+    const float rinv = fast_rsq(r2);
+    const float r = r2 * rinv * unit;   // NaN at zero separation
+    const float hs = hi + pj.w;
+    if (!(r > 0.f && r < kh * hs)) return;
     const int tj = aux_type(aj);
     const float mkj = tj >= ti ? 1.f : 0.f, mjk = ti >= tj ? 1.f : 0.f;
     const float wf[3] = {mkj * fi.x - mjk * fj.x, mkj * fi.y - mjk * fj.y, mkj * fi.z - mjk * fj.z};
-    const float rinv = fast_rsq(r2);
-    const float r = r2 * rinv;
-    const float ih = sp.kappa * fast_rcp(hij);
-    const float q = r * ih, u = fmaf(-0.5f, q, 1.f);
-    float p2, p3;
-    inv_pows<D>(ih, p2, p3);
-    const float gg = a5 * p2 * u * u * u;
-    const float dgr = -a75 * p3 * u * u;
-    const float dgh = a5 * p3 * u * u * (1.5f * q - (float)(D + 2) * u);
-    const float B = colour_differs(aj, ai) ? opb : 1.f;
-    const float sj = pj.w * sp.inv_tau;
-    const float Psum = Pi + sp.p0c * pow2d<D>(sj);
-    const float w = B * Psum * gg;
+    const float i2h = fast_rcp(hs);
+    const float u = fmaf(-r, i2h, 1.f), uh = u * hs;
+    const float bw = (colour_differs(aj, ai) ? opb : 1.f) * slope_factor<D>(i2h, u);
+    const float x = powd_add<D>(pj.w * pj.w, h2di) * bw;
     const float uw = dx * wf[0] + dy * wf[1] + (D == 3 ? dz * wf[2] : 0.f);
-    const float cr = B * Psum * dgr * uw * rinv;
-    xb[0] += w * wf[0] + cr * dx;
-    xb[1] += w * wf[1] + cr * dy;
-    if constexpr (D == 3) xb[2] += w * wf[2] + cr * dz;
-    sb = fmaf(uw * B, dPi * gg + Psum * dgh * (0.5f * sp.tau), sb);
+    const float cw = x * uh, cr = x * uw * (rinv * unit3);
+    xb[0] = fmaf(cw, wf[0], fmaf(cr, dx, xb[0]));
+    xb[1] = fmaf(cw, wf[1], fmaf(cr, dy, xb[1]));
+    if constexpr (D == 3) xb[2] = fmaf(cw, wf[2], fmaf(cr, dz, xb[2]));
+    sb = fmaf(uw, fmaf(dh2di, bw * uh, x * fmaf(-(float)(D + 5), u, 3.f)), sb);
   };
   scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
                                               0u, tp.cstart, pair_body<true>(fetch, use));
@@ -506,9 +509,11 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   for (int a = 0; a < 3; ++a) xb[a] = group_sum<L>(xb[a]);
   sb = group_sum<L>(sb);
   if (sub == 0) {
+    // the factors common to the particle's pairs
+    const float fx = 0.5f * slope_scale<D>(sp.alpha) * sp.p0c * pow2d<D>(sp.inv_tau);
     const float4 x0 = xacc[i];
-    xacc[i] = make_float4(x0.x + xb[0], x0.y + xb[1], x0.z + xb[2], 0.f);
-    sbar[i] += sb;
+    xacc[i] = make_float4(fmaf(fx, xb[0], x0.x), fmaf(fx, xb[1], x0.y), fmaf(fx, xb[2], x0.z), 0.f);
+    sbar[i] = fmaf(fx * sp.tau * unit, sb, sbar[i]);
   }
 }
 
