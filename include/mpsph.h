@@ -270,7 +270,8 @@ MPSPH_API int mpsph_configure(mpsph_ctx *ctx, int32_t cell_log2, int32_t lanes);
 
 /* Pair-kernel variants (mpsph_set_pair_variant).  Every variant computes the same step bit for bit;
  * they differ in how the work reaches the GPU:
- *   MPSPH_PAIRS_DEFAULT     one launch per pass and dimension group, a block per 256 threads;
+ *   MPSPH_PAIRS_DEFAULT     one launch per pass and dimension group (one for both groups of a mixed
+ *                           batch that was not configured), a block per 256 threads;
  *   MPSPH_PAIRS_PERSISTENT  one persistent launch per pass for all domains of both dimensions: a
  *                           fixed grid (8 blocks per CU) takes the blocks from a work queue in
  *                           device memory (one range per XCD, then stealing), so that uneven
