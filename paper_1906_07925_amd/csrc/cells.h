@@ -14,7 +14,7 @@ struct LaunchHook {
 
 // Entries of the count array for ncells cells: whole tiles of the scan, the rest zero.
 size_t cell_count_words(uint32_t ncells);
-// Words of the tile sums.
+// Words of the tile sums, all zero before and after an order.
 size_t cell_sum_words(uint32_t ncells);
 
 // Counts the particles per cell from their keys: counts[key] over all particles and each

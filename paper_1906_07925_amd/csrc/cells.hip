@@ -21,9 +21,15 @@ namespace mpsph {
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;   // counts per thread, four 16-byte loads
 constexpr uint32_t kScanTile = kScanThreads * kScanItems;
-// Up to this many tiles every block of the scan sums the counts before its tile itself; beyond,
-// a launch of cell_sums is cheaper than those reads (240 counts per thread at 16 tiles).
-constexpr uint32_t kSelfSumTiles = 16;
+// Tables of up to this many tiles are scanned by one launch, whose blocks publish their sums: at 16 tiles 4.7 us
+// against 7.9 with every block adding up the counts before its tile (seeded ball of 20000, 4 steps 287 ->
+// 271 us).  Larger tables have a launch of cell_sums first: waiting for the sums of 256 tiles takes as long as
+// that launch (annulus of 2^18 particles 304 us against 298).
+constexpr uint32_t kPublishTiles = 64;
+// Polls of a tile's sum before a block adds the tile up itself, so that no block depends on another
+// one having started.
+constexpr int kSumPolls = 1024;
+constexpr uint32_t kSumReady = 0x80000000u;   // sums stay below 2^31
 
 __device__ __forceinline__ uint32_t wave_inclusive(uint32_t x, int lane) {
 #pragma unroll
@@ -56,13 +62,15 @@ __global__ __launch_bounds__(kScanThreads) void cell_sums(const uint4 *__restric
     s += v.x + v.y + v.z + v.w;
   }
   s = block_sum(s, lds);
-  if (threadIdx.x == 0) sums[blockIdx.x] = s;
+  if (threadIdx.x == 0) sums[blockIdx.x] = kSumReady | s;
 }
 
-// One tile per block; sums may be null (see kSelfSumTiles).
-__global__ __launch_bounds__(kScanThreads) void cell_scan(const uint4 *__restrict__ counts,
-                                                          const uint32_t *__restrict__ sums,
-                                                          uint32_t *__restrict__ cstart, uint32_t ncells, uint32_t n) {
+// One tile per block.  With publish a block stores its tile's sum for the others; it adds up the sums of
+// the tiles before it as they appear.  sums is all zero on entry, or filled by cell_sums; cell_place
+// clears it.
+__global__ __launch_bounds__(kScanThreads) void cell_scan(const uint4 *__restrict__ counts, uint32_t *__restrict__ sums,
+                                                          uint32_t *__restrict__ cstart, uint32_t ncells, uint32_t n,
+                                                          int publish) {
   __shared__ uint32_t lds[2][kScanThreads / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   // each thread's counts are consecutive
@@ -76,25 +84,31 @@ __global__ __launch_bounds__(kScanThreads) void cell_scan(const uint4 *__restric
     v[4 * q + 2] = u.z;
     v[4 * q + 3] = u.w;
   }
-  // everything before the tile
-  uint32_t before = 0;
-  if (sums) {
-    for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kScanThreads) before += sums[t];
-  } else {
-    const uint32_t end = blockIdx.x * (kScanTile / 4);
-#pragma unroll 4
-    for (uint32_t t = threadIdx.x; t < end; t += kScanThreads) {
-      const uint4 u = counts[t];
-      before += u.x + u.y + u.z + u.w;
-    }
-  }
-  before = block_sum(before, lds[0]);
   uint32_t own = 0;
 #pragma unroll
   for (int q = 0; q < kScanItems; ++q) own += v[q];
   const uint32_t incl = wave_inclusive(own, lane);
   if (lane == 63) lds[1][w] = incl;
   __syncthreads();
+  if (publish && threadIdx.x == 0) {
+    uint32_t t = kSumReady;
+#pragma unroll
+    for (int ww = 0; ww < kScanThreads / 64; ++ww) t += lds[1][ww];
+    __hip_atomic_store(&sums[blockIdx.x], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // everything before the tile
+  uint32_t before = 0;
+  for (uint32_t t = threadIdx.x; t < blockIdx.x; t += kScanThreads) {
+    uint32_t x = 0;
+    for (int k = 0; k < kSumPolls && x == 0; ++k) x = __hip_atomic_load(&sums[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (x == 0)
+      for (uint32_t q = 0; q < kScanTile / 4; ++q) {
+        const uint4 u = counts[(size_t)t * (kScanTile / 4) + q];
+        x += u.x + u.y + u.z + u.w;
+      }
+    before += x & ~kSumReady;
+  }
+  before = block_sum(before, lds[0]);
   uint32_t run = before + incl - own;
   for (int ww = 0; ww < w; ++ww) run += lds[1][ww];
   const uint32_t c0 = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
@@ -118,9 +132,11 @@ __global__ __launch_bounds__(kScanThreads) void cell_scan(const uint4 *__restric
 
 __global__ __launch_bounds__(256) void cell_place(const uint32_t *__restrict__ keys, const float4 *__restrict__ off,
                                                   const uint32_t *__restrict__ cstart, uint4 *__restrict__ counts,
-                                                  uint32_t nquads, uint32_t *__restrict__ slots, int n) {
+                                                  uint32_t nquads, uint32_t *__restrict__ sums, uint32_t nsums,
+                                                  uint32_t *__restrict__ slots, int n) {
   const uint32_t t = blockIdx.x * 256u + threadIdx.x, stride = gridDim.x * 256u;
   for (uint32_t q = t; q < nquads; q += stride) counts[q] = make_uint4(0u, 0u, 0u, 0u);
+  for (uint32_t q = t; q < nsums; q += stride) sums[q] = 0u;
   if (t >= (uint32_t)n) return;
   const uint32_t at = cstart[keys[t]] + __float_as_uint(off[t].w);
   if (at < (uint32_t)n) slots[at] = t;
@@ -195,7 +211,6 @@ hipError_t cell_order(const uint32_t *keys, const float4 *off, uint32_t *counts,
                       uint32_t *slots, int n, uint32_t ncells, bool keep, hipStream_t stream, LaunchHook *hook) {
   const uint32_t tiles = (uint32_t)cell_sum_words(ncells);
   const uint4 *c4 = reinterpret_cast<const uint4 *>(counts);
-  const bool self = tiles <= kSelfSumTiles;
   // One block for up to 4,096 particles with a table of one tile: 3.4 us in place of two launches of 2.5
   // and 1.8 us with a gap between them (a call of one step of 1,024 particles 94 -> 90.5 us).  With a table of 4
   // tiles the block takes 6.3 us and a step is 1 us slower than with the two launches.
@@ -207,12 +222,12 @@ hipError_t cell_order(const uint32_t *keys, const float4 *off, uint32_t *counts,
     return hipGetLastError();
   }
   if (hook) hook->begin("cell_scan");
-  if (!self) cell_sums<<<tiles, kScanThreads, 0, stream>>>(c4, sums);
-  cell_scan<<<tiles, kScanThreads, 0, stream>>>(c4, self ? nullptr : sums, cstart, ncells, (uint32_t)n);
+  if (tiles > kPublishTiles) cell_sums<<<tiles, kScanThreads, 0, stream>>>(c4, sums);
+  cell_scan<<<tiles, kScanThreads, 0, stream>>>(c4, sums, cstart, ncells, (uint32_t)n, tiles <= kPublishTiles ? 1 : 0);
   if (hook) hook->end();
   if (hook) hook->begin("cell_place");
   cell_place<<<(n + 255) / 256, 256, 0, stream>>>(keys, off, cstart, reinterpret_cast<uint4 *>(counts),
-                                                  keep ? 0u : tiles * (kScanTile / 4), slots, n);
+                                                  keep ? 0u : tiles * (kScanTile / 4), sums, tiles, slots, n);
   if (hook) hook->end();
   return hipGetLastError();
 }

@@ -52,3 +52,9 @@ def test_cell_table_and_order(dim, n, k):
 @pytest.mark.parametrize("dim,n,k", [(2, 1, 3), (2, 65, 3), (2, 1023, 3), (2, 4095, 3), (2, 4096, 3), (2, 4097, 3), (3, 4096, 2)])
 def test_one_block_order(dim, n, k):
     test_cell_table_and_order(dim, n, k)
+
+
+# tables of 32, 64 and 128 tiles: the last that one launch scans and the first with a launch for the sums
+@pytest.mark.parametrize("dim,n,k", [(2, 60000, 9), (2, 60000, 10), (2, 60000, 11)])
+def test_scan_of_many_tiles(dim, n, k):
+    test_cell_table_and_order(dim, n, k)
