@@ -198,8 +198,8 @@ __global__ __launch_bounds__(kBlock) void reorder_field_mixed(int im, int nblk2,
 // are copied into LDS once; the targets' row tables then index that copy.  A block whose union
 // has more than kTileRows rows or MPSPH_TILE_CAP particles reads its neighbours from global memory.
 // Staged particles per block.  Measured on the 2M-particle graded cube (2^6 cells, 8 lanes):
-// 768 particles (39 KB of LDS per block with the row table, 4 waves per SIMD) 2.38 ms per density
-// pass, 1536 (54 KB, 3 waves) 4.33 ms, against 1.43 ms for the pass that reads its neighbours
+// 768 particles (39 KB of LDS per block with the row table, 4 waves per SIMD) 1.82 ms per density
+// pass (1536, 54 KB and 3 waves, took 1.8 times as long), against 0.91 ms for the pass that reads its neighbours
 // through the caches at 8 waves per SIMD.
 #ifndef MPSPH_TILE_CAP
 #define MPSPH_TILE_CAP 768
@@ -2524,7 +2524,7 @@ __global__ __launch_bounds__(kBlock) void rbf_extremes(RbfGrid r, double *__rest
 
 // The same extremes on the device: an optimisation loop sets new coefficients before every gradient, and
 // the 262,144 nodes times 32 terms took the host 67 of the 70 ms of a gradient of 8192 particles
-// (a gradient of four steps then takes 1.4 ms).
+// (a gradient of four steps now takes 0.9 ms).
 // In: the field's grid and terms; out: 3 doubles per block.
 bool rbf_bounds_device(mpsph_ctx *ctx, const mpsph_params *p, double s0, double *bounds) {
   const RbfGrid r = rbf_grid(p);
@@ -2996,8 +2996,7 @@ int reconfigure(mpsph_ctx *ctx, const std::vector<Domain> &base, int kdelta, int
 // again from their checkpoints.  A recorded step writes its arrays in place, the last of a segment
 // the context's own, so that no copy is made and the exports refer to the last step recorded.
 // 262,144 particles, 4 steps, a checkpoint every 2, with copies of every array and all segments
-// recomputed 4.10 ms, this way and with the reverse kernels as they are 3.01; 8,192 particles 1.30 and
-// 0.93 ms.
+// recomputed 4.10 ms, this way and with five reverse kernels a step 3.01; 8,192 particles 1.30 and 0.93 ms.
 // ------------------------------------------------------------------------------------------
 
 struct GradPlan {

@@ -39,10 +39,10 @@ enum : int {
 
 // Geometry of the cell grid and of the meshing region, in cell units.  Positions are held as
 // an integer cell coordinate per axis plus a float offset in [0, 1).
-// Most sub-cells per cell along x in the cell key (log2).  Measured on the 2M-particle graded
-// cube at 2^6 cells: 0 / 1 / 2 / 3 / 4 bits give 4.49 / 4.03 / 3.84 / 3.76 / 3.79 ms per step
-// (4 lanes, before the row-table scan; with it and 8 lanes 4 bits gain only 0.3 % over 3); with
-// the neighbour loads one slot round ahead 3 / 4 / 5 bits give 2.516 / 2.496 / 2.510 ms.
+// Most sub-cells per cell along x in the cell key and in the search grid (log2).  Measured on the
+// 2M-particle graded cube at 2^6 cells: 1 / 2 / 3 / 4 bits of the search grid give 2.65 / 2.40 / 2.25 /
+// 2.16 ms per step; more than 4 entries per particle cost the scan of the table more than they save
+// (level set of 262,144 particles: 1 / 3 / 4 bits 284 / 285 / 298 us).
 #ifndef MPSPH_XSUB
 #define MPSPH_XSUB 4
 #endif
