@@ -2999,6 +2999,12 @@ int reconfigure(mpsph_ctx *ctx, const std::vector<Domain> &base, int kdelta, int
 // recomputed 4.10 ms, this way and with five reverse kernels a step 3.01; 8,192 particles 1.30 and 0.93 ms.
 // ------------------------------------------------------------------------------------------
 
+// Most particles of a 3D gradient whose loss and adjoint pair kernels take 16 lanes per particle: at 8 the
+// grid leaves SIMDs with a single wave (8,192 particles), whose loops are a chain of latencies.  Gradient of 4
+// steps at 8 / 16 lanes: 2,000 particles 647 / 582 us, 4,096 691 / 620, 8,192 615 / 569, 16,384 606 / 590, 24,000
+// 728 / 723, 65,536 995 / 1026.
+constexpr int kAdjSmall = 16384;
+
 struct GradPlan {
   int nck = 0, ckpt = 0;
   size_t ck0 = 0, ck_stride = 0, ck_key = 0, ck_off = 0, ck_ct = 0, ck_id = 0, ck_cell = 0;
@@ -3076,7 +3082,8 @@ struct GradRun {
   hipStream_t st;
   const Group *gr;
   int nb1;
-  int nbp;   // blocks of the adjoint pair kernels (MPSPH_ADJ_LANES lanes per particle)
+  int lanes; // of the loss and adjoint pair kernels: MPSPH_ADJ_LANES or MPSPH_ADJ_LANES_SMALL
+  int nbp;   // blocks of those kernels
   int nrow;  // rows of coefficient sums: waves of adj_field
   char *g;
   template <typename T>
@@ -3186,14 +3193,17 @@ int loss_backward(GradRun &R, double lam, int m) {
     return fail(ctx, MPSPH_E_DEVICE);
   launch_group<D>(ctx, w, *R.gr, kDtSlots, R.st, nullptr);
   const int nbp = R.nbp;
-  loss_density<D, MPSPH_ADJ_LANES><<<nbp, kBlock, 0, R.st>>>(dom, w.key, w.fix, w.jaux, w.cstart, R.at<float>(R.P.e),
+  const bool wide = R.lanes == MPSPH_ADJ_LANES_SMALL;
+  const auto density = wide ? loss_density<D, MPSPH_ADJ_LANES_SMALL> : loss_density<D, MPSPH_ADJ_LANES>;
+  const auto grad = wide ? loss_grad<D, MPSPH_ADJ_LANES_SMALL> : loss_grad<D, MPSPH_ADJ_LANES>;
+  density<<<nbp, kBlock, 0, R.st>>>(dom, w.key, w.fix, w.jaux, w.cstart, R.at<float>(R.P.e),
                                                        R.at<double>(R.P.pb));
   loss_value<<<1, kLossThreads, 0, R.st>>>(R.at<double>(R.P.pb), nbp, 1.0 / n, lam, R.at<double>(R.P.out));
   // every neighbour j whose support reaches k: r < kappa h_j <= kappa h_k / (1 - kappa L_h)
   const double Lh = dm.p.tau * dm.d.lip;
   const double kl = dm.p.kappa * Lh;
   const float reach = kl < 0.95 ? (float)(dm.p.kappa / (1.0 - kl) * (1.0 + 1e-4)) : 1e30f;
-  loss_grad<D, MPSPH_ADJ_LANES><<<nbp, kBlock, 0, R.st>>>(dom, w.key, w.fix, w.jaux, w.cstart, R.at<float>(R.P.e),
+  grad<<<nbp, kBlock, 0, R.st>>>(dom, w.key, w.fix, w.jaux, w.cstart, R.at<float>(R.P.e),
                                                     (float)(2.0 / n), (float)(lam / n), reach, R.at<float4>(R.P.xacc),
                                                     R.at<float>(R.P.sbar));
   field_backward<D>(R, R.tape(w, nullptr, nullptr), true);
@@ -3212,14 +3222,17 @@ int step_backward(GradRun &R, int m, bool last, int64_t t) {
   adj_drift<D><<<R.nb1, kBlock, 0, R.st>>>(dom, tv, R.at<float4>(R.P.xbar), R.at<float4>(R.P.xacc),
                                            R.at<float4>(R.P.abv), R.at<float4>(R.P.vtb), R.at<float>(R.P.dtc), R.minslots(),
                                            R.at<double>(R.P.pa));
-  adj_visc<D, MPSPH_ADJ_LANES><<<nbp, kBlock, 0, R.st>>>(dom, tv, R.at<float4>(R.P.abv), R.at<float4>(R.P.vtb),
+  const bool wide = R.lanes == MPSPH_ADJ_LANES_SMALL;
+  const auto visc = wide ? adj_visc<D, MPSPH_ADJ_LANES_SMALL> : adj_visc<D, MPSPH_ADJ_LANES>;
+  const auto force = wide ? adj_force<D, MPSPH_ADJ_LANES_SMALL> : adj_force<D, MPSPH_ADJ_LANES>;
+  visc<<<nbp, kBlock, 0, R.st>>>(dom, tv, R.at<float4>(R.P.abv), R.at<float4>(R.P.vtb),
                                                    R.at<float4>(R.P.xacc), R.at<float>(R.P.sbar),
                                                    R.at<float4>(R.P.fbar), R.at<float>(R.P.dtc), R.minslots(), R.argmin(),
                                                    R.at<double>(R.P.pb));
   adj_time_step<D><<<1, kTimeStepThreads, 0, R.st>>>(dom, tv, R.at<double>(R.P.pa), R.nb1, R.at<double>(R.P.pb), nbp,
                                                      (float)dt2_factor(&ctx->dom[0].p), R.argmin(), R.at<float>(R.P.sbar),
                                                      R.at<float4>(R.P.fbar));
-  adj_force<D, MPSPH_ADJ_LANES><<<nbp, kBlock, 0, R.st>>>(dom, tv, (float)t, R.at<float4>(R.P.fbar),
+  force<<<nbp, kBlock, 0, R.st>>>(dom, tv, (float)t, R.at<float4>(R.P.fbar),
                                                     R.at<float4>(R.P.xacc), R.at<float>(R.P.sbar));
   field_backward<D>(R, tv, false);
   HIP_OK(hipGetLastError());
@@ -3237,7 +3250,8 @@ int grad_run(mpsph_ctx *ctx, int nsteps, int ckpt, double lam, double *loss_out,
   R.st = ctx->stream;
   R.gr = &L.grp[D - 2];
   R.nb1 = (n + kBlock - 1) / kBlock;
-  R.nbp = (int)(((int64_t)n * MPSPH_ADJ_LANES + kBlock - 1) / kBlock);
+  R.lanes = D == 3 && n <= kAdjSmall ? MPSPH_ADJ_LANES_SMALL : MPSPH_ADJ_LANES;
+  R.nbp = (int)(((int64_t)n * R.lanes + kBlock - 1) / kBlock);
   R.nrow = (n + kWave - 1) / kWave;
   const int nseg = nsteps > 0 ? (nsteps + ckpt - 1) / ckpt : 0;
   const int seg_len = std::min(ckpt, std::max(nsteps, 1));

@@ -32,6 +32,10 @@ namespace mpsph {
 #ifndef MPSPH_ADJ_LANES
 #define MPSPH_ADJ_LANES 8
 #endif
+// The adjoint's pair kernels of small 3D gradients (kAdjSmall).
+#ifndef MPSPH_ADJ_LANES_SMALL
+#define MPSPH_ADJ_LANES_SMALL 16
+#endif
 
 // Separation of two particles from their fixed-point coordinates, in units of 2^-fb cells: the integer
 // difference is exact, in a periodic box of the minimum image (the coordinates' wrap divides the

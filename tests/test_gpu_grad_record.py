@@ -75,3 +75,29 @@ def test_steps_go_on_after_a_gradient(torch_cuda, steps, ckpt, debug):
     assert ga[0] == gb[0] and np.array_equal(ga[1], gb[1])
     A.close()
     B.close()
+
+
+def _tree_candidates(x, reach):
+    """The oracle's candidate pairs (all with |x_i - x_j| < max(reach_i, reach_j)) by a k-d tree instead of all n^2."""
+    import torch
+    from scipy.spatial import cKDTree
+    p = cKDTree(x).query_pairs(float(reach.max()) * (1.0 + 1e-9), output_type="ndarray")
+    i, j = np.concatenate([p[:, 0], p[:, 1]]), np.concatenate([p[:, 1], p[:, 0]])
+    keep = np.linalg.norm(x[i] - x[j], axis=1) < np.maximum(reach[i], reach[j]) * (1.0 + 1e-9)
+    o = np.lexsort((j[keep], i[keep]))
+    return torch.as_tensor(i[keep][o]), torch.as_tensor(j[keep][o])
+
+
+@pytest.mark.parametrize("n", [16384, 16385])   # the most particles at 16 lanes, the fewest at 8
+def test_lanes_of_the_adjoint_match_oracle(torch_cuda, monkeypatch, n):
+    spec, x, col, typ = _case(3, 6, n)
+    monkeypatch.setattr(G, "_candidates", _tree_candidates)
+    pr = G.Problem(spec, spec["s0"], col, typ)
+    L0, gc0, gx0, _, _, _ = G.run(pr, x.astype(np.float64), spec["rbf_coeff"], 1, 1.0, want_x0_grad=True)
+    R = _relaxer(torch_cuda, spec, x, col, typ)
+    L, gc, gx = R.grad(1, 1, 1.0, n_rbf=6, want_pos=True)
+    R.close()
+    gx = gx.cpu().numpy().astype(np.float64)
+    assert abs(L - L0) <= 1e-5 * abs(L0)
+    assert np.linalg.norm(gc - gc0) <= 2e-3 * np.linalg.norm(gc0)
+    assert np.linalg.norm(gx - gx0) <= 2e-3 * np.linalg.norm(gx0)
