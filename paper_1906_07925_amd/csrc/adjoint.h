@@ -226,7 +226,7 @@ __global__ __launch_bounds__(kBlock) void adj_drift(const DomDev *__restrict__ d
 // and Kbar's share of eta_k, s_k, X_k; then eta -> v~, s; a-bar = T1/2 v~bar; T1-bar partials.
 // fbar receives Pi a-bar, the adjoint of the force before the mapping but for the share of the
 // time step in the particle attaining T1 (adj_time_step).
-template <int D, int L>
+template <int D, int L, bool WIDE>
 __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const DomDev *__restrict__ dom, TapeView tp,
                                                    const float4 *__restrict__ abv, const float4 *__restrict__ vtb,
                                                    float4 *__restrict__ xacc, float *__restrict__ sbar,
@@ -260,41 +260,33 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
     {
     // the pair sum; the particle's own data is scoped to it (the epilogue reads it again), so
     // that the kernel fits its register budget without spilling
-    int ci[3];
-    unpack_key<D>(tp.wkey[i], g, ci);
-    const float4 pi = tp.wfix[i];
-    const FixedPos xi = fixed_of(pi);
-    const OwnRow own = own_row<D>(ci, xi, g);
-    const float unit = g.funit;
+    const PairPos<D, false, WIDE> pos(g, 0u, i, tp.wkey, tp.wfix);
+    const float unit = pos.unit;
     const int ti = aux_type(tp.wjaux[i]);
-    const float hi = pi.w;
+    const float hi = pos.h;
     const float h2di = pow2d<D>(hi);
     const float4 *gd = gdat[threadIdx.x / L];
     const float ei = gd[0].w;
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
     const float kh = 0.5f * sp.kappa;
     if (hdt * ei > 0.f) {
-      const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n);
       const BufRes racc = buf_res(tp.acc, 16, (uint32_t)g.n), rabv = buf_res(abv, 16, (uint32_t)g.n);
       struct Nb {
-        float4 p, a4, ab;   // ab.w: the neighbour's type
+        typename PairPos<D, false, WIDE>::Nb p;
+        float4 a4, ab;   // ab.w: the neighbour's type
       };
       // the neighbour's loads (bounds-checked: slots past the arrays read zeros) are issued one
       // slot round ahead of the pair's arithmetic
       const auto fetch = [&](uint32_t jr) {
-        return Nb{buf_f4(rpos, jr), buf_f4(racc, jr), buf_f4(rabv, jr)};
+        return Nb{pos.fetch(jr), buf_f4(racc, jr), buf_f4(rabv, jr)};
       };
       const auto use = [&](const Nb &nb) {
-        const float4 pj = nb.p, aj4 = nb.a4, abj = nb.ab;
-        // separations in fixed-point units
-        const float dx = fixed_diff(xi.x, pj.x);
-        const float dy = fixed_diff(xi.y, pj.y);
-        float dz = 0.f;
+        const float4 pj = nb.p.p, aj4 = nb.a4, abj = nb.ab;
+        // separations in units of pos.unit cells
+        float dx, dy, dz = 0.f;
+        pos.sep(nb.p, dx, dy, dz);
         float r2 = dx * dx + dy * dy;
-        if constexpr (D == 3) {
-          dz = fixed_diff(xi.z, pj.z);
-          r2 += dz * dz;
-        }
+        if constexpr (D == 3) r2 += dz * dz;
         const float rinv = fast_rsq(r2);
         const float r = r2 * rinv * unit;   // NaN at zero separation
         const float hs = hi + pj.w;
@@ -324,7 +316,7 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
         xb[1] = fmaf(cx, dy, xb[1]);
         if constexpr (D == 3) xb[2] = fmaf(cx, dz, xb[2]);
       };
-      scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own,
+      scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), pos.row,
                                                   rs, g, 0u, tp.cstart, pair_body<true>(fetch, use));
     }
     }
@@ -438,7 +430,7 @@ __global__ __launch_bounds__(kTimeStepThreads) void adj_time_step(const DomDev *
 // and w = B (P_k + P_j) g(r, H):
 //   X-bar_k += w W + B (P_k + P_j) dg/dr (u.W) u / r
 //   s-bar_k += (u.W) B [2d p0c s_k^(2d-1) g + (P_k + P_j) dg/dH tau / 2]
-template <int D, int L>
+template <int D, int L, bool WIDE>
 __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ dom, TapeView tp, float tstep,
                                                     const float4 *__restrict__ fbar, float4 *__restrict__ xacc,
                                                     float *__restrict__ sbar) {
@@ -449,15 +441,11 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   const int i = local / L, sub = local % L;
   __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   if (i >= dom->n) return;
-  int ci[3];
-  unpack_key<D>(tp.wkey[i], g, ci);
-  const float4 pi = tp.wfix[i];
-  const FixedPos xi = fixed_of(pi);
-  const OwnRow own = own_row<D>(ci, xi, g);
-  const float unit = g.funit;
+  const PairPos<D, false, WIDE> pos(g, 0u, i, tp.wkey, tp.wfix);
+  const float unit = pos.unit;
   const uint32_t ai = tp.wjaux[i];
   const int ti = aux_type(ai);
-  const float hi = pi.w;
+  const float hi = pos.h;
   const float h2di = pow2d<D>(hi);
   const float dh2di = (2.f * (float)D) * h2di / hi;
   const float4 fi = fbar[i];
@@ -465,26 +453,22 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
   const float kh = 0.5f * sp.kappa, unit3 = -3.f * unit;
   const float opb = 1.f + sigma_of(sp, tstep);   // surface tension of the step (Eq. 24-25)
   float xb[3] = {0.f, 0.f, 0.f}, sb = 0.f;
-  const BufRes rpos = buf_res(tp.wfix, 16, (uint32_t)g.n);
   const BufRes rfb = buf_res(fbar, 16, (uint32_t)g.n);
   struct Nb {
-    float4 p, f;   // f.w: the neighbour's type and colour
+    typename PairPos<D, false, WIDE>::Nb p;
+    float4 f;   // f.w: the neighbour's type and colour
   };
   // the neighbour's loads (bounds-checked: slots past the arrays read zeros) are issued one slot
   // round ahead of the pair's arithmetic
-  const auto fetch = [&](uint32_t jr) { return Nb{buf_f4(rpos, jr), buf_f4(rfb, jr)}; };
+  const auto fetch = [&](uint32_t jr) { return Nb{pos.fetch(jr), buf_f4(rfb, jr)}; };
   const auto use = [&](const Nb &nb) {
-    const float4 pj = nb.p, fj = nb.f;
+    const float4 pj = nb.p.p, fj = nb.f;
     const uint32_t aj = __float_as_uint(fj.w);
-    // separations in fixed-point units
-    const float dx = fixed_diff(xi.x, pj.x);
-    const float dy = fixed_diff(xi.y, pj.y);
-    float dz = 0.f;
+    // separations in units of pos.unit cells
+    float dx, dy, dz = 0.f;
+    pos.sep(nb.p, dx, dy, dz);
     float r2 = dx * dx + dy * dy;
-    if constexpr (D == 3) {
-      dz = fixed_diff(xi.z, pj.z);
-      r2 += dz * dz;
-    }
+    if constexpr (D == 3) r2 += dz * dz;
     const float rinv = fast_rsq(r2);
     const float r = r2 * rinv * unit;   // NaN at zero separation
     const float hs = hi + pj.w;
@@ -503,7 +487,7 @@ __global__ __launch_bounds__(kBlock) void adj_force(const DomDev *__restrict__ d
     if constexpr (D == 3) xb[2] = fmaf(cw, wf[2], fmaf(cr, dz, xb[2]));
     sb = fmaf(uw, fmaf(dh2di, bw * uh, x * fmaf(-(float)(D + 5), u, 3.f)), sb);
   };
-  scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
+  scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), pos.row, rs, g,
                                               0u, tp.cstart, pair_body<true>(fetch, use));
 #pragma unroll
   for (int a = 0; a < 3; ++a) xb[a] = group_sum<L>(xb[a]);
@@ -616,7 +600,7 @@ __global__ __launch_bounds__(kCoeffSumThreads) void adj_sum_coeff(const double *
 //   e_k = alpha tau^-d sum_{r < kappa h_k} w(r / h_k) - 1 (self included), and the ordered
 //   interface sum sum_{C_j != C_k, r < kappa H} w(r / H); block partials of sum e^2 (slot 0)
 //   and of the interface sum (slot 1).
-template <int D, int L>
+template <int D, int L, bool WIDE>
 __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict__ dom, const uint32_t *__restrict__ wkey,
                                                        const float4 *__restrict__ wfix, const uint32_t *__restrict__ wjaux,
                                                        const uint32_t *__restrict__ cstart, float *__restrict__ e_out,
@@ -630,34 +614,30 @@ __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict_
   double part[2] = {0.0, 0.0};
   const int ops[2] = {0, 0};
   if (i < dom->n) {
-    int ci[3];
-    unpack_key<D>(wkey[i], g, ci);
-    const float4 pi = wfix[i];
-    const FixedPos xi = fixed_of(pi);
-    const OwnRow own = own_row<D>(ci, xi, g);
-    const float unit = g.funit;
+    const PairPos<D, false, WIDE> pos(g, 0u, i, wkey, wfix);
+    const float unit = pos.unit;
     const uint32_t ai = wjaux[i];
-    const float hi = pi.w, ihi = fast_rcp(hi);
+    const float hi = pos.h, ihi = fast_rcp(hi);
     const float rci = sp.kappa * hi, rci2 = rci * rci;
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
     const float kh = 0.5f * sp.kappa;
     float ws = 0.f, wi = 0.f;
-    const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
+    const BufRes raux = buf_res(wjaux, 4, (uint32_t)g.n);
     struct Nb {
-      float4 p;
+      typename PairPos<D, false, WIDE>::Nb p;
       uint32_t a;
     };
-    const auto fetch = [&](uint32_t jr) { return Nb{buf_f4(rpos, jr), buf_u32(raux, jr)}; };
+    const auto fetch = [&](uint32_t jr) { return Nb{pos.fetch(jr), buf_u32(raux, jr)}; };
     const auto use = [&](const Nb &nb) {
-      const float4 pj = nb.p;
+      const float4 pj = nb.p.p;
       const uint32_t aj = nb.a;
-      const float dx = fixed_diff(xi.x, pj.x) * unit;
-      const float dy = fixed_diff(xi.y, pj.y) * unit;
+      float dx, dy, dz = 0.f;
+      pos.sep(nb.p, dx, dy, dz);
+      dx *= unit;
+      dy *= unit;
+      dz *= unit;
       float r2 = dx * dx + dy * dy;
-      if constexpr (D == 3) {
-        const float dz = fixed_diff(xi.z, pj.z) * unit;
-        r2 += dz * dz;
-      }
+      if constexpr (D == 3) r2 += dz * dz;
       const float r = sqrtf(r2);
       if (r2 < rci2) {
         const float q = r * ihi, u = fmaf(-0.5f, q, 1.f);
@@ -669,7 +649,7 @@ __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict_
         wi += u * u * u * u * fmaf(2.f, q, 1.f);
       }
     };
-    scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
+    scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), pos.row, rs, g,
                                                 0u, cstart, pair_body<true>(fetch, use));
     ws = group_sum<L>(ws);
     wi = group_sum<L>(wi);
@@ -689,7 +669,7 @@ __global__ __launch_bounds__(kBlock) void loss_density(const DomDev *__restrict_
 //   s-bar_k = tau sum_j [ebar_k A 5 q_k^2 u_k^3 / h_k + cl [C_j != C_k] 2.5 q^2 u^3 / H]
 // (u_k = 1 - r / (2 h_k) inside the support of particle k, etc.).  The search radius covers
 // every j whose support reaches k: r < kappa h_j <= kappa h_k / (1 - kappa L_h).
-template <int D, int L>
+template <int D, int L, bool WIDE>
 __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ dom, const uint32_t *__restrict__ wkey,
                                                     const float4 *__restrict__ wfix, const uint32_t *__restrict__ wjaux,
                                                     const uint32_t *__restrict__ cstart, const float *__restrict__ e,
@@ -702,37 +682,32 @@ __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ d
   const int i = local / L, sub = local % L;
   __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   if (i >= dom->n) return;
-  int ci[3];
-  unpack_key<D>(wkey[i], g, ci);
-  const float4 pi = wfix[i];
-  const FixedPos xi = fixed_of(pi);
-  const OwnRow own = own_row<D>(ci, xi, g);
-  const float unit = g.funit;
+  const PairPos<D, false, WIDE> pos(g, 0u, i, wkey, wfix);
+  const float unit = pos.unit;
   const uint32_t ai = wjaux[i];
-  const float hi = pi.w, ihi = fast_rcp(hi);
+  const float hi = pos.h, ihi = fast_rcp(hi);
   const float A = sp.alpha * (D == 3 ? sp.inv_tau * sp.inv_tau * sp.inv_tau : sp.inv_tau * sp.inv_tau);
   const float ebi = ebar_scale * e[i];
   const float rs = fminf(reach_fac * hi, sp.kappa * sp.hmax) * 1.0001f;
   const float kh = 0.5f * sp.kappa;
   float xb[3] = {0.f, 0.f, 0.f}, sb = 0.f;
-  const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
+  const BufRes raux = buf_res(wjaux, 4, (uint32_t)g.n);
   const BufRes re = buf_res(e, 4, (uint32_t)g.n);
   struct Nb {
-    float4 p;
+    typename PairPos<D, false, WIDE>::Nb p;
     uint32_t a, e;
   };
-  const auto fetch = [&](uint32_t jr) { return Nb{buf_f4(rpos, jr), buf_u32(raux, jr), buf_u32(re, jr)}; };
+  const auto fetch = [&](uint32_t jr) { return Nb{pos.fetch(jr), buf_u32(raux, jr), buf_u32(re, jr)}; };
   const auto use = [&](const Nb &nb) {
-    const float4 pj = nb.p;
+    const float4 pj = nb.p.p;
     const uint32_t aj = nb.a;
-    const float dx = fixed_diff(xi.x, pj.x) * unit;
-    const float dy = fixed_diff(xi.y, pj.y) * unit;
-    float dz = 0.f;
+    float dx, dy, dz = 0.f;
+    pos.sep(nb.p, dx, dy, dz);
+    dx *= unit;
+    dy *= unit;
+    dz *= unit;
     float r2 = dx * dx + dy * dy;
-    if constexpr (D == 3) {
-      dz = fixed_diff(xi.z, pj.z) * unit;
-      r2 += dz * dz;
-    }
+    if constexpr (D == 3) r2 += dz * dz;
     if (!(r2 > 0.f)) return;
     const float r = sqrtf(r2);
     float cx = 0.f;
@@ -758,7 +733,7 @@ __global__ __launch_bounds__(kBlock) void loss_grad(const DomDev *__restrict__ d
     xb[1] = fmaf(cx, dy, xb[1]);
     if constexpr (D == 3) xb[2] = fmaf(cx, dz, xb[2]);
   };
-  scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g,
+  scan_group_table<D, L, row_table_rows<L>()>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), pos.row, rs, g,
                                               0u, cstart, pair_body<true>(fetch, use));
 #pragma unroll
   for (int a = 0; a < 3; ++a) xb[a] = group_sum<L>(xb[a]);

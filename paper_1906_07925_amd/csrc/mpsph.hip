@@ -363,8 +363,10 @@ __device__ bool stage_tile(TileLds *T, bool active, int sub, const OwnRow &own, 
       const double *__restrict__ metrics, double *__restrict__ partials
 #define MPSPH_PASS1_ARGS \
   doms, ndom, stepctr, wkey, wpos, wfix, wjaux, cstart, acc, rho_out, nn_out, aabs_out, dtslots, metrics, partials
-template <int D, int L, bool PER, bool DBG, bool TILE, bool PIPE, bool K2>
+// WIDE: a wide domain (GridDev::wide).
+template <int D, int L, bool PER, bool DBG, bool TILE, bool PIPE, bool K2, bool WIDE = false>
 __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileLds *tile, MPSPH_PASS1_PARAMS) {
+  static_assert(!(TILE && WIDE), "the staged variant copies fixed-point coordinates");
   const int d = domain_of_block(doms, ndom, lb);
   const GridDev g = doms[d].g;
   const StepDev sp = doms[d].sp;
@@ -401,37 +403,32 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
     }
   }
   if (active) {
-    int ci[3];
-    unpack_key<D>(wkey[i] - cellbase, g, ci);
-    const float4 pi = wfix[i];
-    const FixedPos xi = fixed_of(pi);
-    const OwnRow own = own_row<D>(ci, xi, g);
+    const PairPos<D, PER, WIDE> pos(g, cellbase, i, wkey, wfix);
     const uint32_t ai = wjaux[i];
     const int ti = aux_type(ai);
-    const float hi = pi.w;
+    const float hi = pos.h;
     // P = p0 / rho_t^2 = p0 tau^-2d h^2d and -dW/dr / r = 5 alpha 2^(d+2) (h_i + h_j)^-(d+2) (1 - q/2)^3
     // for the pair's h_ij: the pair sum takes h^2d and (h_i + h_j)^-(d+2), and the factors
-    // common to every pair are applied once to the group's total.  Separations are in fixed-point
-    // units, the distance is converted to cells
+    // common to every pair are applied once to the group's total.  Separations are in units of
+    // pos.unit cells, the distance is converted to cells
     const float Phi = powd<D>(hi * hi);
-    const float fscale = sp.p0c * powd<D>(sp.inv_tau * sp.inv_tau) * (5.f * sp.alpha) * (D == 3 ? 32.f : 16.f) * g.funit;
+    const float fscale = sp.p0c * powd<D>(sp.inv_tau * sp.inv_tau) * (5.f * sp.alpha) * (D == 3 ? 32.f : 16.f) * pos.unit;
     const float mhh = -0.5f * fast_rcp(hi);
     const float rci = sp.kappa * hi;
     const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
     const float kh = 0.5f * sp.kappa;
-    const float unit = g.funit;
+    const float unit = pos.unit;
     const float opb = 1.f + sigma;
     float wsum = 0.f, ax = 0.f, ay = 0.f, az = 0.f, A = 0.f;
     uint32_t npair = 0, nifc = 0, nn = kInfBits;
-    const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
-    const auto pair = [&](const float4 pj, const uint32_t aj) {
-      const float dx = fixed_diff(xi.x, pj.x), dy = fixed_diff(xi.y, pj.y);
+    const BufRes raux = buf_res(wjaux, 4, (uint32_t)g.n);
+    using NbPos = typename PairPos<D, PER, WIDE>::Nb;
+    const auto pair = [&](const NbPos &nj, const uint32_t aj) {
+      const float4 pj = nj.p;
+      float dx, dy, dz = 0.f;
+      pos.sep(nj, dx, dy, dz);
       float r2 = dx * dx + dy * dy;
-      float dz = 0.f;
-      if constexpr (D == 3) {
-        dz = fixed_diff(xi.z, pj.z);
-        r2 += dz * dz;
-      }
+      if constexpr (D == 3) r2 += dz * dz;
       const float r = fast_sqrt(r2) * unit;
       const float hs = hi + pj.w;                   // 2 h_ij
       const bool inter = r < (K2 ? hs : kh * hs);   // kappa h_ij
@@ -474,27 +471,27 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
       if constexpr (DBG) A = fmaf(s, r, A);        // sum of |pair terms| (debug export only)
     };
     struct Nb {
-      float4 p;
+      NbPos p;
       uint32_t a;
     };
-    const auto body = pair_body<PIPE>([&](uint32_t j) { return Nb{buf_f4(rpos, j), buf_u32(raux, j)}; },
+    const auto body = pair_body<PIPE>([&](uint32_t j) { return Nb{pos.fetch(j), buf_u32(raux, j)}; },
                                       [&](const Nb &nb) { pair(nb.p, nb.a); });
     const uint32_t sbase = doms[d].sbase;
     uint32_t ncand;
     if constexpr (TILE) {
       if (staged) {
         // slots index the LDS copy
-        const auto tbody = [&](uint32_t j) { pair(tile->pos[j], tile->aux[j]); };
+        const auto tbody = [&](uint32_t j) { pair(NbPos{tile->pos[j]}, tile->aux[j]); };
         ncand = scan_group_table<D, L, row_table_rows<L>(), PER>(self_t, sub, rowtab + threadIdx.x / L,
-                                                                 row_table_stride<L>(), own, rs, g, sbase, cstart, tbody,
+                                                                 row_table_stride<L>(), pos.row, rs, g, sbase, cstart, tbody,
                                                                  TileRemap{tile, tw});
       } else {
         ncand = scan_group_table<D, L, row_table_rows<L>(), PER>(
-            (uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g, sbase, cstart, body);
+            (uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), pos.row, rs, g, sbase, cstart, body);
       }
     } else {
       ncand = scan_group_table<D, L, row_table_rows<L>(), PER>(
-          (uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), own, rs, g, sbase, cstart, body);
+          (uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(), pos.row, rs, g, sbase, cstart, body);
     }
     gw = group_sum<L>(wsum);
     gx = fscale * group_sum<L>(ax);
@@ -596,11 +593,20 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
   });
 }
 
-// The pass over the logical blocks b0 + [0, gridDim.x) (one dimension group).
-template <int D, int L, bool PER, bool DBG, bool K2>
+// Whether logical block lb belongs to a wide domain (WIDE) or to a narrow one; the same in every thread of the block.
+template <bool WIDE>
+__device__ __forceinline__ bool block_of_kind(const DomDev *doms, int ndom, int lb) {
+  return (doms[domain_of_block(doms, ndom, lb)].g.wide != 0) == WIDE;
+}
+
+// The pass over the logical blocks b0 + [0, gridDim.x) (one dimension group), of its wide domains (WIDE) or of the
+// narrow ones.  In 3D the wide pass holds one round of loads: with a second one it spilled 7 to 21 registers.
+template <int D, int L, bool PER, bool DBG, bool K2, bool WIDE>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_density_force(int b0, MPSPH_PASS1_PARAMS) {
   __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  density_force_block<D, L, PER, DBG, false, true, K2>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, nullptr, MPSPH_PASS1_ARGS);
+  const int lb = b0 + xcd_block(blockIdx.x, gridDim.x);
+  if (!block_of_kind<WIDE>(doms, ndom, lb)) return;
+  density_force_block<D, L, PER, DBG, false, !WIDE || D == 2, K2, WIDE>(lb, rowtab, nullptr, MPSPH_PASS1_ARGS);
 }
 
 // The staged copy limits a CU to 4 blocks (4 waves per SIMD), which the register budget follows.
@@ -803,8 +809,8 @@ __device__ __forceinline__ void close_step(const StepEnd &fin, const DomDev &dd,
 #define MPSPH_PASS2_ARGS \
   doms, ndom, wkey, wpos, wfix, wjaux, wid, cstart, acc, dtslots, skey, soff, sct, sid, cell, counts, at_out, v_out, partials, \
       fin
-// One logical block lb of the pass; PIPE as for density_force_block, END: the pass closes the step.
-template <int D, int L, bool PER, bool PIPE, bool END = false, bool K2 = false>
+// One logical block lb of the pass; PIPE and WIDE as for density_force_block, END: the pass closes the step.
+template <int D, int L, bool PER, bool PIPE, bool END = false, bool K2 = false, bool WIDE = false>
 __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, MPSPH_PASS2_PARAMS) {
   const int d = domain_of_block(doms, ndom, lb);
   const GridDev g = doms[d].g;
@@ -824,13 +830,9 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
     float bx = 0.f, by = 0.f, bz = 0.f;
     {
       // the pair sum; the particle's own data is scoped to it (the epilogue reads it again)
-      int ci[3];
-      unpack_key<D>(wkey[i] - cellbase, g, ci);
-      const float4 pi = wfix[i];
-      const FixedPos xi = fixed_of(pi);
-      const OwnRow own = own_row<D>(ci, xi, g);
+      const PairPos<D, PER, WIDE> pos(g, cellbase, i, wkey, wfix);
       const int ti = aux_type(wjaux[i]);
-      const float hi = pi.w;
+      const float hi = pos.h;
       // 1 / rho_t^2 = tau^-2d h^2d, v = (dt1/2) a, eta = (dt1/2) e and dW/dr / r =
       // -5 alpha 2^(d+2) (h_i + h_j)^-(d+2) (1 - q/2)^3 for the pair's h_ij: the pair sum takes h^2d,
       // a, e and (h_i + h_j)^-(d+2), and the factors common to every pair are applied once to the
@@ -840,27 +842,25 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
       const float ei = (0.5f * dt1) * acci.w;
       const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
       const float kh = 0.5f * sp.kappa;
-      const float unit = g.funit;
+      const float unit = pos.unit;
       // with eta_i = 0 every harmonic-mean viscosity of particle i vanishes: nothing to sum
       if (ei > 0.f) {
-        const BufRes rpos = buf_res(wfix, 16, (uint32_t)g.n), raux = buf_res(wjaux, 4, (uint32_t)g.n);
-        const BufRes racc = buf_res(acc, 16, (uint32_t)g.n);
+        const BufRes raux = buf_res(wjaux, 4, (uint32_t)g.n), racc = buf_res(acc, 16, (uint32_t)g.n);
         struct Nb {
-          float4 p, acc;
+          typename PairPos<D, PER, WIDE>::Nb p;
+          float4 acc;
           uint32_t a;
         };
         // a normal particle feels every type: only feature particles load their neighbours' flags
         const auto fetch = [&](uint32_t j) {
-          return Nb{buf_f4(rpos, j), buf_f4(racc, j), ti > 0 ? buf_u32(raux, j) : 0xFFFFFFFFu};
+          return Nb{pos.fetch(j), buf_f4(racc, j), ti > 0 ? buf_u32(raux, j) : 0xFFFFFFFFu};
         };
         const auto use = [&](const Nb &nb) {
-          const float4 pj = nb.p, accj = nb.acc;
-          const float dx = fixed_diff(xi.x, pj.x), dy = fixed_diff(xi.y, pj.y);
+          const float4 pj = nb.p.p, accj = nb.acc;
+          float dx, dy, dz = 0.f;
+          pos.sep(nb.p, dx, dy, dz);
           float r2 = dx * dx + dy * dy;
-          if constexpr (D == 3) {
-            const float dz = fixed_diff(xi.z, pj.z);
-            r2 += dz * dz;
-          }
+          if constexpr (D == 3) r2 += dz * dz;
           const float r = fast_sqrt(r2) * unit;
           const float hs = hi + pj.w;   // 2 h_ij
           // the particle itself and coincident particles have r = 0 exactly
@@ -875,7 +875,7 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
           if constexpr (D == 3) bz = fmaf(s, acci.z - accj.z, bz);
         };
         scan_group_table<D, L, row_table_rows<L>(), PER, false>((uint32_t)i, sub, rowtab + threadIdx.x / L,
-                                                                 row_table_stride<L>(), own, rs, g, doms[d].sbase,
+                                                                 row_table_stride<L>(), pos.row, rs, g, doms[d].sbase,
                                                                  cstart, pair_body<PIPE>(fetch, use));
         // the factor e_i of every pair term
         bx *= acci.w;
@@ -1084,10 +1084,12 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
   }
 }
 
-template <int D, int L, bool PER, bool END, bool K2>
+template <int D, int L, bool PER, bool END, bool K2, bool WIDE>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_integrate(int b0, MPSPH_PASS2_PARAMS) {
   __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  viscous_integrate_block<D, L, PER, true, END, K2>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, MPSPH_PASS2_ARGS);
+  const int lb = b0 + xcd_block(blockIdx.x, gridDim.x);
+  if (!block_of_kind<WIDE>(doms, ndom, lb)) return;
+  viscous_integrate_block<D, L, PER, !WIDE || D == 2, END, K2, WIDE>(lb, rowtab, MPSPH_PASS2_ARGS);
 }
 
 // Row-table entries of a launch that serves 2D blocks at L lanes and 3D blocks at L3.
@@ -1195,7 +1197,7 @@ __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_inte
 // last step's start-of-step state, enumerated with the same candidate scan and predicate as the
 // pair passes (two lanes per particle).  Pairs go to (out_i, out_j) as load indices while the
 // running count stays below cap; *count receives the total.
-template <int D, bool PER>
+template <int D, bool PER, bool WIDE>
 __global__ __launch_bounds__(kBlock) void dump_pairs(const DomDev *__restrict__ doms, int ndom, int i0, int i1,
                                                      const uint32_t *__restrict__ wkey, const float4 *__restrict__ wfix,
                                                      const uint32_t *__restrict__ wid,
@@ -1208,26 +1210,22 @@ __global__ __launch_bounds__(kBlock) void dump_pairs(const DomDev *__restrict__ 
   if (i >= i1) return;   // both lanes of a particle leave together
   const DomDev &dd = doms[domain_of(doms, ndom, i)];
   const GridDev &g = dd.g;
+  if ((g.wide != 0) != WIDE) return;
   const StepDev &sp = dd.sp;
-  int ci[3];
-  unpack_key<D>(wkey[i] - dd.cellbase, g, ci);
-  const float4 pi = wfix[i];
-  const FixedPos xi = fixed_of(pi);
-  const float hi = pi.w;
+  const PairPos<D, PER, WIDE> pos(g, dd.cellbase, i, wkey, wfix);
+  const float hi = pos.h;
   const float rs = fminf(sp.search_fac * hi, sp.kappa * 0.5f * (hi + sp.hmax)) * 1.0001f;
   const float kh = 0.5f * sp.kappa;
   const uint32_t idi = wid[i];
   __shared__ uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
   scan_group_table<D, L, row_table_rows<L>(), PER>((uint32_t)i, sub, rowtab + threadIdx.x / L, row_table_stride<L>(),
-                                                   own_row<D>(ci, xi, g), rs, g, dd.sbase, cstart, [&](uint32_t j) {
-    const float4 pj = wfix[j];
-    const float dx = fixed_diff(xi.x, pj.x), dy = fixed_diff(xi.y, pj.y);
+                                                   pos.row, rs, g, dd.sbase, cstart, [&](uint32_t j) {
+    const auto nj = pos.fetch(j);
+    float dx, dy, dz = 0.f;
+    pos.sep(nj, dx, dy, dz);
     float r2 = dx * dx + dy * dy;
-    if constexpr (D == 3) {
-      const float dz = fixed_diff(xi.z, pj.z);
-      r2 += dz * dz;
-    }
-    if (!(fast_sqrt(r2) * g.funit < kh * (hi + pj.w))) return;
+    if constexpr (D == 3) r2 += dz * dz;
+    if (!(fast_sqrt(r2) * pos.unit < kh * (hi + nj.p.w))) return;
     const unsigned long long k = atomicAdd(count, 1ull);
     if (k < cap) {
       out_i[k] = idi;
@@ -1336,6 +1334,8 @@ struct Derived {
   int dim, k, gmax;
   int xe;                  // x sub-cells per cell in the cell key: 2^xe
   int rb, xb;              // search grid: rows of 2^rb cells, 2^xb x sub-cells per cell
+  int fb;                  // bits of the fixed-point coordinates' fraction
+  bool wide;               // separations may leave the range of those coordinates (GridDev::wide)
   double L, cs, inv_cs, lo[3], xhi[3];
   double smin, smax, lip;  // spacing bounds (domain units), Lipschitz constant of s
   double search_fac;
@@ -1963,13 +1963,22 @@ void fit_search(int dim, int64_t n, Derived *d) {
   while (d->xb < MPSPH_XSUB && bits() < 26 && std::pow(2.0, bits() + 1) <= 4.0 * (double)std::max<int64_t>(n, 1)) ++d->xb;
 }
 
-// Bits of the fixed-point coordinates' fraction: any separation of candidates stays below 2^31 units; in a
-// periodic box the coordinates' wrap divides the period.
-int fixed_fraction(const mpsph_params *p, const Derived &d) {
+// Cells that the separation of two candidates stays below: the reach of the pair loops (the largest cut-off of the
+// box, a search row and a sub-cell), at most the grid, at most half of it in a periodic box (minimum image).
+double separation_bound(const mpsph_params *p, const Derived &d) {
   const double reach = p->kappa * p->tau * d.smax * d.inv_cs * 1.001 + std::pow(2.0, std::max(d.rb, 0)) + 1.0;
-  int fb = std::min(27, 31 - (int)std::ceil(std::log2(reach)));
-  if (p->geometry == MPSPH_PERIODIC) fb = std::max(fb, 32 - d.k);
-  return std::max(fb, 0);
+  return std::min(reach, std::pow(2.0, p->geometry == MPSPH_PERIODIC ? d.k - 1 : d.k));
+}
+// Whether separations may reach 2^31 units of the fixed-point coordinates, whose difference would then be taken
+// for a smaller one.
+bool wide_field(const mpsph_params *p, const Derived &d) { return separation_bound(p, d) > std::ldexp(1.0, 31 - d.fb); }
+// Bits of the fixed-point coordinates' fraction: 27, or 26 for separations of 16 to 32 cells; more in periodic boxes of
+// few cells, whose period the coordinates' wrap has to divide.  Wider domains load cells as well instead of
+// taking fewer bits: against 64-bit separations of particles 0.6 cells apart fixed-point ones are off by 5.5e-8 at 27
+// and 26 bits, 5.8e-8 at 25, 7.6e-8 at 24 and 1.3e-7 at 23; (cell, offset) pairs of FP32 offsets by 5.8e-8.
+int fixed_fraction(const mpsph_params *p, const Derived &d) {
+  const int fb = separation_bound(p, d) <= 16.0 ? 27 : 26;
+  return p->geometry == MPSPH_PERIODIC ? std::max(fb, 32 - d.k) : fb;
 }
 
 struct EventHook : LaunchHook {
@@ -2145,14 +2154,17 @@ struct Group {
   int D = 0;
   bool periodic = false;  // some domain of the group is a periodic box
   bool kappa2 = true;     // every domain's cut-off is the kernel's support, kappa = 2
+  int nwide = 0;          // wide domains (Derived::wide)
   int d0 = 0, nd = 0;   // internal domains
   int i0 = 0, i1 = 0;   // internal particles
   int b0 = 0, nb = 0;   // pair-kernel blocks
 };
 
-// Cells of the domain's two tables, for its cell size and search rows (d.rb).
-void count_cells_of(Domain *dm) {
+// Cells of the domain's two tables and the coordinates of its pair loops, for its cell size and search rows (d.rb).
+void fit_grid(Domain *dm) {
   fit_search(dm->p.dim, dm->n, &dm->d);
+  dm->d.fb = fixed_fraction(&dm->p, dm->d);
+  dm->d.wide = wide_field(&dm->p, dm->d);
   dm->ncells = (uint32_t)1u << (dm->p.dim * dm->d.k + dm->d.xe);
   dm->scells = (uint32_t)1u << (dm->d.k + dm->d.xb + (dm->p.dim - 1) * (dm->d.k - dm->d.rb));
 }
@@ -2190,7 +2202,7 @@ int make_domain(const mpsph_params *params, int64_t n, Domain *dm) {
   int rc = derive(&dm->p, n, s0, &dm->d);
   if (rc) return rc;
   dm->d.rb = search_rows_rule(&dm->p, s0, dm->d);
-  count_cells_of(dm);
+  fit_grid(dm);
   return MPSPH_OK;
 }
 
@@ -2278,6 +2290,7 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     g.nb += dm.nblk;
     g.periodic |= dm.p.geometry == MPSPH_PERIODIC;
     g.kappa2 &= dm.p.kappa == 2.0;
+    g.nwide += dm.d.wide ? 1 : 0;
   }
   // first-level reduction: rows of at most `chunk` block partials, never straddling domains
   const int64_t chunk = std::max<int64_t>(kRowBlocks, (blocks + kReduceBlocks - 1) / kReduceBlocks);
@@ -2387,8 +2400,9 @@ DomDev domain_device(const Domain &dm, const int *rbf_c, const float *rbf_o, con
   g.rowinv = std::ldexp(1.f, -g.rb);
   g.fx = std::ldexp(1.f, (int)g.xb);
   g.rfx = std::ldexp(1.f, g.rb + (int)g.xb);
-  g.fb = fixed_fraction(&p, dm.d);
+  g.fb = dm.d.fb;
   g.funit = std::ldexp(1.f, -g.fb);
+  g.wide = dm.d.wide ? 1 : 0;
   // background mesh: node spacing (hi - lo) / (n - 1) in cell units
   for (int a = 0; a < 3; ++a) {
     const int na = a < D ? std::max(p.grid_n[a], 2) : 2;
@@ -2583,8 +2597,13 @@ hipError_t order_state(mpsph_ctx *ctx, const WorkView &w, hipStream_t st, Launch
 
 bool dbg_context(const mpsph_ctx *ctx) { return ctx->dom[0].p.debug != 0; }
 
+bool any_wide(const mpsph_ctx *ctx) { return ctx->L.grp[0].nwide + ctx->L.grp[1].nwide > 0; }
+
+// The variant a step's launches take: the persistent and the staged ones serve narrow domains only.
+int launch_variant(const mpsph_ctx *ctx) { return any_wide(ctx) ? MPSPH_PAIRS_DEFAULT : ctx->variant; }
+
 // Whether the viscous pass closes the step (not the persistent launches: their blocks are not co-resident).
-bool fused_end(const mpsph_ctx *ctx) { return ctx->L.fused && ctx->variant != MPSPH_PAIRS_PERSISTENT; }
+bool fused_end(const mpsph_ctx *ctx) { return ctx->L.fused && launch_variant(ctx) != MPSPH_PAIRS_PERSISTENT; }
 
 // The step's end for a launch whose first domain is d0.
 StepEnd step_end(mpsph_ctx *ctx, int d0) {
@@ -2605,20 +2624,26 @@ void launch_group(mpsph_ctx *ctx, const WorkView &w, const Group &gr, int nreset
   if (hk) hk->end();
 }
 
+// A group with domains of both kinds takes a launch for the narrow ones and one for the wide ones.
 template <int D, int L_, bool PER>
 void launch_pass1_l(mpsph_ctx *ctx, const WorkView &w, const Group &gr, hipStream_t st) {
   const Layout &L = ctx->L;
   const bool dbg = ctx->dom[0].p.debug != 0;
-  auto kern = dbg ? pass_density_force<D, L_, PER, true, false>
-                  : (gr.kappa2 ? pass_density_force<D, L_, PER, false, true> : pass_density_force<D, L_, PER, false, false>);
+  auto kern = dbg ? pass_density_force<D, L_, PER, true, false, false>
+                  : (gr.kappa2 ? pass_density_force<D, L_, PER, false, true, false>
+                               : pass_density_force<D, L_, PER, false, false, false>);
   if constexpr (D == 3 && !PER)
-    if (ctx->variant == MPSPH_PAIRS_TILE) kern = dbg ? pass_density_force_tile<L_, true> : pass_density_force_tile<L_, false>;
-  kern<<<gr.nb, kBlock, 0, st>>>(
-      gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<int64_t>(L.stepctr), w.key, w.pos, w.fix, w.jaux,
-      w.cstart, w.acc,
-      dbg ? ctx->at<float>(L.rho) : nullptr, dbg ? ctx->at<float>(L.nn) : nullptr,
-      dbg ? ctx->at<float>(L.aabs) : nullptr, w.dts + (size_t)gr.d0 * kDtWords,
-      ctx->at<double>(L.metrics) + (size_t)gr.d0 * 32, ctx->at<double>(L.partials));
+    if (launch_variant(ctx) == MPSPH_PAIRS_TILE) kern = dbg ? pass_density_force_tile<L_, true> : pass_density_force_tile<L_, false>;
+  for (const bool wide : {false, true}) {
+    if (gr.nwide == (wide ? 0 : gr.nd)) continue;
+    if (wide) kern = dbg ? pass_density_force<D, L_, PER, true, false, true> : pass_density_force<D, L_, PER, false, false, true>;
+    kern<<<gr.nb, kBlock, 0, st>>>(
+        gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<int64_t>(L.stepctr), w.key, w.pos, w.fix, w.jaux,
+        w.cstart, w.acc,
+        dbg ? ctx->at<float>(L.rho) : nullptr, dbg ? ctx->at<float>(L.nn) : nullptr,
+        dbg ? ctx->at<float>(L.aabs) : nullptr, w.dts + (size_t)gr.d0 * kDtWords,
+        ctx->at<double>(L.metrics) + (size_t)gr.d0 * 32, ctx->at<double>(L.partials));
+  }
 }
 
 template <int D>
@@ -2639,13 +2664,21 @@ void launch_pass1(mpsph_ctx *ctx, const WorkView &w, const Group &gr, hipStream_
 template <int D, int L_, bool PER>
 void launch_pass2_l(mpsph_ctx *ctx, const WorkView &w, const Group &gr, hipStream_t st, float4 *at_o, float4 *v_o) {
   const Layout &L = ctx->L;
-  auto kern = fused_end(ctx) ? (gr.kappa2 ? pass_viscous_integrate<D, L_, PER, true, true> : pass_viscous_integrate<D, L_, PER, true, false>)
-                             : (gr.kappa2 ? pass_viscous_integrate<D, L_, PER, false, true> : pass_viscous_integrate<D, L_, PER, false, false>);
-  kern<<<gr.nb, kBlock, 0, st>>>(
-      gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, w.key, w.pos, w.fix, w.jaux, w.id, w.cstart, w.acc,
-      w.dts + (size_t)gr.d0 * kDtWords, ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
-      ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.s_cell), ctx->at<uint32_t>(L.counts), at_o, v_o,
-      ctx->at<double>(L.partials), step_end(ctx, gr.d0));
+  auto kern = fused_end(ctx) ? (gr.kappa2 ? pass_viscous_integrate<D, L_, PER, true, true, false>
+                                          : pass_viscous_integrate<D, L_, PER, true, false, false>)
+                             : (gr.kappa2 ? pass_viscous_integrate<D, L_, PER, false, true, false>
+                                          : pass_viscous_integrate<D, L_, PER, false, false, false>);
+  for (const bool wide : {false, true}) {
+    if (gr.nwide == (wide ? 0 : gr.nd)) continue;
+    if (wide)
+      kern = fused_end(ctx) ? pass_viscous_integrate<D, L_, PER, true, false, true>
+                            : pass_viscous_integrate<D, L_, PER, false, false, true>;
+    kern<<<gr.nb, kBlock, 0, st>>>(
+        gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, w.key, w.pos, w.fix, w.jaux, w.id, w.cstart, w.acc,
+        w.dts + (size_t)gr.d0 * kDtWords, ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
+        ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.s_cell), ctx->at<uint32_t>(L.counts), at_o,
+        v_o, ctx->at<double>(L.partials), step_end(ctx, gr.d0));
+  }
 }
 
 template <int D>
@@ -2747,10 +2780,10 @@ void launch_step_end(mpsph_ctx *ctx, const WorkView &w, hipStream_t st, EventHoo
 }
 
 // Whether one launch per kernel serves both dimension groups: batches of both dimensions, at the lanes of a
-// context that was never configured, without the debug exports (their kernels come one per dimension).
+// context that was never configured, without wide domains or the debug exports (their kernels come one per dimension).
 bool mixed_launch(const mpsph_ctx *ctx) {
   const Layout &L = ctx->L;
-  return L.grp[0].nb > 0 && L.grp[1].nb > 0 && ctx->variant == MPSPH_PAIRS_DEFAULT && !dbg_context(ctx) &&
+  return L.grp[0].nb > 0 && L.grp[1].nb > 0 && ctx->variant == MPSPH_PAIRS_DEFAULT && !any_wide(ctx) && !dbg_context(ctx) &&
          L.lanes == MPSPH_LANES && L.lanes3 == MPSPH_LANES_3D;
 }
 
@@ -2812,7 +2845,7 @@ int enqueue(mpsph_ctx *ctx, int nsteps, hipStream_t st, EventHook *hk) {
         else launch_group<3>(ctx, w, gr, nreset, st, hk);
         nreset = 0;
       }
-      if (ctx->variant == MPSPH_PAIRS_PERSISTENT) {
+      if (launch_variant(ctx) == MPSPH_PAIRS_PERSISTENT) {
         launch_pairs_queue(ctx, st, hk);
       } else {
         for (const Group &gr : L.grp) {
@@ -2909,7 +2942,7 @@ int replan(std::vector<Domain> &doms, int kdelta, int lanes, Layout *L, int kabs
     int rc = derive(&q, dm.n, dm.s0, &dm.d);
     if (rc) return rc;
     dm.d.rb = std::min(search_rows_rule(&q, dm.s0, dm.d) - shift, dm.d.k);
-    count_cells_of(&dm);
+    fit_grid(&dm);
   }
   return plan(doms, lanes, L);
 }
@@ -3193,9 +3226,11 @@ int loss_backward(GradRun &R, double lam, int m) {
     return fail(ctx, MPSPH_E_DEVICE);
   launch_group<D>(ctx, w, *R.gr, kDtSlots, R.st, nullptr);
   const int nbp = R.nbp;
-  const bool wide = R.lanes == MPSPH_ADJ_LANES_SMALL;
-  const auto density = wide ? loss_density<D, MPSPH_ADJ_LANES_SMALL> : loss_density<D, MPSPH_ADJ_LANES>;
-  const auto grad = wide ? loss_grad<D, MPSPH_ADJ_LANES_SMALL> : loss_grad<D, MPSPH_ADJ_LANES>;
+  const bool small = R.lanes == MPSPH_ADJ_LANES_SMALL, wide = dm.d.wide;
+  const auto density = small ? (wide ? loss_density<D, MPSPH_ADJ_LANES_SMALL, true> : loss_density<D, MPSPH_ADJ_LANES_SMALL, false>)
+                             : (wide ? loss_density<D, MPSPH_ADJ_LANES, true> : loss_density<D, MPSPH_ADJ_LANES, false>);
+  const auto grad = small ? (wide ? loss_grad<D, MPSPH_ADJ_LANES_SMALL, true> : loss_grad<D, MPSPH_ADJ_LANES_SMALL, false>)
+                          : (wide ? loss_grad<D, MPSPH_ADJ_LANES, true> : loss_grad<D, MPSPH_ADJ_LANES, false>);
   density<<<nbp, kBlock, 0, R.st>>>(dom, w.key, w.fix, w.jaux, w.cstart, R.at<float>(R.P.e),
                                                        R.at<double>(R.P.pb));
   loss_value<<<1, kLossThreads, 0, R.st>>>(R.at<double>(R.P.pb), nbp, 1.0 / n, lam, R.at<double>(R.P.out));
@@ -3222,9 +3257,11 @@ int step_backward(GradRun &R, int m, bool last, int64_t t) {
   adj_drift<D><<<R.nb1, kBlock, 0, R.st>>>(dom, tv, R.at<float4>(R.P.xbar), R.at<float4>(R.P.xacc),
                                            R.at<float4>(R.P.abv), R.at<float4>(R.P.vtb), R.at<float>(R.P.dtc), R.minslots(),
                                            R.at<double>(R.P.pa));
-  const bool wide = R.lanes == MPSPH_ADJ_LANES_SMALL;
-  const auto visc = wide ? adj_visc<D, MPSPH_ADJ_LANES_SMALL> : adj_visc<D, MPSPH_ADJ_LANES>;
-  const auto force = wide ? adj_force<D, MPSPH_ADJ_LANES_SMALL> : adj_force<D, MPSPH_ADJ_LANES>;
+  const bool small = R.lanes == MPSPH_ADJ_LANES_SMALL, wide = ctx->dom[0].d.wide;
+  const auto visc = small ? (wide ? adj_visc<D, MPSPH_ADJ_LANES_SMALL, true> : adj_visc<D, MPSPH_ADJ_LANES_SMALL, false>)
+                          : (wide ? adj_visc<D, MPSPH_ADJ_LANES, true> : adj_visc<D, MPSPH_ADJ_LANES, false>);
+  const auto force = small ? (wide ? adj_force<D, MPSPH_ADJ_LANES_SMALL, true> : adj_force<D, MPSPH_ADJ_LANES_SMALL, false>)
+                           : (wide ? adj_force<D, MPSPH_ADJ_LANES, true> : adj_force<D, MPSPH_ADJ_LANES, false>);
   visc<<<nbp, kBlock, 0, R.st>>>(dom, tv, R.at<float4>(R.P.abv), R.at<float4>(R.P.vtb),
                                                    R.at<float4>(R.P.xacc), R.at<float>(R.P.sbar),
                                                    R.at<float4>(R.P.fbar), R.at<float>(R.P.dtc), R.minslots(), R.argmin(),
@@ -3767,14 +3804,18 @@ int mpsph_debug_pairs(mpsph_ctx *ctx, int64_t cap, uint32_t *d_i, uint32_t *d_j,
   HIP_OK(hipMemsetAsync(cnt, 0, 8, ctx->stream));
   for (const Group &gr : L.grp) {
     if (gr.i1 <= gr.i0) continue;
-    auto kern = gr.D == 2 ? (gr.periodic ? dump_pairs<2, true> : dump_pairs<2, false>)
-                          : (gr.periodic ? dump_pairs<3, true> : dump_pairs<3, false>);
-    // two lanes per particle
-    kern<<<(int)((2 * (int64_t)(gr.i1 - gr.i0) + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
-        ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, gr.i0, gr.i1, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_fix),
-        ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart),
-        (unsigned long long)cap, d_i, d_j, cnt);
-    HIP_OK(hipGetLastError());
+    for (const bool wide : {false, true}) {
+      if (gr.nwide == (wide ? 0 : gr.nd)) continue;
+      auto kern = gr.D == 2 ? (wide ? (gr.periodic ? dump_pairs<2, true, true> : dump_pairs<2, false, true>)
+                                    : (gr.periodic ? dump_pairs<2, true, false> : dump_pairs<2, false, false>))
+                            : (wide ? (gr.periodic ? dump_pairs<3, true, true> : dump_pairs<3, false, true>)
+                                    : (gr.periodic ? dump_pairs<3, true, false> : dump_pairs<3, false, false>));
+      // two lanes per particle
+      kern<<<(int)((2 * (int64_t)(gr.i1 - gr.i0) + kBlock - 1) / kBlock), kBlock, 0, ctx->stream>>>(
+          ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, gr.i0, gr.i1, ctx->at<uint32_t>(L.w_key), ctx->at<float4>(L.w_fix),
+          ctx->at<uint32_t>(L.w_id), ctx->at<uint32_t>(L.cstart), (unsigned long long)cap, d_i, d_j, cnt);
+      HIP_OK(hipGetLastError());
+    }
   }
   unsigned long long total = 0;
   HIP_OK(hipMemcpyAsync(&total, cnt, 8, hipMemcpyDeviceToHost, ctx->stream));
@@ -3806,8 +3847,14 @@ int mpsph_set_field_coeff(mpsph_ctx *ctx, int32_t domain, const double *coeff) {
     dm.p.rbf_coeff = dm.rbf_coeff.data();
     return MPSPH_E_UNSUPPORTED;
   }
-  nd.rb = dm.d.rb;   // the search grid stays too
+  nd.rb = dm.d.rb;   // the search grid stays too, and the fixed-point coordinates of the last step
   nd.xb = dm.d.xb;
+  nd.fb = dm.d.fb;
+  nd.wide = wide_field(&q, nd);
+  if (nd.wide != dm.d.wide) {
+    ctx->L.grp[dm.p.dim - 2].nwide += nd.wide ? 1 : -1;
+    drop_graph(ctx);   // it holds the other passes
+  }
   dm.d = nd;
   const Layout &L = ctx->L;
   const DomDev dd = domain_device(dm, ctx->at<int>(L.rbf_c), ctx->at<float>(L.rbf_o), ctx->at<float>(L.rbf_k),

@@ -82,9 +82,10 @@ struct GridDev {
   uint32_t sly, slz; // 3D search rows in tiles of 2^sly x 2^slz (search_row)
   float rowinv;      // rows per cell, 2^-rb
   float fx, rfx;     // x sub-cells per cell and per row width
-  // fixed-point coordinates: multiples of 2^-fb cells, modulo 2^32 (any separation met is below 2^31)
+  // fixed-point coordinates: multiples of 2^-fb cells, modulo 2^32
   int fb;
   float funit;       // 2^-fb
+  int wide;          // separations may reach 2^31 of those units (PairPos)
 };
 
 // Target size field in cell units: s_cell(x) = s(x) / cs.

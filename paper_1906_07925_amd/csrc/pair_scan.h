@@ -81,6 +81,81 @@ __device__ __forceinline__ OwnRow own_row(const int *c, const FixedPos &p, const
   return o;
 }
 
+// A particle's position and its neighbours' as the pair loops take separations from them: in units of
+// `unit` cells, the same on every axis.
+// Narrow domains (every separation below 2^(31 - fb) cells) take the difference of the fixed-point
+// coordinates.  In wide ones (GridDev::wide) particles may be further apart, and that difference is the
+// separation but for a multiple of the coordinates' range: the neighbour's key, loaded as well, has the
+// cells that tell which.  Separations inside the range come out the same bit for bit.
+// PER: the launch may hold periodic boxes.
+template <int D, bool PER, bool WIDE>
+struct PairPos {
+  FixedPos x;
+  OwnRow row;
+  float h, unit;
+  BufRes rp;
+  struct Nb {
+    float4 p;
+  };
+  // Of particle i and the sorted arrays of its context.
+  __device__ __forceinline__ PairPos(const GridDev &g, uint32_t cellbase, int i, const uint32_t *__restrict__ wkey,
+                                     const float4 *__restrict__ wfix) {
+    int c[3];
+    unpack_key<D>(wkey[i] - cellbase, g, c);
+    const float4 p = wfix[i];
+    x = fixed_of(p);
+    row = own_row<D>(c, x, g);
+    h = p.w;
+    unit = g.funit;
+    rp = buf_res(wfix, 16, (uint32_t)g.n);
+  }
+  __device__ __forceinline__ Nb fetch(uint32_t j) const { return Nb{buf_f4(rp, j)}; }
+  // dz only in 3D
+  __device__ __forceinline__ void sep(const Nb &nb, float &dx, float &dy, float &dz) const {
+    dx = fixed_diff(x.x, nb.p.x);
+    dy = fixed_diff(x.y, nb.p.y);
+    if constexpr (D == 3) dz = fixed_diff(x.z, nb.p.z);
+  }
+};
+template <int D, bool PER>
+struct PairPos<D, PER, true> : PairPos<D, PER, false> {
+  using Narrow = PairPos<D, PER, false>;
+  int c[3];
+  const GridDev &g;
+  uint32_t cellbase;
+  BufRes rk;
+  struct Nb {
+    float4 p;
+    uint32_t key;
+  };
+  __device__ __forceinline__ PairPos(const GridDev &gr, uint32_t cb, int i, const uint32_t *__restrict__ wkey,
+                                     const float4 *__restrict__ wfix)
+      : Narrow(gr, cb, i, wkey, wfix), g(gr), cellbase(cb) {
+    unpack_key<D>(wkey[i] - cb, g, c);
+    rk = buf_res(wkey, 4, (uint32_t)g.n);
+  }
+  __device__ __forceinline__ Nb fetch(uint32_t j) const { return Nb{buf_f4(Narrow::rp, j), buf_u32(rk, j)}; }
+  __device__ __forceinline__ float axis(int ci, int cj, float t) const {
+    constexpr float kRange = 4294967296.f;   // of the coordinates, in their units
+    const float cell = (float)(1u << g.fb), P = (float)(g.gmax + 1) * cell;
+    int dc = ci - cj;
+    if (PER && g.geometry == 0) {            // the cells' minimum image, at most one cell from the particles'
+      const int p = g.gmax + 1;
+      dc = dc >= p / 2 ? dc - p : (dc < -(p / 2) ? dc + p : dc);
+    }
+    float d = fmaf(rintf(((float)dc * cell - t) * (1.f / kRange)), kRange, t);
+    if (PER && g.geometry == 0) d = d > 0.5f * P ? d - P : (d < -0.5f * P ? d + P : d);
+    return d;
+  }
+  __device__ __forceinline__ void sep(const Nb &nb, float &dx, float &dy, float &dz) const {
+    int cj[3];
+    unpack_key<D>(nb.key - cellbase, g, cj);
+    dx = axis(c[0], cj[0], fixed_diff(Narrow::x.x, nb.p.x));
+    dy = axis(c[1], cj[1], fixed_diff(Narrow::x.y, nb.p.y));
+    if constexpr (D == 3) dz = axis(c[2], cj[2], fixed_diff(Narrow::x.z, nb.p.z));
+  }
+};
+
 // Value of lane l - o (o < 16) within the lane's row of 16 lanes, through a DPP row shift (no
 // LDS round trip and no lane arithmetic); lanes l < o of the row get 0.  Used for prefix sums
 // inside groups of at most 16 lanes, where the lanes that would read across the group's start
