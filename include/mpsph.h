@@ -342,12 +342,25 @@ MPSPH_API int mpsph_debug_fields(mpsph_ctx *ctx, int32_t which, float *d_out);
  * rows are numbered in tiles of 2^ly x 2^lz rows, ly = min(4, k), lz = min(4, k):
  * row = (cy mod 2^ly) + 2^ly (cz mod 2^lz) + 2^(ly+lz) floor(cy / 2^ly) + 2^(k+lz) floor(cz / 2^lz)),
  * d_cell_start
- * (ncells + 1 uint32: index of the first sorted particle of each cell, last entry n) -- either
+ * (ncells + 1 uint32: the number of particles with a smaller key, last entry n, counted from the
+ * keys; the table that the step itself works on is that of mpsph_debug_search) -- either
  * may be NULL -- and the host values ncells (all domains) and cell_log2 (of domain 0).  The
  * two host values are available from creation on; the arrays need a completed step.
- * Synchronises. */
+ * Synchronises.  Errors: MPSPH_E_STATE, MPSPH_E_NOMEM (no host memory for the table), MPSPH_E_DEVICE. */
 MPSPH_API int mpsph_debug_cells(mpsph_ctx *ctx, uint32_t *d_key, uint32_t *d_cell_start, int64_t *ncells,
                       int32_t *cell_log2);
+
+/* Search structure of the last step, as the pair passes read it: d_start (ncells + 1 uint32: index of
+ * the first particle of each search cell in search order, last entry n) and d_order (n uint32: the load
+ * index of each particle in search order) -- either may be NULL -- and the host values ncells (search
+ * cells of all domains), rows_log2 and xsub_log2 (of domain 0, cell_log2 being k): a domain's search
+ * cell is xf + 2^(k+xsub) row with xf = cx 2^xsub + floor(ox 2^xsub); the rows are 2^rows cells wide along y
+ * and z (rows < 0: 2^-rows of them per cell), row = ry in 2D and in 3D numbered in tiles as in
+ * mpsph_debug_cells with k - rows in k's place.  Particles of one cell keep the order of the
+ * step before (of the load in the first step).  The host values are available from creation on; the
+ * arrays need a completed step.  Any output may be NULL.  Synchronises.  Errors: MPSPH_E_STATE, MPSPH_E_DEVICE. */
+MPSPH_API int mpsph_debug_search(mpsph_ctx *ctx, uint32_t *d_start, uint32_t *d_order, int64_t *ncells, int32_t *rows_log2,
+                                 int32_t *xsub_log2);
 
 /* Neighbour pairs of the last step (for testing at small n): the ordered pairs (i, j), j != i,
  * with |x_i - x_j| < kappa (h_i + h_j) / 2 at the start of that step, before the type mask is

@@ -3773,25 +3773,48 @@ int mpsph_debug_cells(mpsph_ctx *ctx, uint32_t *d_key, uint32_t *d_cell_start, i
   if ((d_key || d_cell_start) && (!ctx->loaded || ctx->steps_done == 0)) return MPSPH_E_STATE;
   const Layout &L = ctx->L;
   const int n = (int)L.n;
-  if (d_key && n > 0) {
-    // keys of the last step's start in load order: scatter w_key by w_id
-    std::vector<uint32_t> k(n), id(n), outk(n);
-    HIP_OK(hipMemcpyAsync(k.data(), ctx->at<uint32_t>(L.w_key), 4 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_OK(hipMemcpyAsync(id.data(), ctx->at<uint32_t>(L.w_id), 4 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
+  try {
+    std::vector<uint32_t> k(n), out;
+    if (n > 0 && (d_key || d_cell_start))
+      HIP_OK(hipMemcpyAsync(k.data(), ctx->at<uint32_t>(L.w_key), 4 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
+    if (d_key && n > 0) {
+      // keys of the last step's start in load order: scatter w_key by w_id
+      std::vector<uint32_t> id(n);
+      out.resize(n);
+      HIP_OK(hipMemcpyAsync(id.data(), ctx->at<uint32_t>(L.w_id), 4 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
+      HIP_OK(hipStreamSynchronize(ctx->stream));
+      for (int i = 0; i < n; ++i) out[id[i]] = k[i];
+      HIP_OK(hipMemcpyAsync(d_key, out.data(), 4 * (size_t)n, hipMemcpyHostToDevice, ctx->stream));
+    }
     HIP_OK(hipStreamSynchronize(ctx->stream));
-    for (int i = 0; i < n; ++i) outk[id[i]] = k[i];
-    HIP_OK(hipMemcpyAsync(d_key, outk.data(), 4 * (size_t)n, hipMemcpyHostToDevice, ctx->stream));
+    if (d_cell_start) {
+      // lower bound of every cell in the sorted keys, from the counts (the search order is another)
+      out.assign((size_t)L.ncells + 1, 0u);
+      for (int i = 0; i < n; ++i) ++out[(size_t)k[i] + 1];
+      for (size_t c = 0; c < (size_t)L.ncells; ++c) out[c + 1] += out[c];
+      HIP_OK(hipMemcpyAsync(d_cell_start, out.data(), 4 * out.size(), hipMemcpyHostToDevice, ctx->stream));
+      HIP_OK(hipStreamSynchronize(ctx->stream));
+    }
+  } catch (const std::bad_alloc &) {
+    return MPSPH_E_NOMEM;
   }
-  if (d_cell_start) {
-    // lower bound of every cell in the sorted keys, from the counts (the search order is another)
-    std::vector<uint32_t> k(n), start((size_t)L.ncells + 1, 0u);
-    HIP_OK(hipMemcpyAsync(k.data(), ctx->at<uint32_t>(L.w_key), 4 * (size_t)n, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_OK(hipStreamSynchronize(ctx->stream));
-    for (int i = 0; i < n; ++i) ++start[(size_t)k[i] + 1];
-    for (size_t c = 0; c < (size_t)L.ncells; ++c) start[c + 1] += start[c];
-    HIP_OK(hipMemcpyAsync(d_cell_start, start.data(), 4 * start.size(), hipMemcpyHostToDevice, ctx->stream));
-    HIP_OK(hipStreamSynchronize(ctx->stream));
-  }
+  return MPSPH_OK;
+}
+
+int mpsph_debug_search(mpsph_ctx *ctx, uint32_t *d_start, uint32_t *d_order, int64_t *ncells, int32_t *rows_log2,
+                       int32_t *xsub_log2) {
+  if (!ctx) return MPSPH_E_INVALID;
+  if (ctx->poisoned) return MPSPH_E_STATE;
+  const Layout &L = ctx->L;
+  const Derived &d = ctx->dom[L.internal[0]].d;
+  if (ncells) *ncells = L.scells;
+  if (rows_log2) *rows_log2 = d.rb;
+  if (xsub_log2) *xsub_log2 = d.xb;
+  if ((d_start || d_order) && (!ctx->loaded || ctx->steps_done == 0)) return MPSPH_E_STATE;
+  if (d_start)
+    HIP_OK(hipMemcpyAsync(d_start, ctx->at<uint32_t>(L.cstart), 4 * ((size_t)L.scells + 1), hipMemcpyDeviceToDevice, ctx->stream));
+  if (d_order)
+    HIP_OK(hipMemcpyAsync(d_order, ctx->at<uint32_t>(L.w_id), 4 * (size_t)L.n, hipMemcpyDeviceToDevice, ctx->stream));
   HIP_OK(hipStreamSynchronize(ctx->stream));
   return MPSPH_OK;
 }

@@ -95,6 +95,7 @@ def lib():
             "mpsph_store": (C.c_int, [V, V, V]),
             "mpsph_debug_fields": (C.c_int, [V, I32, V]),
             "mpsph_debug_cells": (C.c_int, [V, V, V, C.POINTER(I64), C.POINTER(I32)]),
+            "mpsph_debug_search": (C.c_int, [V, V, V, C.POINTER(I64), C.POINTER(I32), C.POINTER(I32)]),
             "mpsph_debug_pairs": (C.c_int, [V, I64, V, V, C.POINTER(I64)]),
             "mpsph_set_field_coeff": (C.c_int, [V, I32, C.POINTER(C.c_double)]),
             "mpsph_autotune": (C.c_int, [V, V, V, V, I32, I32, C.POINTER(I32), C.POINTER(I32)]),
@@ -365,6 +366,18 @@ class Relaxer:
         _check(lib().mpsph_debug_cells(self._ctx, C.c_void_p(keys.data_ptr()), C.c_void_p(cstart.data_ptr()),
                                        C.byref(nc), C.byref(k)), "mpsph_debug_cells")
         return keys, cstart, k.value
+
+    def search(self):
+        """Search table and order of the last step: first sorted particle of each search cell, load index of
+        each sorted particle, log2 of the rows' width in cells and of the x sub-cells per cell (domain 0)."""
+        torch = self._torch
+        nc, rb, xb = C.c_int64(0), C.c_int32(0), C.c_int32(0)
+        _check(lib().mpsph_debug_search(self._ctx, None, None, C.byref(nc), C.byref(rb), C.byref(xb)), "mpsph_debug_search")
+        start = torch.empty((nc.value + 1,), dtype=torch.int32, device="cuda")
+        order = torch.empty((self.n,), dtype=torch.int32, device="cuda")
+        _check(lib().mpsph_debug_search(self._ctx, C.c_void_p(start.data_ptr()), C.c_void_p(order.data_ptr()), None, None,
+                                        None), "mpsph_debug_search")
+        return start, order, rb.value, xb.value
 
     def pairs(self):
         """Ordered neighbour pairs (i, j) of the last step (load indices, unspecified order)."""
