@@ -2929,7 +2929,6 @@ int replan(std::vector<Domain> &doms, int kdelta, int lanes, Layout *L, int kabs
   std::stable_sort(doms.begin(), doms.end(), [](const Domain &a, const Domain &b) { return a.uidx < b.uidx; });
   for (auto &dm : doms) {
     mpsph_params q = dm.p;
-    int shift = 0;
     if (kabs >= 1) {
       q.cell_log2 = kabs;
     } else if (q.cell_log2 < 0) {
@@ -2937,11 +2936,10 @@ int replan(std::vector<Domain> &doms, int kdelta, int lanes, Layout *L, int kabs
       int rc = derive(&q, dm.n, dm.s0, &r);
       if (rc) return rc;
       q.cell_log2 = std::min(std::max(r.k + kdelta, 1), q.dim == 3 ? 8 : 12);
-      shift = q.cell_log2 - r.k;   // the rows follow the cells of the candidate
     }
     int rc = derive(&q, dm.n, dm.s0, &dm.d);
     if (rc) return rc;
-    dm.d.rb = std::min(search_rows_rule(&q, dm.s0, dm.d) - shift, dm.d.k);
+    dm.d.rb = search_rows_rule(&q, dm.s0, dm.d);   // by the cells alone: the same exponent gives the same rows again
     fit_grid(&dm);
   }
   return plan(doms, lanes, L);
