@@ -3767,24 +3767,17 @@ int mpsph_debug_fields(mpsph_ctx *ctx, int32_t which, float *d_out) {
   if (which == MPSPH_F_V) vec = ctx->at<float4>(L.v);
   if (which == MPSPH_F_DR) vec = ctx->at<float4>(L.v);
   if (which == MPSPH_F_VT || which == MPSPH_F_DR) {
-    std::vector<float> vs(L.ndom);
-    if (which == MPSPH_F_VT) {
-      // v~ = a dt1 / 2 (Eq. 26 after the velocity reset) with the domain's dt1; fixed particles
-      // carry a = 0
-      std::vector<double> m((size_t)L.ndom * 32);
-      HIP_OK(hipMemcpyAsync(m.data(), ctx->at<double>(L.metrics), m.size() * 8, hipMemcpyDeviceToHost, ctx->stream));
-      HIP_OK(hipStreamSynchronize(ctx->stream));
-      for (int d = 0; d < L.ndom; ++d) vs[d] = (float)(0.5 * m[(size_t)d * 32 + 16]);
-    } else {
-      // the drift is v dt2, the product the integrator forms (Eq. 28)
-      std::vector<float> slots((size_t)L.ndom * kDtWords);
-      HIP_OK(hipMemcpyAsync(slots.data(), ctx->at<float>(L.dtslots), slots.size() * 4, hipMemcpyDeviceToHost, ctx->stream));
-      HIP_OK(hipStreamSynchronize(ctx->stream));
-      for (int d = 0; d < L.ndom; ++d) {
-        float d1 = INFINITY;
-        for (int q = 0; q < kDtSlots; ++q) d1 = std::min(d1, slots[(size_t)d * kDtWords + q * kDtStride]);
-        vs[d] = (std::isfinite(d1) ? d1 : 0.f) * (float)dt2_factor(&ctx->dom[d].p);
-      }
+    // by the first time step of the exported step itself (the metrics may be another step's after a gradient):
+    // v~ = a dt1 / 2 (Eq. 26 after the velocity reset; fixed particles carry a = 0), and the drift is v dt2, the
+    // product the integrator forms (Eq. 28)
+    std::vector<float> vs(L.ndom), slots((size_t)L.ndom * kDtWords);
+    HIP_OK(hipMemcpyAsync(slots.data(), ctx->at<float>(L.dtslots), slots.size() * 4, hipMemcpyDeviceToHost, ctx->stream));
+    HIP_OK(hipStreamSynchronize(ctx->stream));
+    for (int d = 0; d < L.ndom; ++d) {
+      float d1 = INFINITY;
+      for (int q = 0; q < kDtSlots; ++q) d1 = std::min(d1, slots[(size_t)d * kDtWords + q * kDtStride]);
+      d1 = std::isfinite(d1) ? d1 : 0.f;
+      vs[d] = d1 * (which == MPSPH_F_VT ? 0.5f : (float)dt2_factor(&ctx->dom[d].p));
     }
     HIP_OK(hipMemcpyAsync(ctx->at<float>(L.vscale), vs.data(), vs.size() * 4, hipMemcpyHostToDevice, ctx->stream));
     vscale = ctx->at<float>(L.vscale);
