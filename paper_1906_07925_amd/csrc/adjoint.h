@@ -376,7 +376,8 @@ __global__ __launch_bounds__(kBlock) MPSPH_ADJ_OCCUPANCY void adj_visc(const Dom
       sbar[io] = sb;
       const float4 x0 = xacc[io];
       xacc[io] = make_float4(x0.x + xb[0], x0.y + xb[1], x0.z + xb[2], 0.f);
-      if (__float_as_uint(dtc[io]) == tmin) atomicMin(argmin, (uint32_t)io);
+      // tmin stays infinite where no particle has a force: none attains T1 then
+      if (tmin != kInfBits && __float_as_uint(dtc[io]) == tmin) atomicMin(argmin, (uint32_t)io);
       part[0] = t1;
     }
   }
