@@ -8,8 +8,9 @@
 // (cell_order_small does all of it in one block for small sets)
 // The arrival order inside a cell depends on timing; the gather that follows ranks each
 // particle among its cell's slots by index, so the final order is that of a stable sort by key.
-// Bound by launch latency up to ~10^5 particles and beyond by the table's bytes (12 per cell; at
-// most 4 cells per particle by the sub-cell rule, 8 by the size rule) and one atomic per particle.
+// Bound by launch latency up to ~10^5 particles and beyond by the table's bytes (12 per entry; at
+// most 4 entries per particle by the sub-cell rule, 8 per particle or 2^20 a domain by the rows) and one atomic per
+// particle.
 // Measured per step (scan, place and gather, against radix passes with their gather and gap fill):
 // 4096 particles 9.4 us against 54, 262,144 in 2D 25 against 98, 2M with 4M cells 56 against 133.
 #include "cells.h"

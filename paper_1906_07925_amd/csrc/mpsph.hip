@@ -2319,9 +2319,11 @@ int plan(std::vector<Domain> &doms, int lanes, Layout *out) {
     scells += dm.scells;
     blocks += dm.nblk;
     nrbf += (size_t)dm.p.n_rbf;
-    // thread indices of the pair kernels (particles x lanes) stay below 2^31
+    // thread indices of the pair kernels (particles x lanes) stay below 2^31, indices of the search table below 2^32:
+    // no larger than 2^(dim-1) times the cells (rows of half a cell) or 4 times the particles per domain
+    // (fit_search), it stays so within the other limits
     if (n > ((int64_t)1 << 30) || n * most >= ((int64_t)1 << 31) || cells > ((uint64_t)1 << 28) ||
-        blocks > ((int64_t)1 << 30))
+        scells >= ((uint64_t)1 << 32) || blocks > ((int64_t)1 << 30))
       return MPSPH_E_UNSUPPORTED;
     g.nd += 1;
     g.i1 = (int)n;
