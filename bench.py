@@ -290,9 +290,8 @@ def mesh_run(torch, M, W, steps: int = 50, warmup: int = 20):
     """The ball given as a level set and a graded field on a 48^3 background mesh, 2^20
     particles (random equal-mass init, 16 colours): step time and the state-gather kernel that
     interpolates the field (HIP events on the library stream, over 20 steps after the timed
-    ones).  Its algorithmic HBM bytes: per particle 28 read (permutation, offsets, flags, id)
-    and 28 written (key, position + h, flags, id), plus 4 per cell of the cell table it fills;
-    the 442 KB mesh stays in cache."""
+    ones).  Its algorithmic HBM bytes: per particle 40 read (slot, key, cell range, offsets, flags,
+    id) and 32 written (key, position + h, flags, id, source index); the 442 KB mesh stays in cache."""
     spec = W.levelset_ball(1 << 20)
     x, col, typ = W.make_state(dict(spec=spec, seed=W.BASE_SEED + 50, init="random", n_colours=16))
     n = x.shape[0]

@@ -238,7 +238,8 @@ MPSPH_API int mpsph_create_static(const mpsph_params *params, int64_t n, void *h
 
 /* Batched context: ndom >= 1 independent domains (one mpsph_params and particle count n[d]
  * each; 2D and 3D domains may be mixed; one debug flag for all) advanced together: each kernel
- * of a step is launched once for all domains of one dimension.  Particle arrays passed to
+ * of a step is launched once for all domains of one dimension (the gather and the pair passes once for both
+ * dimensions in a batch that was never configured nor tuned).  Particle arrays passed to
  * mpsph_load / mpsph_store / mpsph_debug_fields hold the domains one after the other in the
  * given order: domain d owns rows [u_d, u_d + n[d]) of the colour / type / scalar arrays,
  * u_d = n[0] + ... + n[d-1], and the n[d] x dim_d row-major block of positions (or vector
@@ -298,7 +299,8 @@ MPSPH_API int mpsph_set_pair_variant(mpsph_ctx *ctx, int32_t variant);
  * max(warm_steps, 1) steps (warm_steps <= 10000) are run untimed -- the best lane count changes
  * while a lattice relaxes, so warm_steps chooses the stage of the run to tune for -- and
  * probe_steps steps (1 .. 1000) are timed with HIP events on the context's stream.  The fastest candidate is kept and the state loaded into it (step counter
- * 0).  A library-owned workspace grows when a candidate needs more; with a caller workspace,
+ * 0).  Every candidate has one lane count for both dimensions, so a tuned or configured batch of 2D and 3D
+ * domains takes a launch per dimension.  A library-owned workspace grows when a candidate needs more; with a caller workspace,
  * candidates that do not fit are skipped.  Any captured step graph is dropped.  Outputs (may be
  * NULL): the chosen cell exponent of domain 0 and lanes.  Synchronises.
  * Errors: MPSPH_E_INVALID (arguments or state, as mpsph_load), MPSPH_E_STATE, MPSPH_E_DEVICE. */

@@ -17,11 +17,8 @@ size_t cell_count_words(uint32_t ncells);
 // Words of the tile sums, all zero before and after an order.
 size_t cell_sum_words(uint32_t ncells);
 
-// Counts the particles per cell from their keys: counts[key] over all particles and each
-// particle's arrival number in its cell (the bits of off[i].w).  counts is all zero on entry.
-hipError_t count_cells(const uint32_t *keys, float4 *off, uint32_t *counts, int n, hipStream_t stream);
-
-// From the counts and arrival numbers: the cell table cstart[c] = particles in cells below c
+// From the particles counted per cell (counts[key]) and each one's arrival number in its cell (the bits of
+// off[i].w): the cell table cstart[c] = particles in cells below c
 // (c <= ncells), and the particles grouped by cell, slots[s] for s in [cstart[c], cstart[c + 1])
 // naming those of cell c in an unspecified order.  Leaves counts all zero, or with keep as they are.
 // Enqueued on stream.

@@ -143,12 +143,6 @@ __global__ __launch_bounds__(256) void cell_place(const uint32_t *__restrict__ k
   if (at < (uint32_t)n) slots[at] = t;
 }
 
-__global__ __launch_bounds__(256) void cell_count(const uint32_t *__restrict__ keys, float4 *__restrict__ off,
-                                                  uint32_t *__restrict__ counts, int n) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < n) off[i].w = __uint_as_float(atomicAdd(&counts[keys[i]], 1u));
-}
-
 // Scan, place and clearing of a set whose table is one tile, in one block: a 16-byte load of the
 // counts per thread and up to kSmallItems particles.  Latency only: the particles' keys are loaded with
 // the counts, and what a second launch would cost (its start and the gap before it) is saved.
@@ -202,11 +196,6 @@ __global__ __launch_bounds__(kSmallThreads) void cell_order_small(const uint32_t
 
 size_t cell_sum_words(uint32_t ncells) { return ((size_t)ncells + kScanTile - 1) / kScanTile; }
 size_t cell_count_words(uint32_t ncells) { return cell_sum_words(ncells) * kScanTile; }
-
-hipError_t count_cells(const uint32_t *keys, float4 *off, uint32_t *counts, int n, hipStream_t stream) {
-  if (n > 0) cell_count<<<(n + 255) / 256, 256, 0, stream>>>(keys, off, counts, n);
-  return hipGetLastError();
-}
 
 hipError_t cell_order(const uint32_t *keys, const float4 *off, uint32_t *counts, uint32_t *sums, uint32_t *cstart,
                       uint32_t *slots, int n, uint32_t ncells, bool keep, hipStream_t stream, LaunchHook *hook) {

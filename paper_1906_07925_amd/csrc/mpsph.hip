@@ -2413,7 +2413,6 @@ DomDev domain_device(const Domain &dm, const int *rbf_c, const float *rbf_o, con
   g.k = dm.d.k;
   g.n = (int)(dm.off + dm.n);
   g.gmax = dm.d.gmax;
-  g.xmask = (uint32_t)dm.d.gmax;
   g.geometry = p.geometry;
   for (int a = 0; a < 3; ++a) {
     double Xhi = a < D ? (p.hi[a] - p.lo[a]) * ics : 0.0;

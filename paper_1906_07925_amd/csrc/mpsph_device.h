@@ -61,7 +61,6 @@ struct GridDev {
   int k;             // cells per axis = 2^k
   int n;             // particles of the context (bound of every sorted index)
   int gmax;          // 2^k - 1
-  uint32_t xmask;    // 2^k - 1
   int geometry;      // MPSPH_BOX | MPSPH_ANNULUS | MPSPH_BALL
   int whi_c[3];      // upper box wall: cell + offset (lower wall is cell 0, offset 0)
   float whi_o[3];

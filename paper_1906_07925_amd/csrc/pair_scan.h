@@ -303,7 +303,7 @@ __device__ __forceinline__ uint32_t scan_group_table(uint32_t self, int sub, uin
         beyond = true;
         q -= nrows;
       }
-      const int qz = (int)(((float)q + 0.5f) * inv_ny);   // q / ny (q, ny < 2^12)
+      const int qz = (int)(((float)q + 0.5f) * inv_ny);   // q / ny, exact for nz = 1 and for ny, nz <= 2^9
       const int cz = z0 + qz, cy = y0 + (q - qz * ny);
       float ez = 0.f;
       if constexpr (D == 3) {
