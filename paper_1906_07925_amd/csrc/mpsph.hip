@@ -593,20 +593,13 @@ __device__ __forceinline__ void density_force_block(int lb, uint2 *rowtab, TileL
   });
 }
 
-// Whether logical block lb belongs to a wide domain (WIDE) or to a narrow one; the same in every thread of the block.
-template <bool WIDE>
-__device__ __forceinline__ bool block_of_kind(const DomDev *doms, int ndom, int lb) {
-  return (doms[domain_of_block(doms, ndom, lb)].g.wide != 0) == WIDE;
-}
-
-// The pass over the logical blocks b0 + [0, gridDim.x) (one dimension group), of its wide domains (WIDE) or of the
-// narrow ones.  In 3D the wide pass holds one round of loads: with a second one it spilled 7 to 21 registers.
+// The pass over the logical blocks b0 + [0, gridDim.x) (of one dimension group, of wide domains or of narrow ones).  In
+// 3D the wide pass holds one round of loads: with a second one it spilled 7 to 21 registers.
 template <int D, int L, bool PER, bool DBG, bool K2, bool WIDE>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_density_force(int b0, MPSPH_PASS1_PARAMS) {
   __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  const int lb = b0 + xcd_block(blockIdx.x, gridDim.x);
-  if (!block_of_kind<WIDE>(doms, ndom, lb)) return;
-  density_force_block<D, L, PER, DBG, false, !WIDE || D == 2, K2, WIDE>(lb, rowtab, nullptr, MPSPH_PASS1_ARGS);
+  density_force_block<D, L, PER, DBG, false, !WIDE || D == 2, K2, WIDE>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab, nullptr,
+                                                                        MPSPH_PASS1_ARGS);
 }
 
 // The staged copy limits a CU to 4 blocks (4 waves per SIMD), which the register budget follows.
@@ -1087,9 +1080,8 @@ __device__ __forceinline__ void viscous_integrate_block(int lb, uint2 *rowtab, M
 template <int D, int L, bool PER, bool END, bool K2, bool WIDE>
 __global__ __launch_bounds__(kBlock) MPSPH_PAIR_OCCUPANCY void pass_viscous_integrate(int b0, MPSPH_PASS2_PARAMS) {
   __shared__ __align__(16) uint2 rowtab[row_table_rows<L>() * row_table_stride<L>()];
-  const int lb = b0 + xcd_block(blockIdx.x, gridDim.x);
-  if (!block_of_kind<WIDE>(doms, ndom, lb)) return;
-  viscous_integrate_block<D, L, PER, !WIDE || D == 2, END, K2, WIDE>(lb, rowtab, MPSPH_PASS2_ARGS);
+  viscous_integrate_block<D, L, PER, !WIDE || D == 2, END, K2, WIDE>(b0 + xcd_block(blockIdx.x, gridDim.x), rowtab,
+                                                                     MPSPH_PASS2_ARGS);
 }
 
 // Row-table entries of a launch that serves 2D blocks at L lanes and 3D blocks at L3.
@@ -2663,7 +2655,21 @@ void launch_group(mpsph_ctx *ctx, const WorkView &w, const Group &gr, int nreset
   if (hk) hk->end();
 }
 
-// A group with domains of both kinds takes a launch for the narrow ones and one for the wide ones.
+// launch(wide, b0, nb) for the blocks of every run of domains of one kind, wide or narrow, of a group: as a rule the
+// whole group.
+template <typename F>
+void launch_kinds(const mpsph_ctx *ctx, const Group &gr, F &&launch) {
+  if (gr.nwide == 0 || gr.nwide == gr.nd) {
+    launch(gr.nwide > 0, gr.b0, gr.nb);
+    return;
+  }
+  for (int d = gr.d0, e; d < gr.d0 + gr.nd; d = e) {
+    int nb = 0;
+    for (e = d; e < gr.d0 + gr.nd && ctx->dom[e].d.wide == ctx->dom[d].d.wide; ++e) nb += ctx->dom[e].nblk;
+    launch(ctx->dom[d].d.wide, ctx->dom[d].blk0, nb);
+  }
+}
+
 template <int D, int L_, bool PER>
 void launch_pass1_l(mpsph_ctx *ctx, const WorkView &w, const Group &gr, hipStream_t st) {
   const Layout &L = ctx->L;
@@ -2673,16 +2679,15 @@ void launch_pass1_l(mpsph_ctx *ctx, const WorkView &w, const Group &gr, hipStrea
                                : pass_density_force<D, L_, PER, false, false, false>);
   if constexpr (D == 3 && !PER)
     if (launch_variant(ctx) == MPSPH_PAIRS_TILE) kern = dbg ? pass_density_force_tile<L_, true> : pass_density_force_tile<L_, false>;
-  for (const bool wide : {false, true}) {
-    if (gr.nwide == (wide ? 0 : gr.nd)) continue;
-    if (wide) kern = dbg ? pass_density_force<D, L_, PER, true, false, true> : pass_density_force<D, L_, PER, false, false, true>;
-    kern<<<gr.nb, kBlock, 0, st>>>(
-        gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<int64_t>(L.stepctr), w.key, w.pos, w.fix, w.jaux,
+  const auto kwide = dbg ? pass_density_force<D, L_, PER, true, false, true> : pass_density_force<D, L_, PER, false, false, true>;
+  launch_kinds(ctx, gr, [&](bool wide, int b0, int nb) {
+    (wide ? kwide : kern)<<<nb, kBlock, 0, st>>>(
+        b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, ctx->at<int64_t>(L.stepctr), w.key, w.pos, w.fix, w.jaux,
         w.cstart, w.acc,
         dbg ? ctx->at<float>(L.rho) : nullptr, dbg ? ctx->at<float>(L.nn) : nullptr,
         dbg ? ctx->at<float>(L.aabs) : nullptr, w.dts + (size_t)gr.d0 * kDtWords,
         ctx->at<double>(L.metrics) + (size_t)gr.d0 * 32, ctx->at<double>(L.partials));
-  }
+  });
 }
 
 template <int D>
@@ -2707,17 +2712,15 @@ void launch_pass2_l(mpsph_ctx *ctx, const WorkView &w, const Group &gr, hipStrea
                                           : pass_viscous_integrate<D, L_, PER, true, false, false>)
                              : (gr.kappa2 ? pass_viscous_integrate<D, L_, PER, false, true, false>
                                           : pass_viscous_integrate<D, L_, PER, false, false, false>);
-  for (const bool wide : {false, true}) {
-    if (gr.nwide == (wide ? 0 : gr.nd)) continue;
-    if (wide)
-      kern = fused_end(ctx) ? pass_viscous_integrate<D, L_, PER, true, false, true>
-                            : pass_viscous_integrate<D, L_, PER, false, false, true>;
-    kern<<<gr.nb, kBlock, 0, st>>>(
-        gr.b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, w.key, w.pos, w.fix, w.jaux, w.id, w.cstart, w.acc,
+  const auto kwide = fused_end(ctx) ? pass_viscous_integrate<D, L_, PER, true, false, true>
+                                    : pass_viscous_integrate<D, L_, PER, false, false, true>;
+  launch_kinds(ctx, gr, [&](bool wide, int b0, int nb) {
+    (wide ? kwide : kern)<<<nb, kBlock, 0, st>>>(
+        b0, ctx->at<DomDev>(L.doms) + gr.d0, gr.nd, w.key, w.pos, w.fix, w.jaux, w.id, w.cstart, w.acc,
         w.dts + (size_t)gr.d0 * kDtWords, ctx->at<uint32_t>(L.s_key), ctx->at<float4>(L.s_off),
         ctx->at<uint32_t>(L.s_ct), ctx->at<uint32_t>(L.s_id), ctx->at<uint32_t>(L.s_cell), ctx->at<uint32_t>(L.counts), at_o,
         v_o, ctx->at<double>(L.partials), step_end(ctx, gr.d0));
-  }
+  });
 }
 
 template <int D>
