@@ -101,10 +101,11 @@ def _mean_spacing(s, dim):
     return (f ** (1 - dim)).sum() / (f ** -dim).sum()
 
 
-@pytest.mark.parametrize("dim,kind,a,b", [(3, "sphere", 0.25, 30), (3, "sphere", 0.05, 60), (3, "sphere", 0.25, 100),
-                                          (2, "sphere", 0.05, 200), (3, "mesh", 30.0, 40), (3, "rbf", 0.05, 3)])
+@pytest.mark.parametrize("dim,kind,a,b", [(3, "sphere", 0.25, 60), (3, "sphere", 0.05, 60), (3, "sphere", 0.25, 100),
+                                          (2, "sphere", 0.05, 200), (3, "mesh", 30.0, 40), (3, "rbf", 0.04, 4)])
 def test_rows_follow_the_mean_cut_off_of_steep_fields(dim, kind, a, b):
-    """Rows between the mean cut-off over 1.05 and half of it, as everywhere."""
+    """Rows between the mean cut-off over 1.05 and half of it, as everywhere (fields whose mean a coarse lattice misses by
+    more than 1.6)."""
     torch = pytest.importorskip("torch")
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
